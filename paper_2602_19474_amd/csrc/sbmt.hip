@@ -2641,7 +2641,8 @@ static PreArgs pre_args(const PreLayout& PL, char* w, double a, double b, double
   P.rtbase = PL.off_rtbase ? (int64_t*)(w + PL.off_rtbase) : nullptr;
   P.cbase = PL.off_cbase ? (int32_t*)(w + PL.off_cbase) : nullptr;
   P.cblk = PL.off_cblk ? (int64_t*)(w + PL.off_cblk) : nullptr;
-  P.cstore = PL.off_cstore ? (uint32_t*)(w + PL.off_cstore) : nullptr;
+  P.citem = PL.off_citem ? (uint64_t*)(w + PL.off_citem) : nullptr;
+  P.cstore = PL.off_cstore ? (PreCut*)(w + PL.off_cstore) : nullptr;
   P.ccap = PL.off_cstore ? PL.ccap : 0;
   return P;
 }
@@ -2767,12 +2768,14 @@ sbmt_status sbmt_preprocess_mesh(sbmt_handle h, const sbmt_image* img, double a,
   hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(kScanThreads), 0, s, sh);
   hipLaunchKernelGGL(k_scan_apply, dim3(PL.L.nblk), dim3(kScanThreads), 0, s, sh);
   hipLaunchKernelGGL(k_pre_mesh_count, dim3((unsigned)nqb), dim3(256), 0, s, src, P, sh);
+  hipLaunchKernelGGL(k_pre_mesh_probe_plain, resident(&k_pre_mesh_probe_plain), dim3(256), 0, s, src, P, sh);
   hipLaunchKernelGGL(k_pre_mesh_probe_owner, resident(&k_pre_mesh_probe_owner), dim3(256), 0, s, src, P, sh);
   // slots of the cut triangles' kept outputs, then their counts
   if (PL.ncblk > 0x7fffffffLL) return SBMT_E_INVALID_ARG;
   hipLaunchKernelGGL(k_pre_cut_count, dim3((unsigned)PL.ncblk), dim3(256), 0, s, P, sh);
   hipLaunchKernelGGL(k_pre_cut_top, dim3(1), dim3(256), 0, s, P, PL.ncblk);
   hipLaunchKernelGGL(k_pre_cut_apply, dim3((unsigned)PL.ncblk), dim3(256), 0, s, P, sh);
+  hipLaunchKernelGGL(k_pre_cut_make, resident(&k_pre_cut_make), dim3(256), 0, s, src, P);
   hipLaunchKernelGGL(k_pre_mesh_cut_count, resident(&k_pre_mesh_cut_count), dim3(256), 0, s, src, P, sh);
   // the output counts per row segment and their offsets
   hipLaunchKernelGGL(k_pre_mesh_segsum, dim3((unsigned)nqb), dim3(256), 0, s, src, P, sh);
@@ -2784,11 +2787,10 @@ sbmt_status sbmt_preprocess_mesh(sbmt_handle h, const sbmt_image* img, double a,
   hipLaunchKernelGGL(k_pre_vscan_top, dim3(1), dim3(256), 0, s, P, PL.nvblk);
   hipLaunchKernelGGL(k_pre_vscan_apply, dim3((unsigned)PL.nvblk), dim3(256), 0, s, P);
   hipLaunchKernelGGL(k_pre_mesh_vbase, dim3((unsigned)nqb), dim3(256), 0, s, src, P, sh);
-  hipLaunchKernelGGL(k_pre_mesh_edge_verts, resident(&k_pre_mesh_edge_verts), dim3(256), 0, s, src, P);
-  hipLaunchKernelGGL(k_pre_mesh_inner_verts, resident(&k_pre_mesh_inner_verts), dim3(256), 0, s, src, P);
   hipLaunchKernelGGL(k_pre_mesh_triangles, dim3((unsigned)nqb), dim3(256), 0, s, src, P, sh);
   hipLaunchKernelGGL(k_pre_mesh_whole_tris, resident(&k_pre_mesh_whole_tris), dim3(256), 0, s, src, P);
-  hipLaunchKernelGGL(k_pre_mesh_cut_tris, resident(&k_pre_mesh_cut_tris), dim3(256), 0, s, src, P);
+  hipLaunchKernelGGL(k_pre_cut_write, resident(&k_pre_cut_write), dim3(256), 0, s, P);
+  hipLaunchKernelGGL(k_pre_mesh_cut_rest, resident(&k_pre_mesh_cut_rest), dim3(256), 0, s, src, P);
   hipLaunchKernelGGL(k_pre_mesh_sizes, dim3(1), dim3(1), 0, s, P, sh, out2);
   if (hipGetLastError() != hipSuccess) return SBMT_E_DEVICE;
   if ((st = pre_read_sizes(h, out2, 8, counts, s)) != SBMT_OK) return st;
