@@ -2617,6 +2617,7 @@ static PreArgs pre_args(const PreLayout& PL, char* w, double a, double b, double
   P.on_polyline = nullptr;
   P.tris = nullptr;
   P.vcap = P.tcap = 0;
+  P.wshift = pre_wave_words(PL.L.g[0]);
   P.mid = (uint8_t*)(w + PL.off_mid);
   P.split = (int32_t*)(w + PL.off_split);
   P.flags = (uint8_t*)(w + PL.off_flags);
@@ -2640,7 +2641,8 @@ static PreArgs pre_args(const PreLayout& PL, char* w, double a, double b, double
   P.tlist = PL.off_tlist ? (int32_t*)(w + PL.off_tlist) : nullptr;
   P.rtbase = PL.off_rtbase ? (int64_t*)(w + PL.off_rtbase) : nullptr;
   P.cbase = PL.off_cbase ? (int32_t*)(w + PL.off_cbase) : nullptr;
-  P.cblk = PL.off_cblk ? (int64_t*)(w + PL.off_cblk) : nullptr;
+  P.touched = PL.off_touched ? (uint32_t*)(w + PL.off_touched) : nullptr;
+  P.ntouched = PL.ntouched;
   P.citem = PL.off_citem ? (uint64_t*)(w + PL.off_citem) : nullptr;
   P.cstore = PL.off_cstore ? (PreCut*)(w + PL.off_cstore) : nullptr;
   P.ccap = PL.off_cstore ? PL.ccap : 0;
@@ -2653,7 +2655,7 @@ static sbmt_status pre_launch_grid(const PreLayout& PL, const OneSrc& src, const
   const Geo& g = PL.L.g[0];
   const int64_t ncb = PL.L.tab[PL.L.n];
   const int64_t nseg = PL.L.nseg;
-  const int64_t nwb = ((int64_t)(g.CH + 1) * g.wpr + 255) / 256;  // raster words of rows -1 .. CH - 1
+  const int64_t nwb = pre_word_blocks(g);  // raster words of rows -1 .. CH - 1
   const int nchunk = (g.NI + kPreQuad - 1) / kPreQuad;  // 1024-vertex chunks of a lattice row
   const int64_t nqb = (nseg + 3) / 4;                    // four row segments (waves) per block
   if ((int64_t)g.NK * nchunk > 0x7fffffffLL) return SBMT_E_INVALID_ARG;
@@ -2750,8 +2752,7 @@ sbmt_status sbmt_preprocess_mesh(sbmt_handle h, const sbmt_image* img, double a,
   if ((st = pre_launch_grid(PL, src, P, sh, w, false, s)) != SBMT_OK) return st;
   const int64_t nqb = (PL.L.nseg + 3) / 4;
   int64_t* out2 = (int64_t*)(w + PL.off_out2);
-  const Geo& gg = PL.L.g[0];
-  const int64_t nwb = ((int64_t)(gg.CH + 1) * gg.wpr + 255) / 256;
+  const int64_t nwb = pre_word_blocks(g);
   // grid-stride passes: as many blocks as run at once on the device
   const int ncu = std::max(h->cus, 1);
   auto resident = [ncu](auto* k) {
@@ -2763,18 +2764,14 @@ sbmt_status sbmt_preprocess_mesh(sbmt_handle h, const sbmt_image* img, double a,
   };
   hipLaunchKernelGGL(k_pre_mesh_touch, dim3((unsigned)nwb), dim3(256), 0, s, src, P);
   // the touched owners' list: counts per row segment, their offsets, the list
-  hipLaunchKernelGGL(k_pre_mesh_tcount, dim3((unsigned)nqb), dim3(256), 0, s, src, P, sh);
+  hipLaunchKernelGGL(k_pre_mesh_tcount, dim3((unsigned)((PL.L.nseg + 255) / 256)), dim3(256), 0, s, P, sh);
   hipLaunchKernelGGL(k_scan_reduce, dim3(PL.L.nblk), dim3(kScanThreads), 0, s, sh);
   hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(kScanThreads), 0, s, sh);
   hipLaunchKernelGGL(k_scan_apply, dim3(PL.L.nblk), dim3(kScanThreads), 0, s, sh);
   hipLaunchKernelGGL(k_pre_mesh_count, dim3((unsigned)nqb), dim3(256), 0, s, src, P, sh);
   hipLaunchKernelGGL(k_pre_mesh_probe_plain, resident(&k_pre_mesh_probe_plain), dim3(256), 0, s, src, P, sh);
   hipLaunchKernelGGL(k_pre_mesh_probe_owner, resident(&k_pre_mesh_probe_owner), dim3(256), 0, s, src, P, sh);
-  // slots of the cut triangles' kept outputs, then their counts
-  if (PL.ncblk > 0x7fffffffLL) return SBMT_E_INVALID_ARG;
-  hipLaunchKernelGGL(k_pre_cut_count, dim3((unsigned)PL.ncblk), dim3(256), 0, s, P, sh);
-  hipLaunchKernelGGL(k_pre_cut_top, dim3(1), dim3(256), 0, s, P, PL.ncblk);
-  hipLaunchKernelGGL(k_pre_cut_apply, dim3((unsigned)PL.ncblk), dim3(256), 0, s, P, sh);
+  hipLaunchKernelGGL(k_pre_cut_slots, resident(&k_pre_cut_slots), dim3(256), 0, s, P, sh);
   hipLaunchKernelGGL(k_pre_cut_make, resident(&k_pre_cut_make), dim3(256), 0, s, src, P);
   hipLaunchKernelGGL(k_pre_mesh_cut_count, resident(&k_pre_mesh_cut_count), dim3(256), 0, s, src, P, sh);
   // the output counts per row segment and their offsets

@@ -46,11 +46,14 @@ struct PreArgs {
   uint8_t* on_polyline;  // per vertex: sits on a polyline vertex
   int32_t* tris;         // [triangles][3]
   int64_t vcap, tcap;
+  int wshift;            // log2 of the raster words a wave enumerates the polyline from (pre_wave_words)
   uint8_t* mid;          // per midpoint: 1 if a lattice vertex snapped to it
-  uint8_t* flags;        // per lattice vertex: bits 0-2 owned side E0-E2 split, 3 moved, 4 claimed, 5 snapped, 6 touched (mesh)
+  uint8_t* flags;        // per lattice vertex: bits 0-2 owned side E0-E2 split, 3 moved, 4 claimed, 5 snapped
   int32_t* split;        // [NK NI][3]: midpoint splitting side E0, E1, E2 (written where split)
   int64_t* ins_base;     // [NK NI]: first inserted vertex of the owner (written where it has one)
   int64_t* counts;       // [8 + 512]: [2] error, [3] touched owners, [4] cut triangles, [5] some not kept (mesh); from kPreTally 256 counters of snapped, then of repelled vertices
+  uint32_t* touched;     // [NK][8 NCB]: bit per owner, those a segment can reach (mesh)
+  int64_t ntouched;      // its words
   int32_t* snap_mid;     // [NK NI]: the polyline vertex a lattice vertex snapped to (written where snapped)
   // retriangulation of the grid (sbmt_preprocess_mesh)
   uint32_t* rcount;      // [NK NI]: per-owner counts (pre_rc_*)
@@ -71,14 +74,13 @@ struct PreArgs {
   int64_t* rtbase;       // [NK NI]: a touched owner's first output triangle
   int64_t* vbsum;        // per block of kPreVScan grid vertices: used count, then base
   int64_t* nused;        // [1]: grid vertices in the mesh
-  // the cut grid triangles, numbered in list order (slots)
-  int32_t* cbase;        // [NK NI]: cut grid triangles of the touched owners before list position t
-  int64_t* cblk;         // per block of kPreVScan list positions: cut count, then base
+  // the cut grid triangles, numbered (slots)
+  int32_t* cbase;        // [NK NI]: first slot of list position t
   uint64_t* citem;       // [ccap]: list position * 4 + grid triangle of each slot
   PreCut* cstore;        // [ccap]: its output, kept by the count pass for the triangle pass
   int64_t ccap;
 };
-constexpr int kPreVScan = 16384;  // grid vertices (list positions) per block of the compaction (cut) scan
+constexpr int kPreVScan = 16384;  // grid vertices per block of the compaction scan
 constexpr uint8_t kPreMoved = 8;
 constexpr int kPreTally = 8;
 constexpr int kPreCounts = kPreTally + 512;
@@ -205,8 +207,8 @@ __global__ void __launch_bounds__(256) k_pre_lattice(OneSrc src, PreArgs P, int 
   }
 }
 
-// The polyline is enumerated from the coarse raster: thread t of the launch
-// takes stored word t of coarse rows -1 .. CH - 1.  Bit j concerns column
+// The polyline is enumerated from the coarse raster, stored words of coarse rows
+// -1 .. CH - 1: a wave takes 2^wshift of them, one a lane.  Bit j concerns column
 // C = C0 + j: dh marks the horizontal midpoint (R, C)-(R, C+1) as a polyline
 // vertex, dv the vertical one (R, C)-(R+1, C), and cur / c1 / bel / b1 hold
 // the samples (R, C), (R, C+1), (R+1, C), (R+1, C+1) of dual cell (R, C).
@@ -219,9 +221,10 @@ __device__ __forceinline__ void pre_word_at(const Geo& g, uint32_t t, int& R, in
   R = (int)r - 1;
   C0 = 32 * (int)(t - r * (uint32_t)g.wpr) - kRingC;
 }
-__device__ __forceinline__ bool pre_word(const Img& d, const Geo& g, PreWord& W) {
-  const uint32_t t = blockIdx.x * 256u + threadIdx.x;
-  if (t >= (uint32_t)((g.CH + 1) * g.wpr)) return false;
+__device__ __forceinline__ uint32_t pre_wave_word0(const PreArgs& P) { return (blockIdx.x * 4u + (threadIdx.x >> 6)) << P.wshift; }
+__device__ __forceinline__ bool pre_word(const Img& d, const Geo& g, const PreArgs& P, PreWord& W) {
+  const uint32_t lane = threadIdx.x & 63u, t = pre_wave_word0(P) + lane;
+  if (lane >> P.wshift || t >= (uint32_t)((g.CH + 1) * g.wpr)) return false;
   pre_word_at(g, t, W.R, W.C0);
   const int w = (W.C0 + kRingC) >> 5;
   const uint32_t* row = d.bits + (int64_t)(W.R + kRing) * g.wpr;
@@ -239,16 +242,28 @@ __device__ __forceinline__ void pre_mid_xy(const Geo& g, int R, int C, int vt, d
   y = (double)g.s * R + sample_off(g) + (vt ? 0.5 * g.s : 0.0);
 }
 // The items the lanes of a wave found (set bits of m0, then of m1; each with a
-// 4-bit payload per bit read from pay0 / pay1 when given) are gathered in LDS
-// and dealt round-robin to the lanes: f(source lane, which mask, bit, payload).
+// 4-bit payload per bit read from pay0 / pay1 when given) are gathered in LDS,
+// those that keep(source lane, which mask, bit) refuses dropped when given, and
+// dealt round-robin to the lanes: f(source lane, which mask, bit, payload).
 // Every thread of the block must call it (it synchronises the block).
 constexpr int kPreDeal = 64 * 64;
-template <class Pay, class F>
-__device__ __forceinline__ void pre_deal(uint16_t (*lds)[kPreDeal], uint32_t m0, uint32_t m1, Pay pay, F f) {
+struct PreKeepAll {
+  static constexpr bool all = true;
+  __device__ __forceinline__ bool operator()(int, int, int) const { return true; }
+};
+template <class F>
+struct PreKeepIf {
+  static constexpr bool all = false;
+  F f;
+  __device__ __forceinline__ bool operator()(int sl, int which, int bit) const { return f(sl, which, bit); }
+};
+template <class Pay, class F, class Keep = PreKeepAll>
+__device__ __forceinline__ void pre_deal(uint16_t (*lds)[kPreDeal], uint32_t m0, uint32_t m1, Pay pay, F f,
+                                         Keep keep = Keep()) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int n = __builtin_popcount(m0) + __builtin_popcount(m1);
   const int incl = wave_incl_scan_dpp(n);
-  const int total = __builtin_amdgcn_readlane(incl, 63);
+  int total = __builtin_amdgcn_readlane(incl, 63);
   int pos = incl - n;
   for (int which = 0; which < 2; ++which) {
     uint32_t m = which ? m1 : m0;
@@ -259,6 +274,21 @@ __device__ __forceinline__ void pre_deal(uint16_t (*lds)[kPreDeal], uint32_t m0,
     }
   }
   __syncthreads();
+  if constexpr (!Keep::all) {
+    // the kept ones to the front, in place (a write stays behind the reads)
+    int kept = 0;
+    for (int q = 0; q < total; q += 64) {  // uniform per wave
+      const uint32_t e = q + lane < total ? lds[wv][q + lane] : 0u;
+      const bool k = q + lane < total && keep((int)(e & 63u), (int)((e >> 6) & 1u), (int)((e >> 7) & 31u));
+      const unsigned long long bal = __ballot(k);
+      if (k) lds[wv][kept + lanes_below(bal)] = (uint16_t)e;
+      kept += (int)__popcll(bal);
+    }
+    total = kept;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
   for (int q = lane; q < total; q += 64) {
     const uint32_t e = lds[wv][q];
     f((int)(e & 63u), (int)((e >> 6) & 1u), (int)((e >> 7) & 31u), e >> 12);
@@ -300,9 +330,9 @@ __global__ void __launch_bounds__(256) k_pre_snap(OneSrc src, PreArgs P) {
   const Img& d = src.d;
   const Geo g = d.g;
   PreWord W;
-  const bool on = P.a > 0.0 && pre_word(d, g, W);
+  const bool on = P.a > 0.0 && pre_word(d, g, P, W);
   int n = 0;
-  const uint32_t base = blockIdx.x * 256u + (threadIdx.x & ~63u);
+  const uint32_t base = pre_wave_word0(P);
   pre_deal(lds, on ? W.dh : 0u, on ? W.dv : 0u, pre_no_pay, [&](int sl, int vt, int j, uint32_t) {
     int R, C0;
     pre_word_at(g, base + sl, R, C0);
@@ -321,6 +351,7 @@ __device__ int pre_repel_seg(const PreArgs& P, const Geo& g, double px, double p
   const double x0 = __builtin_fmin(px, qx) - cw, x1 = __builtin_fmax(px, qx) + cw;
   const double y0 = __builtin_fmin(py, qy) - cw, y1 = __builtin_fmax(py, qy) + cw;
   int n = 0;
+  const double ex = qx - px, ey = qy - py, reach = P.c * P.c * (ex * ex + ey * ey) * (1.0 + 1e-9);
   for (int k = max(0, pre_row_floor(g, y0)); k <= min(g.NK - 1, pre_row_floor(g, y1)); ++k) {
     const double yv = lat_y(g, k);
     if (yv < y0 || yv > y1) continue;
@@ -328,6 +359,8 @@ __device__ int pre_repel_seg(const PreArgs& P, const Geo& g, double px, double p
     for (int i = i0; i <= i1; ++i) {
       const double xv = lat_x(g, pre_lat_X(g, k, i));
       if (xv < x0 || xv > x1) continue;
+      const double off = ex * (yv - py) - ey * (xv - px);
+      if (off * off > reach) continue;  // farther from the line than c
       const int64_t v = (int64_t)k * g.NI + i;
       if (P.flags[v] & kPreSnapped) continue;
       double t;
@@ -349,10 +382,10 @@ __global__ void __launch_bounds__(256) k_pre_repel(OneSrc src, PreArgs P) {
   const Img& d = src.d;
   const Geo g = d.g;
   PreWord W;
-  const bool on = P.c > 0.0 && pre_word(d, g, W);
+  const bool on = P.c > 0.0 && pre_word(d, g, P, W);
   const uint32_t cells = on ? (W.dh | W.dv | (W.cur ^ W.b1)) : 0u;  // dual cells whose samples differ
   int n = 0;
-  const uint32_t base = blockIdx.x * 256u + (threadIdx.x & ~63u);
+  const uint32_t base = pre_wave_word0(P);
   auto cs_of = [&](int, int j) {
     return ((W.cur >> j) & 1u) | (((W.c1 >> j) & 1u) << 1) | (((W.b1 >> j) & 1u) << 2) | (((W.bel >> j) & 1u) << 3);
   };
@@ -384,9 +417,11 @@ __device__ void pre_split_one(const PreArgs& P, const Geo& g, int64_t id, double
   int64_t hv = -1;
   int he = 0;
   for (int k = max(0, pre_row_floor(g, my - r) - 1); k <= min(g.NK - 1, pre_row_floor(g, my + r)); ++k) {
-    const double yu = lat_y(g, k), z = pre_col(g, k, mx);
+    const double yu = lat_y(g, k), yd = lat_y(g, k + 1), z = pre_col(g, k, mx);
     const int o = k & 1;
     for (int e = 0; e < 3; ++e) {
+      const double yw = e == 0 ? yu : yd;
+      if (my < yu - r || my > yw + r) continue;
       // side e of owner i spans columns [i, i+1], [i-1/2, i], [i, i+1/2]
       const double lo = e == 0 ? z - 1.0 - rr : (e == 1 ? z - rr : z - 0.5 - rr);
       const double hi = e == 0 ? z + rr : (e == 1 ? z + 0.5 + rr : z + rr);
@@ -395,12 +430,11 @@ __device__ void pre_split_one(const PreArgs& P, const Geo& g, int64_t id, double
         if (!pre_edge_live(g, k, i, e)) continue;
         const int iw = e == 0 ? i + 1 : (e == 1 ? i + o - 1 : i + o);
         const double xu = lat_x(g, pre_lat_X(g, k, i)), xw = lat_x(g, pre_lat_X(g, kw, iw));
-        const double yw = e == 0 ? yu : lat_y(g, kw);
-        if (mx < __builtin_fmin(xu, xw) - r || mx > __builtin_fmax(xu, xw) + r || my < __builtin_fmin(yu, yw) - r ||
-            my > __builtin_fmax(yu, yw) + r)
-          continue;
+        if (mx < __builtin_fmin(xu, xw) - r || mx > __builtin_fmax(xu, xw) + r) continue;
         const int64_t v = (int64_t)k * g.NI + i;
         const double2 U = V[v], Wv = V[(int64_t)kw * g.NI + iw];
+        const double dx = Wv.x - U.x, dy = Wv.y - U.y, off = dx * (my - U.y) - dy * (mx - U.x);
+        if (off * off > P.b * P.b * (dx * dx + dy * dy) * (1.0 + 1e-9)) continue;  // farther from the line than b
         // both orientations, as the side's two triangles see it
         if (seg_dist_d(mx, my, U.x, U.y, Wv.x, Wv.y, nullptr) < P.b ||
             seg_dist_d(mx, my, Wv.x, Wv.y, U.x, U.y, nullptr) < P.b) {
@@ -416,22 +450,33 @@ __device__ void pre_split_one(const PreArgs& P, const Geo& g, int64_t id, double
   if (pre_flag_or(P.flags, hv, 1u << he) & (1u << he)) pre_error(P);  // a side split twice
   P.split[3 * hv + he] = (int32_t)id;
 }
+// Two in three polyline vertices have been snapped to: they are dropped before
+// the deal, so that the lanes that look for sides are full, and a side's
+// distance is taken only where the vertex lies within b of its line (together
+// 125 -> 106 us on 4000 x 3000).
 __global__ void __launch_bounds__(256) k_pre_split(OneSrc src, PreArgs P) {
   __shared__ uint16_t lds[4][kPreDeal];
   const Img& d = src.d;
   const Geo g = d.g;
   PreWord W;
-  const bool on = P.b > 0.0 && pre_word(d, g, W);
-  const uint32_t base = blockIdx.x * 256u + (threadIdx.x & ~63u);
+  const bool on = P.b > 0.0 && pre_word(d, g, P, W);
+  const uint32_t base = pre_wave_word0(P);
+  auto id_of = [&](int sl, int vt, int j, int& R, int& C) {
+    pre_word_at(g, base + sl, R, C);
+    C += j;
+    return mid_id(g, R, C, vt);
+  };
+  auto free_one = [&](int sl, int vt, int j) {
+    int R, C;
+    return P.mid[id_of(sl, vt, j, R, C)] == 0;  // no lattice vertex sits on it
+  };
   pre_deal(lds, on ? W.dh : 0u, on ? W.dv : 0u, pre_no_pay, [&](int sl, int vt, int j, uint32_t) {
-    int R, C0;
-    pre_word_at(g, base + sl, R, C0);
-    const int64_t id = mid_id(g, R, C0 + j, vt);
-    if (P.mid[id]) return;  // a lattice vertex sits on it
+    int R, C;
+    const int64_t id = id_of(sl, vt, j, R, C);
     double mx, my;
-    pre_mid_xy(g, R, C0 + j, vt, mx, my);
+    pre_mid_xy(g, R, C, vt, mx, my);
     pre_split_one(P, g, id, mx, my);
-  });
+  }, PreKeepIf<decltype(free_one)>{free_one});
 }
 
 // Slots of owner (k, i): Tb = [v, vdr, vdl] has sides E2 of v, E0 of vdl, E1 of
@@ -662,6 +707,8 @@ __global__ void k_pre_clear(PreArgs P, int64_t nmid) {
   for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < (nmid + 3) / 4; q += (int64_t)gridDim.x * blockDim.x)
     m4[q] = 0u;
   for (int q = threadIdx.x; blockIdx.x == 0 && q < kPreCounts; q += blockDim.x) P.counts[q] = 0;
+  for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < P.ntouched; q += (int64_t)gridDim.x * blockDim.x)
+    P.touched[q] = 0u;
   if (P.used) {
     uint32_t* u4 = reinterpret_cast<uint32_t*>(P.used);  // padded to 256 bytes
     for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < (P.usedcap + 3) / 4;
@@ -1376,27 +1423,36 @@ __device__ int pre_tri_mesh(const Img& d, const Geo& g, const PreArgs& P, const 
 // inserted vertices stay within it), meets the segment's box.  An unmarked
 // owner is quiet: its triangles are uncut, its corners are lattice vertices
 // off the polyline, and the inside label of the owner vertex decides them.
-constexpr uint32_t kPreTouched = 64;
+// One bit per owner: a row of a segment's box is one or two words, set without
+// a look at what is there (a byte each, loaded and set by an atomic, took
+// 520 us on 0.9 M segments; now 100 us).
 __device__ void pre_touch_seg(const PreArgs& P, const Geo& g, double px, double py, double qx, double qy) {
   const double r = widen(P.a + P.b) + 1e-9, hx = pre_hx(g);
   const double x0 = fmin(px, qx) - r, x1 = fmax(px, qx) + r, y0 = fmin(py, qy) - r, y1 = fmax(py, qy) + r;
   for (int k = max(0, pre_row_floor(g, y0) - 1); k <= min(g.NK - 1, pre_row_floor(g, y1)); ++k) {
     const int ia = max(0, (int)__builtin_floor(pre_col(g, k, x0 - hx)));
     const int ib = min(g.NI - 1, (int)__builtin_floor(pre_col(g, k, x1 + 0.5 * hx)) + 1);
-    for (int i = ia; i <= ib; ++i) {
-      const int64_t v = (int64_t)k * g.NI + i;
-      if (!(P.flags[v] & kPreTouched)) pre_flag_or(P.flags, v, kPreTouched);
+    if (ia > ib) continue;
+    uint32_t* const row = P.touched + (int64_t)k * 8 * g.NCB;
+    for (int w = ia >> 5; w <= ib >> 5; ++w) {
+      const uint32_t lo = w == ia >> 5 ? ~0u << (ia & 31) : ~0u, hi = w == ib >> 5 ? ~0u >> (31 - (ib & 31)) : ~0u;
+      atomicOr(row + w, lo & hi);
     }
   }
+}
+// The touched bits of the 64 owners of step j of a row segment.
+__device__ __forceinline__ unsigned long long pre_touched64(const PreArgs& P, int64_t seg, int j) {
+  const uint2 w = reinterpret_cast<const uint2*>(P.touched)[4 * seg + j];
+  return (unsigned long long)w.x | ((unsigned long long)w.y << 32);
 }
 __global__ void __launch_bounds__(256) k_pre_mesh_touch(OneSrc src, PreArgs P) {
   __shared__ uint16_t lds[4][kPreDeal];
   const Img& d = src.d;
   const Geo g = d.g;
   PreWord W;
-  const bool on = pre_word(d, g, W);
+  const bool on = pre_word(d, g, P, W);
   const uint32_t cells = on ? (W.dh | W.dv | (W.cur ^ W.b1)) : 0u;
-  const uint32_t base = blockIdx.x * 256u + (threadIdx.x & ~63u);
+  const uint32_t base = pre_wave_word0(P);
   auto cs_of = [&](int, int j) {
     return ((W.cur >> j) & 1u) | (((W.c1 >> j) & 1u) << 1) | (((W.b1 >> j) & 1u) << 2) | (((W.bel >> j) & 1u) << 3);
   };
@@ -1559,22 +1615,16 @@ __device__ void pre_owner_triangle(const Img& d, const Geo& g, const PreArgs& P,
 }
 
 
-// The touched owners of each row segment (their list offsets come from a scan).
-__global__ void __launch_bounds__(256) k_pre_mesh_tcount(OneSrc src, PreArgs P, Shared sh) {
-  const Geo g = src.d.g;
-  int64_t seg;
-  int k, i0;
-  if (!pre_segment(g, sh, seg, k, i0)) return;  // wave-uniform
-  const int lane = threadIdx.x & 63;
+// The touched owners of each row segment (their list offsets come from a
+// scan), a thread each.
+__global__ void __launch_bounds__(256) k_pre_mesh_tcount(PreArgs P, Shared sh) {
+  const int64_t seg = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (seg >= sh.nseg) return;
   int n = 0;
-  for (int j = 0; j < 4; ++j) {
-    const int i = i0 + 64 * j + lane;
-    n += (int)__popcll(__ballot(i < g.NI && (P.flags[(int64_t)k * g.NI + i] & kPreTouched)));
-  }
-  if (lane == 0) {
-    sh.seg_cnt[seg] = make_int4(n, 0, 0, 0);
-    sh.seg_slow[seg] = 0ull;
-  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) n += (int)__popcll(pre_touched64(P, seg, j));
+  sh.seg_cnt[seg] = make_int4(n, 0, 0, 0);
+  sh.seg_slow[seg] = 0ull;
 }
 
 // Quiet owners in place (their slots kept whole when the owner vertex is
@@ -1592,8 +1642,8 @@ __global__ void __launch_bounds__(256) k_pre_mesh_count(OneSrc src, PreArgs P, S
   for (int j = 0; j < 4; ++j) {
     const int i = i0 + 64 * j + lane;
     const int64_t v = (int64_t)k * g.NI + i;
-    const bool touched = i < g.NI && (P.flags[v] & kPreTouched);
-    const unsigned long long bal = __ballot(touched);
+    const unsigned long long bal = pre_touched64(P, seg, j);  // uniform
+    const bool touched = (bal >> lane) & 1ull;
     if (touched) {
       P.tlist[at + lanes_below(bal)] = (int32_t)v;
       P.rcount[v] = 0u;
@@ -1850,56 +1900,88 @@ __global__ void __launch_bounds__(256, 4) k_pre_mesh_probe_plain(OneSrc src, Pre
   }
 }
 
-__device__ void pre_mesh_probe(const Img& d, const Geo& g, const PreArgs& P, int64_t t) {
-  int kk, ii;
-  pre_tl_owner(g, P, t, kk, ii);
-  const int64_t v = (int64_t)kk * g.NI + ii;
-  const PreSlots S = pre_owner_slots(P, g, kk, ii);
-  PreBits Bits;
-  pre_owner_bits(d, g, P, kk, ii, Bits);
-  uint32_t rt = 0, rc = 0;
-  for (int z = 0; z < 4; ++z) {
-    PreGT Tg;
-    if (!pre_owner_tri(P, g, kk, ii, S, z, Tg)) continue;
-    int nt = 0;
-    PrePt in;
-    bool cut = false;
-    const int nin = pre_tri_mesh<true>(d, g, P, Tg, [&](const PrePt& a, const PrePt& b, const PrePt& c, int) {
-      ++nt;
-      if (a.kind == 0) P.used[a.a] = 1;
-      if (b.kind == 0) P.used[b.a] = 1;
-      if (c.kind == 0) P.used[c.a] = 1;
-    }, &in, &cut, &Bits);
-    if (nin < 0) {  // cut: k_pre_mesh_cut_count takes it
-      rt |= 1u << (28 + z);
-      continue;
-    }
-    rt |= (uint32_t)nt << (6 * z);  // uncut: at most one triangle, no inner vertex
-    rc += (uint32_t)nt << 19;
-  }
-  for (int e = 0; e < 8; ++e) {
-    PreGV A, B;
-    if (!pre_edge_slot(P, g, kk, ii, S, e, A, B)) continue;
-    int c = 0;
-    pre_edge_crossings(d, g, A, B, [&](const PreSeg&, double) { ++c; }, &Bits);
-    if (c > 3) {  // more crossings of one grid edge than the numbering holds
-      pre_error(P);
-      c = 3;
-    }
-    rc |= (uint32_t)c << (2 * e);
-  }
-  P.rtri[v] = rt;
-  P.rcount[v] = rc;
-}
+// The owners marked kPreTodo, 64 at a time: a lane per grid triangle, then a
+// lane per edge slot in two rounds, their results added up in LDS.  A lane that
+// goes through an owner's four triangles and eight edges waits for twelve
+// chains of loads in turn: 95 us for the few owners of a 1024 x 1024 image,
+// where this takes 33 (on the 8192 x 8192 one, with waves enough to hide them,
+// 400 against 520 us).
+constexpr int kPreOwners = 64;
 __global__ void __launch_bounds__(256) k_pre_mesh_probe_owner(OneSrc src, PreArgs P, Shared sh) {
-  __shared__ int64_t dl[512];
+  __shared__ int32_t dl[256 + kPreOwners];
+  __shared__ uint32_t rt[kPreOwners], rc[kPreOwners];
   __shared__ int nd;
   const Img& d = src.d;
   const Geo g = d.g;
   if (threadIdx.x == 0) nd = 0;
   __syncthreads();
-  pre_dense(sh.seg_off[sh.nseg].x, dl, &nd, [&](int64_t t) -> bool { return P.rtri[P.tlist[t]] == kPreTodo; },
-            [&](int64_t t) { pre_mesh_probe(d, g, P, t); });
+  const int64_t T = sh.seg_off[sh.nseg].x;
+  for (int64_t base = (int64_t)blockIdx.x * 256;; base += (int64_t)gridDim.x * 256) {
+    const bool more = base < T;  // uniform
+    const int64_t it = base + threadIdx.x;
+    if (more && it < T) {
+      const int32_t v = P.tlist[it];
+      if (P.rtri[v] == kPreTodo) dl[atomicAdd(&nd, 1)] = v;
+    }
+    __syncthreads();
+    int m = nd;
+    while (m >= kPreOwners || (!more && m > 0)) {  // uniform
+      const int take = min(m, kPreOwners);
+      const int32_t* const own = dl + (m - take);
+      if (threadIdx.x < kPreOwners) rt[threadIdx.x] = rc[threadIdx.x] = 0u;
+      __syncthreads();
+      for (int r = 0; r < 3; ++r) {
+        const int q = r == 0 ? (int)threadIdx.x >> 2 : (((r - 1) * 256 + (int)threadIdx.x) >> 3);
+        if (q >= take) continue;
+        const uint32_t v = (uint32_t)own[q];
+        const int kk = (int)(v / (uint32_t)g.NI), ii = (int)(v - (uint32_t)kk * (uint32_t)g.NI);
+        const PreSlots S = pre_owner_slots(P, g, kk, ii);
+        PreBits Bits;
+        pre_owner_bits(d, g, P, kk, ii, Bits);
+        if (r == 0) {
+          const int z = (int)threadIdx.x & 3;
+          PreGT Tg;
+          if (!pre_owner_tri(P, g, kk, ii, S, z, Tg)) continue;
+          int nt = 0;
+          PrePt in;
+          bool cut = false;
+          const int nin = pre_tri_mesh<true>(d, g, P, Tg, [&](const PrePt& a, const PrePt& b, const PrePt& c, int) {
+            ++nt;
+            if (a.kind == 0) P.used[a.a] = 1;
+            if (b.kind == 0) P.used[b.a] = 1;
+            if (c.kind == 0) P.used[c.a] = 1;
+          }, &in, &cut, &Bits);
+          if (nin < 0) {  // cut: the cut triangles' pass takes it
+            atomicOr(&rt[q], 1u << (28 + z));
+          } else {  // uncut: at most one triangle, no inner vertex
+            atomicOr(&rt[q], (uint32_t)nt << (6 * z));
+            atomicAdd(&rc[q], (uint32_t)nt << 19);
+          }
+        } else {
+          const int e = (int)threadIdx.x & 7;
+          PreGV A, B;
+          if (!pre_edge_slot(P, g, kk, ii, S, e, A, B)) continue;
+          int c = 0;
+          pre_edge_crossings(d, g, A, B, [&](const PreSeg&, double) { ++c; }, &Bits);
+          if (c > 3) {  // more crossings of one grid edge than the numbering holds
+            pre_error(P);
+            c = 3;
+          }
+          atomicAdd(&rc[q], (uint32_t)c << (2 * e));
+        }
+      }
+      __syncthreads();
+      if ((int)threadIdx.x < take) {
+        P.rtri[own[threadIdx.x]] = rt[threadIdx.x];
+        P.rcount[own[threadIdx.x]] = rc[threadIdx.x];
+      }
+      m -= take;
+      __syncthreads();
+    }
+    if (threadIdx.x == 0) nd = m;
+    __syncthreads();
+    if (!more) break;
+  }
 }
 
 // Exclusive scan in place of nblk block counts by one block; *total (if
@@ -1926,52 +2008,42 @@ __device__ __forceinline__ void pre_scan_blocks(int64_t* a, int64_t nblk, int64_
   }
   if (total && threadIdx.x == 0) *total = run;
 }
-// Slots of the cut grid triangles' kept outputs, in list order: per block of
-// kPreVScan list positions the number of cut triangles; one block scans the
-// counts; then each position's first slot (clamped to 32 bits: slots past the
-// capacity keep nothing).
-__device__ __forceinline__ int pre_cut_n(const PreArgs& P, int64_t t, int64_t T) {
-  return t < T ? __builtin_popcount(P.rtri[P.tlist[t]] >> 28) : 0;
-}
-__global__ void __launch_bounds__(256) k_pre_cut_count(PreArgs P, Shared sh) {
+// Slots of the cut grid triangles, kPreCScan list positions to a block: the
+// block's triangles take a run of slots with one atomic (which run does not
+// matter: a slot is only a place to keep a triangle's output), and each
+// position its first one (clamped to 32 bits: slots past the room keep
+// nothing).
+constexpr int kPreCScan = 2048;
+__global__ void __launch_bounds__(256) k_pre_cut_slots(PreArgs P, Shared sh) {
   __shared__ int part[4];
+  __shared__ int64_t base;
   const int64_t T = sh.seg_off[sh.nseg].x;
-  const int64_t b0 = (int64_t)blockIdx.x * kPreVScan;
-  int n = 0;
-  for (int q = threadIdx.x; q < kPreVScan && b0 < T; q += 256) n += pre_cut_n(P, b0 + q, T);
-  const int w = __builtin_amdgcn_readlane(wave_incl_scan_dpp(n), 63);
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = w;
-  __syncthreads();
-  if (threadIdx.x == 0) P.cblk[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
-}
-__global__ void __launch_bounds__(256) k_pre_cut_top(PreArgs P, int64_t nblk) {
-  pre_scan_blocks(P.cblk, nblk, &P.counts[4]);
-}
-__global__ void __launch_bounds__(256) k_pre_cut_apply(PreArgs P, Shared sh) {
-  __shared__ int part[4];
-  const int64_t T = sh.seg_off[sh.nseg].x;
-  const int64_t b0 = (int64_t)blockIdx.x * kPreVScan;
-  if (b0 >= T) return;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  int64_t run = P.cblk[blockIdx.x];
-  for (int c = 0; c < kPreVScan / 256; ++c) {
-    const int64_t t = b0 + (int64_t)c * 256 + threadIdx.x;
-    const uint32_t cuts = t < T ? P.rtri[P.tlist[t]] >> 28 : 0u;
-    const int n = __builtin_popcount(cuts);
+  constexpr int kPer = kPreCScan / 256;
+  for (int64_t b0 = (int64_t)blockIdx.x * kPreCScan; b0 < T; b0 += (int64_t)gridDim.x * kPreCScan) {
+    uint32_t cuts[kPer];
+    int n = 0;
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const int64_t t = b0 + q * 256 + threadIdx.x;
+      cuts[q] = t < T ? P.rtri[P.tlist[t]] >> 28 : 0u;
+      n += __builtin_popcount(cuts[q]);
+    }
     const int incl = wave_incl_scan_dpp(n);
     if (lane == 63) part[wv] = incl;
     __syncthreads();
-    int before = 0, tot = 0;
+    if (threadIdx.x == 0)
+      base = (int64_t)atomicAdd((unsigned long long*)&P.counts[4], (unsigned long long)(part[0] + part[1] + part[2] + part[3]));
+    __syncthreads();
+    int64_t slot = base + incl - n;
+    for (int w = 0; w < wv; ++w) slot += part[w];
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const int tw = part[w];
-      before += w < wv ? tw : 0;
-      tot += tw;
+    for (int q = 0; q < kPer; ++q) {
+      const int64_t t = b0 + q * 256 + threadIdx.x;
+      if (t < T) P.cbase[t] = (int32_t)min(slot, (int64_t)0x7fffffff);
+      for (uint32_t c = cuts[q]; c; c &= c - 1, ++slot)
+        if (slot < P.ccap) P.citem[slot] = 4 * (uint64_t)t + __builtin_ctz(c);
     }
-    int64_t slot = run + before + incl - n;
-    if (t < T) P.cbase[t] = (int32_t)min(slot, (int64_t)0x7fffffff);
-    for (uint32_t c = cuts; c && slot < P.ccap; c &= c - 1) P.citem[slot++] = 4 * (uint64_t)t + __builtin_ctz(c);
-    run += tot;
     __syncthreads();
   }
 }
@@ -2294,7 +2366,7 @@ __global__ void __launch_bounds__(256) k_pre_mesh_triangles(OneSrc src, PreArgs 
     const int n = pre_rc_tris(rc);
     const int incl = wave_incl_scan_dpp(n);
     const int tot = __builtin_amdgcn_readlane(incl, 63);  // at most 4 * 64 (a touched owner: 4 * 63)
-    const bool touched = n > 0 && (P.flags[v] & kPreTouched);
+    const bool touched = n > 0 && ((pre_touched64(P, seg, j) >> lane) & 1ull);
     if (touched) P.rtbase[v] = t0 + acc + (incl - n);
     for (int b = 0; b < tot; b += 128) {  // uniform
       full[wv][lane] = full[wv][lane + 64] = 0;
@@ -2570,8 +2642,9 @@ struct PreLayout {
   size_t off_mid, off_split, off_flags, off_ins, off_counts, off_out, off_snap, total;
   // the retriangulation (sbmt_preprocess_mesh): grid on-polyline bytes, per-owner counts and bases, sizes
   size_t off_onp, off_rcount, off_rtri, off_rbase, off_out2, off_gverts, off_used, off_vmap, off_vbsum, off_nused,
-      off_tlist, off_rtbase, off_cbase, off_cblk, off_citem, off_cstore;
-  int64_t ncblk, ccap;  // blocks of the cut scan; cut triangles whose output is kept
+      off_tlist, off_rtbase, off_cbase, off_citem, off_cstore, off_touched;
+  int64_t ccap;      // cut triangles whose output is kept
+  int64_t ntouched;  // words of the touched bits
   int64_t nvblk;  // blocks of the vertex compaction scan
   int64_t nmid, nown;
 };
@@ -2599,8 +2672,8 @@ static sbmt_status pre_layout(const sbmt_image* img, bool need_ptr, PreLayout* P
   off = align256(off + (size_t)P->nown * 4);
   P->off_onp = P->off_rcount = P->off_rtri = P->off_rbase = P->off_out2 = 0;
   P->off_gverts = P->off_used = P->off_vmap = P->off_vbsum = P->off_nused = P->off_tlist = P->off_rtbase = 0;
-  P->off_cbase = P->off_cblk = P->off_citem = P->off_cstore = 0;
-  P->ncblk = P->ccap = 0;
+  P->off_cbase = P->off_citem = P->off_cstore = P->off_touched = 0;
+  P->ccap = P->ntouched = 0;
   P->nvblk = 0;
   if (mesh) {
     P->off_onp = off;
@@ -2630,12 +2703,12 @@ static sbmt_status pre_layout(const sbmt_image* img, bool need_ptr, PreLayout* P
     P->off_rtbase = off;
     off = align256(off + (size_t)P->nown * 8);
     // kept outputs of the cut grid triangles: room for one in 16 owners
-    P->ncblk = (P->nown + kPreVScan - 1) / kPreVScan;
+    P->ntouched = 8LL * g.NK * g.NCB;
+    P->off_touched = off;
+    off = align256(off + (size_t)P->ntouched * 4);
     P->ccap = std::max<int64_t>(65536, P->nown / 16);
     P->off_cbase = off;
     off = align256(off + (size_t)P->nown * 4);
-    P->off_cblk = off;
-    off = align256(off + (size_t)P->ncblk * 8);
     P->off_citem = off;
     off = align256(off + (size_t)P->ccap * 8);
     P->off_cstore = off;
@@ -2643,6 +2716,21 @@ static sbmt_status pre_layout(const sbmt_image* img, bool need_ptr, PreLayout* P
   }
   P->total = off;
   return SBMT_OK;
+}
+// Words a wave enumerates the polyline from (log2): full waves of items where
+// there are words enough for four waves per SIMD, else fewer words, down to
+// four, so that the waves of a small image run side by side and not their items
+// one after the other (Step 3 on 4000 x 3000 with 64 words a wave, 1.5 blocks
+// per CU: 106 us; with 16: 45 us).
+static int pre_wave_words(const Geo& g) {
+  const int64_t words = (int64_t)(g.CH + 1) * g.wpr;
+  int shift = 2;
+  while (shift < 6 && (words >> (shift + 1)) >= 4096) ++shift;
+  return shift;
+}
+static int64_t pre_word_blocks(const Geo& g) {
+  const int64_t per = 4LL << pre_wave_words(g);
+  return ((int64_t)(g.CH + 1) * g.wpr + per - 1) / per;
 }
 static bool pre_thresholds_ok(double a, double b, double c, double h) {
   if (!(a >= 0 && b >= 0 && c >= 0)) return false;
