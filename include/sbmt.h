@@ -330,13 +330,23 @@ sbmt_status sbmt_preprocess(sbmt_handle h, const sbmt_image* img, double a, doub
  *             n_grid_vertices (grid vertices kept), n_cut (grid triangles
  *             the polyline cuts)
  * Rows beyond a capacity are not written; SBMT_E_CAPACITY then comes with the
- * counts filled in (size the outputs from them and call again).  Errors as
+ * counts filled in (size the outputs from them, then call again or, quicker,
+ * sbmt_preprocess_mesh_fill).  Errors as
  * for sbmt_preprocess, and SBMT_E_INDEX_OVERFLOW before any launch when the
  * query's grid vertex bound exceeds 2^31 - 1. */
 sbmt_status sbmt_pre_mesh_query(const sbmt_image* img, size_t* workspace_bytes, int64_t* grid_vert_bound);
 sbmt_status sbmt_preprocess_mesh(sbmt_handle h, const sbmt_image* img, double a, double b, double c,
                                  void* workspace, size_t ws_bytes, double* verts, int64_t vert_cap, int32_t* tris,
                                  uint8_t* codes, int64_t tri_cap, int64_t* counts, void* stream);
+
+/* Writes the mesh that the last sbmt_preprocess_mesh call on this workspace
+ * counted, without counting again: the same image, thresholds and workspace
+ * (contents untouched in between), arguments, outputs and errors as there
+ * (waits for `stream`).  A sizing call and this one do the work of one call
+ * with outputs large enough. */
+sbmt_status sbmt_preprocess_mesh_fill(sbmt_handle h, const sbmt_image* img, double a, double b, double c,
+                                      void* workspace, size_t ws_bytes, double* verts, int64_t vert_cap, int32_t* tris,
+                                      uint8_t* codes, int64_t tri_cap, int64_t* counts, void* stream);
 
 /* Number of canonical classes and the key code of class id c (1-based). */
 int32_t sbmt_num_classes(void);

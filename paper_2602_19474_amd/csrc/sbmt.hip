@@ -2721,47 +2721,61 @@ sbmt_status sbmt_pre_mesh_query(const sbmt_image* img, size_t* workspace_bytes, 
   return SBMT_OK;
 }
 
-sbmt_status sbmt_preprocess_mesh(sbmt_handle h, const sbmt_image* img, double a, double b, double c, void* workspace,
-                                 size_t ws_bytes, double* verts, int64_t vert_cap, int32_t* tris, uint8_t* codes,
-                                 int64_t tri_cap, int64_t* counts, void* stream) {
+// A call of the mesh of Alg. 3 over its workspace: checked, with the kernels'
+// arguments.  The grid goes to the workspace; the mesh keeps the grid vertices
+// its triangles use, then the new ones.
+struct PreCall {
+  PreLayout PL;
+  Shared sh;
+  OneSrc src;
+  PreArgs P;
+  char* w;
+};
+static sbmt_status pre_mesh_prepare(sbmt_handle h, const sbmt_image* img, double a, double b, double c, void* workspace,
+                                    size_t ws_bytes, double* verts, int64_t vert_cap, int32_t* tris, uint8_t* codes,
+                                    int64_t tri_cap, const int64_t* counts, PreCall* o) {
   if (!h || !counts || vert_cap < 0 || tri_cap < 0) return SBMT_E_INVALID_ARG;
   if ((vert_cap > 0 && !verts) || (tri_cap > 0 && (!tris || !codes))) return SBMT_E_INVALID_ARG;
-  PreLayout PL;
-  sbmt_status st = pre_layout(img, true, &PL, true);
+  sbmt_status st = pre_layout(img, true, &o->PL, true);
   if (st != SBMT_OK) return st;
+  const PreLayout& PL = o->PL;
   const Geo& g = PL.L.g[0];
   if (!pre_thresholds_ok(a, b, c, (double)g.h / g.U)) return SBMT_E_INVALID_ARG;
   if (!workspace || ws_bytes < PL.total) return SBMT_E_WORKSPACE;
   if (PL.nown + PL.nmid > 0x7fffffffLL) return SBMT_E_INDEX_OVERFLOW;  // grid vertex indices in 32 bits
-  hipStream_t s = (hipStream_t)stream;
-  char* w = (char*)workspace;
-  const Shared sh = shared_of(PL.L, workspace, 1);
-  OneSrc src;
-  src.d = img_of(PL.L, 0, *img, workspace, nullptr);
-  PreArgs P = pre_args(PL, w, a, b, c);
-  // the grid goes to the workspace; the mesh keeps the grid vertices its
-  // triangles use, then the new ones
-  P.verts = (double*)(w + PL.off_gverts);
-  P.on_polyline = (uint8_t*)(w + PL.off_onp);
+  if (PL.nvblk > 0x7fffffffLL) return SBMT_E_INVALID_ARG;
+  o->w = (char*)workspace;
+  o->sh = shared_of(PL.L, workspace, 1);
+  o->src.d = img_of(PL.L, 0, *img, workspace, nullptr);
+  PreArgs& P = o->P;
+  P = pre_args(PL, o->w, a, b, c);
+  P.verts = (double*)(o->w + PL.off_gverts);
+  P.on_polyline = (uint8_t*)(o->w + PL.off_onp);
   P.vcap = PL.nown + PL.nmid;
   P.overts = verts;
   P.ovcap = vert_cap;
   P.otris = tris;
   P.ocodes = codes;
   P.otcap = tri_cap;
-  if ((st = pre_launch_grid(PL, src, P, sh, w, false, s)) != SBMT_OK) return st;
+  return SBMT_OK;
+}
+// Blocks of a grid-stride pass: as many as run at once on the device.
+static dim3 pre_resident(sbmt_handle h, const void* kernel) {
+  int nb = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kernel, 256, 0) != hipSuccess || nb < 1) nb = 2;
+  return dim3((unsigned)(nb * std::max(h->cus, 1)));
+}
+// The grid, every count and the offsets of the output.
+static sbmt_status pre_mesh_plan(sbmt_handle h, const PreCall& C, hipStream_t s) {
+  const PreLayout& PL = C.PL;
+  const Geo& g = PL.L.g[0];
+  const PreArgs& P = C.P;
+  const Shared& sh = C.sh;
+  const OneSrc& src = C.src;
+  sbmt_status st;
+  if ((st = pre_launch_grid(PL, src, P, sh, C.w, false, s)) != SBMT_OK) return st;
   const int64_t nqb = (PL.L.nseg + 3) / 4;
-  int64_t* out2 = (int64_t*)(w + PL.off_out2);
   const int64_t nwb = pre_word_blocks(g);
-  // grid-stride passes: as many blocks as run at once on the device
-  const int ncu = std::max(h->cus, 1);
-  auto resident = [ncu](auto* k) {
-    int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, reinterpret_cast<const void*>(k), 256, 0) != hipSuccess ||
-        nb < 1)
-      nb = 2;
-    return dim3((unsigned)(nb * ncu));
-  };
   hipLaunchKernelGGL(k_pre_mesh_touch, dim3((unsigned)nwb), dim3(256), 0, s, src, P);
   // the touched owners' list: counts per row segment, their offsets, the list
   hipLaunchKernelGGL(k_pre_mesh_tcount, dim3((unsigned)((PL.L.nseg + 255) / 256)), dim3(256), 0, s, P, sh);
@@ -2769,29 +2783,67 @@ sbmt_status sbmt_preprocess_mesh(sbmt_handle h, const sbmt_image* img, double a,
   hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(kScanThreads), 0, s, sh);
   hipLaunchKernelGGL(k_scan_apply, dim3(PL.L.nblk), dim3(kScanThreads), 0, s, sh);
   hipLaunchKernelGGL(k_pre_mesh_count, dim3((unsigned)nqb), dim3(256), 0, s, src, P, sh);
-  hipLaunchKernelGGL(k_pre_mesh_probe_plain, resident(&k_pre_mesh_probe_plain), dim3(256), 0, s, src, P, sh);
-  hipLaunchKernelGGL(k_pre_mesh_probe_owner, resident(&k_pre_mesh_probe_owner), dim3(256), 0, s, src, P, sh);
-  hipLaunchKernelGGL(k_pre_cut_slots, resident(&k_pre_cut_slots), dim3(256), 0, s, P, sh);
-  hipLaunchKernelGGL(k_pre_cut_make, resident(&k_pre_cut_make), dim3(256), 0, s, src, P);
-  hipLaunchKernelGGL(k_pre_mesh_cut_count, resident(&k_pre_mesh_cut_count), dim3(256), 0, s, src, P, sh);
+  hipLaunchKernelGGL(k_pre_mesh_probe_plain, pre_resident(h, (const void*)&k_pre_mesh_probe_plain), dim3(256), 0, s, src, P, sh);
+  hipLaunchKernelGGL(k_pre_mesh_probe_owner, pre_resident(h, (const void*)&k_pre_mesh_probe_owner), dim3(256), 0, s, src, P, sh);
+  hipLaunchKernelGGL(k_pre_cut_slots, pre_resident(h, (const void*)&k_pre_cut_slots), dim3(256), 0, s, P, sh);
+  hipLaunchKernelGGL(k_pre_cut_make, pre_resident(h, (const void*)&k_pre_cut_make), dim3(256), 0, s, src, P);
+  hipLaunchKernelGGL(k_pre_mesh_cut_count, pre_resident(h, (const void*)&k_pre_mesh_cut_count), dim3(256), 0, s, src, P, sh);
   // the output counts per row segment and their offsets
   hipLaunchKernelGGL(k_pre_mesh_segsum, dim3((unsigned)nqb), dim3(256), 0, s, src, P, sh);
   hipLaunchKernelGGL(k_scan_reduce, dim3(PL.L.nblk), dim3(kScanThreads), 0, s, sh);
   hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(kScanThreads), 0, s, sh);
   hipLaunchKernelGGL(k_scan_apply, dim3(PL.L.nblk), dim3(kScanThreads), 0, s, sh);
-  if (PL.nvblk > 0x7fffffffLL) return SBMT_E_INVALID_ARG;
   hipLaunchKernelGGL(k_pre_vscan_count, dim3((unsigned)PL.nvblk), dim3(256), 0, s, P);
   hipLaunchKernelGGL(k_pre_vscan_top, dim3(1), dim3(256), 0, s, P, PL.nvblk);
+  return hipGetLastError() == hipSuccess ? SBMT_OK : SBMT_E_DEVICE;
+}
+// The planned output.
+static sbmt_status pre_mesh_write(sbmt_handle h, const PreCall& C, hipStream_t s) {
+  const PreLayout& PL = C.PL;
+  const PreArgs& P = C.P;
+  const Shared& sh = C.sh;
+  const OneSrc& src = C.src;
+  const int64_t nqb = (PL.L.nseg + 3) / 4;
   hipLaunchKernelGGL(k_pre_vscan_apply, dim3((unsigned)PL.nvblk), dim3(256), 0, s, P);
   hipLaunchKernelGGL(k_pre_mesh_vbase, dim3((unsigned)nqb), dim3(256), 0, s, src, P, sh);
   hipLaunchKernelGGL(k_pre_mesh_triangles, dim3((unsigned)nqb), dim3(256), 0, s, src, P, sh);
-  hipLaunchKernelGGL(k_pre_mesh_whole_tris, resident(&k_pre_mesh_whole_tris), dim3(256), 0, s, src, P);
-  hipLaunchKernelGGL(k_pre_cut_write, resident(&k_pre_cut_write), dim3(256), 0, s, P);
-  hipLaunchKernelGGL(k_pre_mesh_cut_rest, resident(&k_pre_mesh_cut_rest), dim3(256), 0, s, src, P);
-  hipLaunchKernelGGL(k_pre_mesh_sizes, dim3(1), dim3(1), 0, s, P, sh, out2);
+  hipLaunchKernelGGL(k_pre_mesh_whole_tris, pre_resident(h, (const void*)&k_pre_mesh_whole_tris), dim3(256), 0, s, src, P);
+  hipLaunchKernelGGL(k_pre_cut_write, pre_resident(h, (const void*)&k_pre_cut_write), dim3(256), 0, s, P);
+  hipLaunchKernelGGL(k_pre_mesh_cut_rest, pre_resident(h, (const void*)&k_pre_mesh_cut_rest), dim3(256), 0, s, src, P);
+  return hipGetLastError() == hipSuccess ? SBMT_OK : SBMT_E_DEVICE;
+}
+static sbmt_status pre_mesh_finish(sbmt_handle h, const PreCall& C, int64_t* counts, hipStream_t s) {
+  int64_t* out2 = (int64_t*)(C.w + C.PL.off_out2);
+  hipLaunchKernelGGL(k_pre_mesh_sizes, dim3(1), dim3(1), 0, s, C.P, C.sh, out2);
   if (hipGetLastError() != hipSuccess) return SBMT_E_DEVICE;
-  if ((st = pre_read_sizes(h, out2, 8, counts, s)) != SBMT_OK) return st;
-  return (sbmt_status)counts[5];
+  const sbmt_status st = pre_read_sizes(h, out2, 8, counts, s);
+  return st != SBMT_OK ? st : (sbmt_status)counts[5];
+}
+
+sbmt_status sbmt_preprocess_mesh(sbmt_handle h, const sbmt_image* img, double a, double b, double c, void* workspace,
+                                 size_t ws_bytes, double* verts, int64_t vert_cap, int32_t* tris, uint8_t* codes,
+                                 int64_t tri_cap, int64_t* counts, void* stream) {
+  PreCall C;
+  sbmt_status st =
+      pre_mesh_prepare(h, img, a, b, c, workspace, ws_bytes, verts, vert_cap, tris, codes, tri_cap, counts, &C);
+  if (st != SBMT_OK) return st;
+  hipStream_t s = (hipStream_t)stream;
+  if ((st = pre_mesh_plan(h, C, s)) != SBMT_OK) return st;
+  // a sizing call has no row to write
+  if ((vert_cap > 0 || tri_cap > 0) && (st = pre_mesh_write(h, C, s)) != SBMT_OK) return st;
+  return pre_mesh_finish(h, C, counts, s);
+}
+
+sbmt_status sbmt_preprocess_mesh_fill(sbmt_handle h, const sbmt_image* img, double a, double b, double c,
+                                      void* workspace, size_t ws_bytes, double* verts, int64_t vert_cap, int32_t* tris,
+                                      uint8_t* codes, int64_t tri_cap, int64_t* counts, void* stream) {
+  PreCall C;
+  sbmt_status st =
+      pre_mesh_prepare(h, img, a, b, c, workspace, ws_bytes, verts, vert_cap, tris, codes, tri_cap, counts, &C);
+  if (st != SBMT_OK) return st;
+  hipStream_t s = (hipStream_t)stream;
+  if ((st = pre_mesh_write(h, C, s)) != SBMT_OK) return st;
+  return pre_mesh_finish(h, C, counts, s);
 }
 
 const char* sbmt_status_string(sbmt_status s) {

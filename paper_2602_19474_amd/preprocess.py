@@ -122,7 +122,7 @@ def preprocess_mesh(bitmap, grid_h: float, a: float | None = None, b: float | No
                     stream=None, ctx=None) -> PreMesh:
     """The mesh of Alg. 3 on a uint8 CUDA tensor [H, W]: the preprocessed grid
     retriangulated against the polyline (waits for the stream; a first call
-    sizes the outputs, a second fills them)."""
+    counts and sizes the outputs, a second fills them)."""
     import torch
     if a is None and b is None and c is None:
         a, b, c = paper_thresholds(grid_h)
@@ -137,19 +137,17 @@ def preprocess_mesh(bitmap, grid_h: float, a: float | None = None, b: float | No
     dev = bitmap.device
     ws = torch.empty(int(ws_bytes.value), dtype=torch.uint8, device=dev)
     counts = (ctypes.c_int64 * 8)()
-    nv, nt = 0, 0
-    for attempt in range(2):
-        verts = torch.empty((max(nv, 1), 2), dtype=torch.float64, device=dev)
-        tris = torch.empty((max(nt, 1), 3), dtype=torch.int32, device=dev)
-        codes = torch.empty((max(nt, 1),), dtype=torch.uint8, device=dev)
-        st = L.sbmt_preprocess_mesh(ctx.handle, ctypes.byref(img), float(a), float(b), float(c), ws.data_ptr(),
-                                    int(ws_bytes.value), verts.data_ptr(), verts.shape[0], tris.data_ptr(),
-                                    codes.data_ptr(), nt, counts, _stream_ptr(stream))
-        if st == 0:
-            break
-        if st != -7 or attempt == 1:
-            _lib.check(st, "sbmt_preprocess_mesh")
-        nv, nt = max(int(counts[0]), nv), int(counts[1])
+    args = (ctx.handle, ctypes.byref(img), float(a), float(b), float(c), ws.data_ptr(), int(ws_bytes.value))
+    st = L.sbmt_preprocess_mesh(*args, None, 0, None, None, 0, counts, _stream_ptr(stream))
+    if st != -7:
+        _lib.check(st, "sbmt_preprocess_mesh")
+    nv, nt = int(counts[0]), int(counts[1])
+    verts = torch.empty((max(nv, 1), 2), dtype=torch.float64, device=dev)
+    tris = torch.empty((max(nt, 1), 3), dtype=torch.int32, device=dev)
+    codes = torch.empty((max(nt, 1),), dtype=torch.uint8, device=dev)
+    if st == -7:
+        _lib.check(L.sbmt_preprocess_mesh_fill(*args, verts.data_ptr(), nv, tris.data_ptr(), codes.data_ptr(), nt,
+                                               counts, _stream_ptr(stream)), "sbmt_preprocess_mesh_fill")
     return PreMesh(verts[:int(counts[0])], tris[:int(counts[1])], codes[:int(counts[1])], int(counts[6]),
                    int(counts[2]), int(counts[3]), int(counts[4]), int(counts[7]))
 
