@@ -7,10 +7,13 @@
 // block) through a prefix table of per-image block counts.
 //
 // Kernels
-//   k_coarsen  block-majority coarse raster as packed bits, with a background ring
+//   k_coarsen  block-majority coarse raster as packed bits, with a background
+//              ring; the row and column tables of the exact predicates
 //   k_count    per tile (RB rows x kCB owners): owners whose 3x3 sample window
 //              is uniform, or that no boundary segment reaches, are counted at
 //              once; the others ("slow" owners) are appended to a record list
+//   k_count_small  the same with the slow owners classified in the tile (calls
+//              of few tiles: fewer launches, see kSmallTiles)
 //   k_slow     every slow owner of the call, densely: exact classification
 //              (Alg. 1), class and rotation (Sec. 3.3.3), a 16-byte record, and
 //              its counts added to its row segment
@@ -74,6 +77,9 @@ constexpr int kMaxBandChunks = 64;             // fused path: row segments per b
 constexpr int kSlowBlocks = 2048;              // dense slow pass: blocks of its grid-stride loop
 constexpr int kDenseLists = 64;                // dense slow lists (tile mod 64), each with its own counter
 constexpr int kSizeWords = SBMT_SIZE_WORDS;    // per-image sizes record
+constexpr int kSmallTiles = 4096;           // calls of at most so many 8-row tiles take k_count_small
+constexpr int kFullRecordTiles = 512;          // calls of at most so many have a record for every owner (16 MB)
+constexpr int kScanOwnPrefix = 512;            // scan blocks whose prefix each block adds up itself
 constexpr int kSegSlots = 64;                  // partial segment counts per image (spread atomics)
 constexpr int kRowPad = 20;                    // row-table entries past the last grid row (tile and halo rows)
 
@@ -237,6 +243,21 @@ __device__ __forceinline__ void coarsen_s2(const Img& d, const Geo& g, int bx, i
   if (part == 0 && rr < g.CH + 2 * kRing && w < g.wpr) d.bits[(int64_t)rr * g.wpr + w] = bits;
 }
 
+// The row table (kRowPad rows past the grid, too) and the column table (window
+// column and x reach of column i in rows of parity o) of an image, spread over
+// its coarsening blocks.
+__device__ __forceinline__ void geometry_tables(const Img& d, const Geo& g, int local, int nblocks) {
+  const int first = local * 256 + (int)threadIdx.x, step = nblocks * 256;
+  for (int k = first; k < g.NK + kRowPad; k += step) d.rows[k] = row_table_entry(g, k);
+  for (int j = first; j < 2 * g.NI; j += step) {
+    const int i = j >> 1, o = j & 1;
+    const int X = g.X0 + 4 * g.h * i + 2 * g.h * o, Clo = clo_of(g, X);
+    int x0, x1;
+    owner_xreach(g, X, Clo, x0, x1);
+    d.cols[j] = (uint32_t)(Clo + 8) | ((uint32_t)x0 << 24) | ((uint32_t)x1 << 28);
+  }
+}
+
 template <class Src>
 __global__ void __launch_bounds__(256) k_coarsen(Src src, const int64_t* __restrict__ tab, Shared sh) {
   __shared__ uint32_t mask[kCoarsenRows * kCoarsenMaxS][kCoarsenWords];
@@ -258,6 +279,7 @@ __global__ void __launch_bounds__(256) k_coarsen(Src src, const int64_t* __restr
        q += (int64_t)gridDim.x * blockDim.x)
     sh.segacc[q] = 0ull;
   if (blockIdx.x == 0 && threadIdx.x < kDenseLists) sh.dctr[threadIdx.x] = 0ull;
+  geometry_tables(d, g, (int)local, nbx * ((g.CH + 2 * kRing + kCoarsenRows - 1) / kCoarsenRows));
   if (g.s == 2 && (((uintptr_t)d.bm | (uintptr_t)g.stride) & 15u) == 0) {  // uniform per image
     coarsen_s2(d, g, (int)local % nbx, (int)local / nbx);
     return;
@@ -334,49 +356,39 @@ __global__ void __launch_bounds__(256) k_coarsen(Src src, const int64_t* __restr
 // foreground->background step of its corners in positive order, and every pair
 // of 4-adjacent samples is walked once in each direction by the two cells that
 // share it, so the count is the number of 4-adjacent sample pairs that differ
-// (ring included).  A block sums a run of stored raster rows (the image's rows
-// split over as many blocks as it has 16-row grid bands), one thread per word.
-template <class Src>
-__global__ void __launch_bounds__(256) k_segcount(Src src, const int64_t* __restrict__ tab, Shared sh) {
-  __shared__ int part[256 / 64];
-  int64_t local;
-  const int ii = src.find(blockIdx.x, tab, local);
-  const Img& d = src.img(ii);
-  const Geo g = d.g;
-  const int nb = (g.NK + 15) / 16;
-  const int nrows = g.CH + 2 * kRing;
-  const int rpb = (nrows + nb - 1) / nb;
-  const int r0 = (int)local * rpb, r1 = min(r0 + rpb, nrows);
-  // the row table: grid rows 16 local .. 16 local + 15 (the last block also
-  // the padding rows past the grid)
-  {
-    const int k0 = 16 * (int)local, k1 = (int)local == nb - 1 ? g.NK + kRowPad : k0 + 16;
-    for (int k = k0 + (int)threadIdx.x; k < k1; k += 256) d.rows[k] = row_table_entry(g, k);
-  }
-  // the column table: window column and x reach of column i in rows of parity o
-  for (int j = (int)local * 256 + (int)threadIdx.x; j < 2 * g.NI; j += nb * 256) {
-    const int i = j >> 1, o = j & 1;
-    const int X = g.X0 + 4 * g.h * i + 2 * g.h * o, Clo = clo_of(g, X);
-    int x0, x1;
-    owner_xreach(g, X, Clo, x0, x1);
-    d.cols[j] = (uint32_t)(Clo + 8) | ((uint32_t)x0 << 24) | ((uint32_t)x1 << 28);
-  }
+// (ring included).  Every kSegEvery-th of an image's nblocks blocks (kT threads
+// each) sums a run of stored raster words; one atomic per wave, spread over the
+// image's slots (summed by segment_total).  The slots share four lines, and
+// atomics on a line take turns (10 ns each): one from every tile of the
+// 8192 x 8192 image cost 88 us.
+constexpr int kSegEvery = 16;
+template <int kT>
+__device__ __forceinline__ void segment_count(const Img& d, const Geo& g, const Shared& sh, int ii, int local, int nblocks) {
+  if (local % kSegEvery) return;  // uniform
+  const int nrows = g.CH + 2 * kRing, words = nrows * g.wpr;
+  const int runs = (nblocks + kSegEvery - 1) / kSegEvery, per = (words + runs - 1) / runs;
+  const int t0 = local / kSegEvery * per, t1 = min(words, t0 + per);
   int n = 0;
-  for (int t = threadIdx.x; t < (r1 - r0) * g.wpr; t += 256) {
-    const int rr = r0 + t / g.wpr, w = t - (t / g.wpr) * g.wpr;
+  for (int t = t0 + (int)threadIdx.x; t < t1; t += kT) {
+    const int rr = t / g.wpr, w = t - rr * g.wpr;
     const uint32_t* row = d.bits + (int64_t)rr * g.wpr;
     const uint32_t x = row[w], xn = w + 1 < g.wpr ? row[w + 1] : 0u;
     const uint32_t xd = rr + 1 < nrows ? row[g.wpr + w] : 0u;
     n += __builtin_popcount(x ^ ((x >> 1) | (xn << 31))) + __builtin_popcount(x ^ xd);
   }
   n = __builtin_amdgcn_readlane(wave_incl_scan_dpp(n), 63);
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = n;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const int tot = part[0] + part[1] + part[2] + part[3];
-    // one atomic per block, spread over the image's slots (summed by segment_total)
-    if (tot) atomicAdd(&sh.segacc[kSegSlots * (int64_t)ii + (blockIdx.x & (kSegSlots - 1))], (unsigned long long)tot);
-  }
+  if ((threadIdx.x & 63) == 0 && n)
+    atomicAdd(&sh.segacc[kSegSlots * (int64_t)ii + (blockIdx.x & (kSegSlots - 1))], (unsigned long long)n);
+}
+// The same as a launch of its own, as many blocks as the image has 16-row grid
+// bands (on k_slow_tiles' small blocks it took 17 us instead of 7).
+template <class Src>
+__global__ void __launch_bounds__(256) k_segcount(Src src, const int64_t* __restrict__ tab, Shared sh) {
+  int64_t local;
+  const int ii = src.find(blockIdx.x, tab, local);
+  const Img& d = src.img(ii);
+  const Geo g = d.g;
+  segment_count<256>(d, g, sh, ii, kSegEvery * (int)local, kSegEvery * ((g.NK + 15) / 16));
 }
 
 __device__ __forceinline__ long long segment_total(const Shared& sh, int ii) {
@@ -446,16 +458,23 @@ struct CountLds {
   int qn[kThreads / 64];         // per wave: entries in q1
   int n2;
   unsigned dbase;
+  unsigned long long slow[RB];   // kCountClassify: counts of each row's slow owners (pack_counts)
   uint32_t win[kWinRows * kWinWords];
 };
+
+// What count_tile does with the slow owners it found: queue them in the tile's
+// record region (the persistent kernel classifies them), and in the dense lists
+// too, or classify them here (their counts to L.slow).
+constexpr int kCountQueue = 0, kCountDense = 1, kCountClassify = 2;
 
 // Rows k0 .. k0+RB-1 of column block cb.  With hdst, the codes of the last
 // row go to hdst[c] instead of the owner map (the persistent kernel counts
 // the first row of the next band that way without writing it).  Slow owners
 // beyond the record region keep the queued mark (0x8000) for k_slow (the
 // persistent kernel's regions hold every owner of a tile), which keeps this
-// routine free of the classification's registers.
-template <int RB, bool kDense = false>
+// routine free of the classification's registers; with kCountClassify they are
+// classified like the others, without a record.
+template <int RB, int kMode = kCountQueue>
 __device__ __forceinline__ void count_tile(const Img& d, const Geo& g, int ii, int64_t tile, int k0, int cb,
                                            const Shared& sh, CountLds<RB>& L, int4* acc_out,
                                            uint16_t* __restrict__ hdst) {
@@ -467,6 +486,7 @@ __device__ __forceinline__ void count_tile(const Img& d, const Geo& g, int ii, i
     L.rowR[threadIdx.x] = rt.R;
     L.rowp[threadIdx.x] = rt.pk;
     L.acc[threadIdx.x][0] = L.acc[threadIdx.x][1] = L.acc[threadIdx.x][2] = L.acc[threadIdx.x][3] = 0;
+    if (kMode == kCountClassify) L.slow[threadIdx.x] = 0ull;
   }
   if (threadIdx.x == 0) L.n2 = 0;
   __syncthreads();
@@ -570,19 +590,33 @@ __device__ __forceinline__ void count_tile(const Img& d, const Geo& g, int ii, i
   if (threadIdx.x == 0) {
     sh.tile_n[tile] = L.n2;
     // list tile mod kDenseLists, so that no counter takes every tile's atomic
-    if (kDense && L.n2)
+    if (kMode == kCountDense && L.n2)
       L.dbase = (unsigned)((tile & (kDenseLists - 1)) * sh.dcap +
                            (int64_t)atomicAdd(&sh.dctr[tile & (kDenseLists - 1)],
                                               (unsigned long long)min((int64_t)L.n2, sh.tcap)));
   }
-  if (kDense) __syncthreads();
+  if (kMode == kCountDense) __syncthreads();
   for (int q = threadIdx.x; q < L.n2; q += kThreads) {
     const int e = L.q2[q], r = e / kCB, c = c0 + (e - r * kCB);
     const int k = k0 + r;
-    if (q < sh.tcap) {
+    if (kMode == kCountClassify) {
+      const RowT& rt = d.rows[k];
+      const uint32_t xc = L.xc[k & 1][e - r * kCB];
+      const Frame f = owner_frame_at(g, bw, k, c, L.rowR[r], (int)(xc & 0xffffu) - kRingC + bw.cc0);
+      Slow sr;
+      slow_classify(g, f, rt, d.rows[k + 1].FL, sr);
+      L.code[r][e - r * kCB] = (uint16_t)map_code(sr.info);
+      atomicAdd(&L.slow[r], pack_counts(sr.info));
+      if (info_err(sr.info)) atomicOr(&sh.imgerr[ii], 1);
+      if (q < sh.tcap) {
+        SlowRec R = pack_slow(sr);
+        R.x |= (uint64_t)((r << 8) | (e - r * kCB)) << 48;
+        sh.rec[tile * sh.tcap + q] = R;
+      }
+    } else if (q < sh.tcap) {
       // the owner's position for the dense pass
       sh.rec[tile * sh.tcap + q].x = (uint64_t)c | ((uint64_t)k << 24) | ((uint64_t)ii << 48);
-      if (kDense) sh.dense[L.dbase + q] = (uint32_t)(tile * sh.tcap + q);
+      if (kMode == kCountDense) sh.dense[L.dbase + q] = (uint32_t)(tile * sh.tcap + q);
     }
   }
   __syncthreads();
@@ -619,10 +653,35 @@ __global__ void __launch_bounds__(kThreads, 8) k_count(Src src, const int64_t* _
   const Img& d = src.img(ii);
   const Geo g = d.g;
   const int cb = (int)local % g.NCB, ky = (int)local / g.NCB;  // tile index of an image: 32 bits
-  count_tile<RB, true>(d, g, ii, (int64_t)blockIdx.x, ky * RB, cb, sh, L, out, nullptr);
+  count_tile<RB, kCountDense>(d, g, ii, (int64_t)blockIdx.x, ky * RB, cb, sh, L, out, nullptr);
   __syncthreads();
   const int k = ky * RB + (int)threadIdx.x;
   if (threadIdx.x < RB && k < g.NK) sh.seg_cnt[d.seg0 + (int64_t)k * g.NCB + cb] = out[threadIdx.x];
+}
+
+// A tile with its slow owners classified at once and the image's boundary
+// segments counted: the whole of k_segcount, k_count, k_slow_dense and
+// k_slow_tiles, for calls of few tiles.  There three launches cost more than
+// waves that are not full (one sbmt_mesh_async: 10 tiles 43 -> 35 us, 225
+// 58 -> 46, 1302 84 -> 75, 2312 118 -> 112, 5208 the same, 9248 242 -> 255).
+template <class Src>
+__global__ void __launch_bounds__(kThreads, 4) k_count_small(Src src, const int64_t* __restrict__ tab, Shared sh) {
+  constexpr int RB = 8;
+  __shared__ CountLds<RB> L;
+  __shared__ int4 out[RB];
+  int64_t local;
+  const int ii = src.find(blockIdx.x, tab, local);
+  const Img& d = src.img(ii);
+  const Geo g = d.g;
+  const int cb = (int)local % g.NCB, ky = (int)local / g.NCB;
+  segment_count<kThreads>(d, g, sh, ii, (int)local, g.NCB * ((g.NK + RB - 1) / RB));
+  count_tile<RB, kCountClassify>(d, g, ii, (int64_t)blockIdx.x, ky * RB, cb, sh, L, out, nullptr);
+  __syncthreads();
+  const int k = ky * RB + (int)threadIdx.x;
+  if (threadIdx.x < RB && k < g.NK) {
+    sh.seg_cnt[d.seg0 + (int64_t)k * g.NCB + cb] = out[threadIdx.x];
+    sh.seg_slow[d.seg0 + (int64_t)k * g.NCB + cb] = L.slow[threadIdx.x];
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -821,7 +880,26 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_blocks(Shared sh) {
   if (threadIdx.x == 0) sh.seg_off[sh.nseg] = make_longlong4(ra, rb, rc, 0);
 }
 
-__global__ void __launch_bounds__(kScanThreads) k_scan_apply(Shared sh) {
+// Where the sizes record of a single image goes once the scan knows its
+// totals (all null: nowhere): the workspace, the caller's device record, the
+// handle's pinned host record.
+struct SizesTo {
+  int64_t* ws;
+  int64_t* user;
+  int64_t* host;
+  int64_t vcap, tcap;
+};
+__device__ __forceinline__ int64_t size_status(int err, long long nv, long long nt, int64_t vcap, int64_t tcap) {
+  if (err) return SBMT_E_PROTOCOL;
+  if (nv > 0x7fffffffLL) return SBMT_E_INDEX_OVERFLOW;
+  if (nv > vcap || nt > tcap) return SBMT_E_CAPACITY;
+  return SBMT_OK;
+}
+
+// kOwn: every block adds up the sums of the blocks before it (few of them: a
+// launch less than k_scan_blocks), and the last one writes the totals.
+template <bool kOwn>
+__global__ void __launch_bounds__(kScanThreads) k_scan_apply(Shared sh, SizesTo to) {
   __shared__ long long sa[33], sb[33];
   const int64_t base = (int64_t)blockIdx.x * kScanChunk;
   long long va[4], vb[4], vc[4];
@@ -838,7 +916,42 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_apply(Shared sh) {
   block_excl_scan2(a, b, sa, sb, ta, tb);
   long long z = 0;
   block_excl_scan2(c, z, sa, sb, tc, dd);
-  const longlong4 bo = sh.blk[blockIdx.x];
+  longlong4 bo = make_longlong4(0, 0, 0, 0);
+  if (kOwn) {
+    long long pa = 0, pb = 0, pc = 0, pz = 0;
+    for (int j = threadIdx.x; j < (int)blockIdx.x; j += kScanThreads) {
+      const longlong4 v = sh.blk[j];
+      pa += v.x;
+      pb += v.y;
+      pc += v.z;
+    }
+    if (blockIdx.x > 0) {  // uniform
+      long long qa, qb, qc;
+      block_excl_scan2(pa, pb, sa, sb, qa, qb);
+      block_excl_scan2(pc, pz, sa, sb, qc, dd);
+      bo = make_longlong4(qa, qb, qc, 0);
+    }
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x < 64) {
+      const long long nv = bo.x + ta, nt = bo.y + tb, nc = bo.z + tc;
+      if (threadIdx.x == 0) sh.seg_off[sh.nseg] = make_longlong4(nv, nt, nc, 0);
+      if (to.ws) {
+        static_assert(kSegSlots == 64, "a slot per lane");
+        long long ns = (long long)sh.segacc[threadIdx.x];
+        for (int off = 32; off > 0; off >>= 1) ns += __shfl_xor(ns, off);
+        if (threadIdx.x == 0) {
+          const int64_t st = size_status(sh.imgerr[0], nv, nt, to.vcap, to.tcap);
+          const int64_t rec[kSizeWords] = {nv, nt, nc, st, ns};
+          for (int q = 0; q < kSizeWords; ++q) {
+            to.ws[q] = rec[q];
+            if (to.user) to.user[q] = rec[q];
+            if (to.host) to.host[q] = rec[q];
+          }
+        }
+      }
+    }
+  } else {
+    bo = sh.blk[blockIdx.x];
+  }
   a += bo.x;
   b += bo.y;
   c += bo.z;
@@ -863,10 +976,7 @@ __device__ __forceinline__ void image_totals(const Img& d, const Shared& sh, lon
 }
 
 __device__ __forceinline__ int64_t image_status(const Img& d, int err, long long nv, long long nt) {
-  if (err) return SBMT_E_PROTOCOL;
-  if (nv > 0x7fffffffLL) return SBMT_E_INDEX_OVERFLOW;
-  if (nv > d.vcap || nt > d.tcap) return SBMT_E_CAPACITY;
-  return SBMT_OK;
+  return size_status(err, nv, nt, d.vcap, d.tcap);
 }
 
 template <class Src>
@@ -1892,7 +2002,10 @@ static sbmt_status make_call_layout(const sbmt_image* imgs, int n, int64_t recor
   // shared evenly by the tiles
   for (int r = 0; r < 3; ++r) L.ntiles_max = std::max(L.ntiles_max, tab_row(L, 1 + r)[n]);
   if (record_cap == 0) {
-    for (int r = 0; r < 3; ++r) L.rcap = std::max(L.rcap, tab_row(L, 1 + r)[n] * (int64_t)(kRBs[r] * kCB / 2));
+    // a call of few tiles gets a record for every owner, and needs no pass for
+    // owners without one
+    const int part = tab_row(L, 2)[n] <= kFullRecordTiles ? 1 : 2;
+    for (int r = 0; r < 3; ++r) L.rcap = std::max(L.rcap, tab_row(L, 1 + r)[n] * (int64_t)(kRBs[r] * kCB / part));
   } else if (record_cap < 0) {
     // room for every owner of a persistent-kernel band tile (its rows and halo row)
     for (int r = 0; r < 2; ++r) L.rcap = std::max(L.rcap, tab_row(L, 1 + r)[n] * (int64_t)((kRBs[r] + 1) * kCB));
@@ -2007,43 +2120,62 @@ static Img img_of(const CallLayout& L, int i, const sbmt_image& im, void* ws, co
   return d;
 }
 
+// Exclusive scan of the segment counts.  One block (2048 segments) is scanned
+// by itself; up to kScanOwnPrefix blocks add up the blocks before them, which
+// costs less than a launch; beyond, one block scans the block sums.  The sizes
+// record of a single image comes with the first two (scan_writes_sizes).
+static bool scan_writes_sizes(const CallLayout& L) { return L.n == 1 && L.nblk <= kScanOwnPrefix; }
+static sbmt_status launch_scan(const CallLayout& L, const Shared& sh, const SizesTo& to, hipStream_t st) {
+  if (L.nblk > 1) hipLaunchKernelGGL(k_scan_reduce, dim3(L.nblk), dim3(kScanThreads), 0, st, sh);
+  if (L.nblk <= kScanOwnPrefix) {
+    hipLaunchKernelGGL(k_scan_apply<true>, dim3(L.nblk), dim3(kScanThreads), 0, st, sh, to);
+  } else {
+    hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(kScanThreads), 0, st, sh);
+    hipLaunchKernelGGL(k_scan_apply<false>, dim3(L.nblk), dim3(kScanThreads), 0, st, sh, to);
+  }
+  return hipGetLastError() == hipSuccess ? SBMT_OK : SBMT_E_DEVICE;
+}
+constexpr SizesTo kNoSizes = {nullptr, nullptr, nullptr, 0, 0};
+static SizesTo sizes_to(const CallLayout& L, const Shared& sh, const Img& d, int64_t* user, long long* host) {
+  if (!scan_writes_sizes(L)) return kNoSizes;
+  return SizesTo{sh.sizes, user, (int64_t*)host, d.vcap, d.tcap};
+}
+
 template <class Src>
 static sbmt_status launch_front(const CallLayout& L, const Src& src, const int64_t* dtab, const Shared& sh, int rbi,
-                                hipStream_t st) {
+                                const SizesTo& to, hipStream_t st) {
   const int64_t* t0 = dtab;
   const int64_t* tt = dtab ? dtab + (size_t)(1 + rbi) * (L.n + 1) : nullptr;
   const int64_t ncb = L.tab[(size_t)0 * (L.n + 1) + L.n];
   const int64_t ntile = L.tab[(size_t)(1 + rbi) * (L.n + 1) + L.n];
   if (ncb > 0x7fffffffLL || ntile > 0x7fffffffLL) return SBMT_E_INVALID_ARG;
   hipLaunchKernelGGL(k_coarsen<Src>, dim3((unsigned)ncb), dim3(256), 0, st, src, t0, sh);
-  const int64_t nsb = L.tab[(size_t)6 * (L.n + 1) + L.n];  // 16-row bands: segment-count blocks
-  hipLaunchKernelGGL(k_segcount<Src>, dim3((unsigned)nsb), dim3(256), 0, st, src,
-                     dtab ? dtab + (size_t)6 * (L.n + 1) : nullptr, sh);
-  switch (kRBs[rbi]) {
-    case 4: hipLaunchKernelGGL((k_count<Src, 4>), dim3((unsigned)ntile), dim3(kThreads), 0, st, src, tt, sh); break;
-    case 8: hipLaunchKernelGGL((k_count<Src, 8>), dim3((unsigned)ntile), dim3(kThreads), 0, st, src, tt, sh); break;
-    default: hipLaunchKernelGGL((k_count<Src, 16>), dim3((unsigned)ntile), dim3(kThreads), 0, st, src, tt, sh); break;
+  if (kRBs[rbi] == 8 && ntile <= kSmallTiles) {
+    hipLaunchKernelGGL((k_count_small<Src>), dim3((unsigned)ntile), dim3(kThreads), 0, st, src, tt, sh);
+    return launch_scan(L, sh, to, st);
   }
+  hipLaunchKernelGGL(k_segcount<Src>, dim3((unsigned)L.tab[(size_t)6 * (L.n + 1) + L.n]), dim3(256), 0, st, src,
+                     dtab ? dtab + (size_t)6 * (L.n + 1) : nullptr, sh);
   // the dense pass: a grid-stride loop over the queued records (at most rcap)
   const dim3 gd((unsigned)std::max<int64_t>(1, std::min<int64_t>((L.rcap + kThreads - 1) / kThreads, kSlowBlocks)));
   switch (kRBs[rbi]) {
     case 4:
+      hipLaunchKernelGGL((k_count<Src, 4>), dim3((unsigned)ntile), dim3(kThreads), 0, st, src, tt, sh);
       hipLaunchKernelGGL((k_slow_dense<Src, 4>), gd, dim3(kThreads), 0, st, src, sh);
       hipLaunchKernelGGL((k_slow_tiles<Src, 4>), dim3((unsigned)ntile), dim3(64), 0, st, src, tt, sh);
       break;
     case 8:
+      hipLaunchKernelGGL((k_count<Src, 8>), dim3((unsigned)ntile), dim3(kThreads), 0, st, src, tt, sh);
       hipLaunchKernelGGL((k_slow_dense<Src, 8>), gd, dim3(kThreads), 0, st, src, sh);
       hipLaunchKernelGGL((k_slow_tiles<Src, 8>), dim3((unsigned)ntile), dim3(64), 0, st, src, tt, sh);
       break;
     default:
+      hipLaunchKernelGGL((k_count<Src, 16>), dim3((unsigned)ntile), dim3(kThreads), 0, st, src, tt, sh);
       hipLaunchKernelGGL((k_slow_dense<Src, 16>), gd, dim3(kThreads), 0, st, src, sh);
       hipLaunchKernelGGL((k_slow_tiles<Src, 16>), dim3((unsigned)ntile), dim3(64), 0, st, src, tt, sh);
       break;
   }
-  hipLaunchKernelGGL(k_scan_reduce, dim3(L.nblk), dim3(kScanThreads), 0, st, sh);
-  hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(kScanThreads), 0, st, sh);
-  hipLaunchKernelGGL(k_scan_apply, dim3(L.nblk), dim3(kScanThreads), 0, st, sh);
-  return hipGetLastError() == hipSuccess ? SBMT_OK : SBMT_E_DEVICE;
+  return launch_scan(L, sh, to, st);
 }
 
 template <class Src>
@@ -2059,18 +2191,19 @@ static sbmt_status launch_emit(const CallLayout& L, const Src& src, const int64_
   const int64_t ntile = L.tab[(size_t)(1 + rbi) * (L.n + 1) + L.n];
   if (ntile > 0x7fffffffLL) return SBMT_E_INVALID_ARG;
   const dim3 gm((unsigned)((ntile + kThreads - 1) / kThreads));
+  const bool missing = L.tcap[rbi] < (int64_t)kRBs[rbi] * kCB;  // else every owner has a record
   switch (kRBs[rbi]) {
     case 4:
       hipLaunchKernelGGL((k_emit<Src, 4>), dim3((unsigned)ntile), dim3(kThreads), 0, st, src, tt, sh);
-      hipLaunchKernelGGL((k_emit_missing<Src, 4>), gm, dim3(kThreads), 0, st, src, tt, sh, ntile);
+      if (missing) hipLaunchKernelGGL((k_emit_missing<Src, 4>), gm, dim3(kThreads), 0, st, src, tt, sh, ntile);
       break;
     case 8:
       hipLaunchKernelGGL((k_emit<Src, 8>), dim3((unsigned)ntile), dim3(kThreads), 0, st, src, tt, sh);
-      hipLaunchKernelGGL((k_emit_missing<Src, 8>), gm, dim3(kThreads), 0, st, src, tt, sh, ntile);
+      if (missing) hipLaunchKernelGGL((k_emit_missing<Src, 8>), gm, dim3(kThreads), 0, st, src, tt, sh, ntile);
       break;
     default:
       hipLaunchKernelGGL((k_emit<Src, 16>), dim3((unsigned)ntile), dim3(kThreads), 0, st, src, tt, sh);
-      hipLaunchKernelGGL((k_emit_missing<Src, 16>), gm, dim3(kThreads), 0, st, src, tt, sh, ntile);
+      if (missing) hipLaunchKernelGGL((k_emit_missing<Src, 16>), gm, dim3(kThreads), 0, st, src, tt, sh, ntile);
       break;
   }
   return hipGetLastError() == hipSuccess ? SBMT_OK : SBMT_E_DEVICE;
@@ -2257,10 +2390,12 @@ sbmt_status sbmt_plan(sbmt_handle h, const sbmt_image* img, void* workspace, siz
   const Shared sh = shared_of(L, workspace, 1);
   OneSrc src;
   src.d = img_of(L, 0, *img, workspace, nullptr);
-  if ((st = launch_front(L, src, nullptr, sh, 1, s)) != SBMT_OK) return st;
-  if ((st = launch_sizes(L, src, sh, nullptr, s)) != SBMT_OK) return st;
-  if (hipMemcpyAsync(h->pinned, sh.sizes, kSizeWords * sizeof(int64_t), hipMemcpyDeviceToHost, s) != hipSuccess)
-    return SBMT_E_DEVICE;
+  if ((st = launch_front(L, src, nullptr, sh, 1, sizes_to(L, sh, src.d, nullptr, h->pinned), s)) != SBMT_OK) return st;
+  if (!scan_writes_sizes(L)) {
+    if ((st = launch_sizes(L, src, sh, nullptr, s)) != SBMT_OK) return st;
+    if (hipMemcpyAsync(h->pinned, sh.sizes, kSizeWords * sizeof(int64_t), hipMemcpyDeviceToHost, s) != hipSuccess)
+      return SBMT_E_DEVICE;
+  }
   if (hipStreamSynchronize(s) != hipSuccess) return SBMT_E_DEVICE;
   if (h->pinned[3] == SBMT_E_PROTOCOL) return SBMT_E_PROTOCOL;
   host_sizes_of((const int64_t*)h->pinned, out);
@@ -2304,9 +2439,9 @@ sbmt_status sbmt_mesh_async(sbmt_handle h, const sbmt_image* img, void* workspac
   o.tri_cap = tri_cap;
   OneSrc src;
   src.d = img_of(L, 0, *img, workspace, &o);
-  if ((st = launch_front(L, src, nullptr, sh, 1, s)) != SBMT_OK) return st;
+  if ((st = launch_front(L, src, nullptr, sh, 1, sizes_to(L, sh, src.d, sizes_dev, nullptr), s)) != SBMT_OK) return st;
   if ((st = launch_emit(L, src, nullptr, sh, 1, s)) != SBMT_OK) return st;
-  return launch_sizes(L, src, sh, sizes_dev, s);
+  return scan_writes_sizes(L) ? SBMT_OK : launch_sizes(L, src, sh, sizes_dev, s);
 }
 
 sbmt_status sbmt_mesh_noalloc(sbmt_handle h, const sbmt_image* img, double* verts, int64_t vert_cap, int32_t* tris,
@@ -2400,7 +2535,7 @@ sbmt_status sbmt_batch_plan(sbmt_batch b, sbmt_sizes* out, void* stream) {
   hipStream_t s = (hipStream_t)stream;
   const Shared sh = shared_of(b->L, b->ws, rb_index(b->tune.tile_rows));
   const ManySrc src = many_of(b);
-  sbmt_status st = launch_front(b->L, src, dtab_of(b), sh, rb_index(b->tune.tile_rows), s);
+  sbmt_status st = launch_front(b->L, src, dtab_of(b), sh, rb_index(b->tune.tile_rows), kNoSizes, s);
   if (st != SBMT_OK) return st;
   b->count_rbi = rb_index(b->tune.tile_rows);
   if ((st = launch_sizes(b->L, src, sh, nullptr, s)) != SBMT_OK) return st;
@@ -2423,7 +2558,7 @@ sbmt_status sbmt_batch_plan_async(sbmt_batch b, void* stream) {
   hipStream_t s = (hipStream_t)stream;
   const Shared sh = shared_of(b->L, b->ws, rb_index(b->tune.tile_rows));
   const ManySrc src = many_of(b);
-  sbmt_status st = launch_front(b->L, src, dtab_of(b), sh, rb_index(b->tune.tile_rows), s);
+  sbmt_status st = launch_front(b->L, src, dtab_of(b), sh, rb_index(b->tune.tile_rows), kNoSizes, s);
   if (st != SBMT_OK) return st;
   b->count_rbi = rb_index(b->tune.tile_rows);
   if ((st = launch_sizes(b->L, src, sh, nullptr, s)) != SBMT_OK) return st;
@@ -2470,7 +2605,7 @@ sbmt_status sbmt_batch_mesh(sbmt_batch b, int64_t* sizes_dev, void* stream) {
   const int64_t* dtab = dtab_of(b);
   if (b->tune.strategy == SBMT_STRATEGY_MULTI || !fused_records_fit(L, b->tune.tile_rows)) {
     b->count_rbi = rbi;
-    sbmt_status st = launch_front(L, src, dtab, sh, rbi, s);
+    sbmt_status st = launch_front(L, src, dtab, sh, rbi, kNoSizes, s);
     if (st != SBMT_OK) return st;
     if ((st = launch_emit(L, src, dtab, sh, rbi, s)) != SBMT_OK) return st;
     return launch_sizes(L, src, sh, sizes_dev, s);
@@ -2667,9 +2802,7 @@ static sbmt_status pre_launch_grid(const PreLayout& PL, const OneSrc& src, const
   hipLaunchKernelGGL(k_pre_repel, dim3((unsigned)nwb), dim3(256), 0, s, src, P);
   hipLaunchKernelGGL(k_pre_split, dim3((unsigned)nwb), dim3(256), 0, s, src, P);
   hipLaunchKernelGGL(k_pre_count, dim3((unsigned)nqb), dim3(256), 0, s, src, P, sh);
-  hipLaunchKernelGGL(k_scan_reduce, dim3(PL.L.nblk), dim3(kScanThreads), 0, s, sh);
-  hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(kScanThreads), 0, s, sh);
-  hipLaunchKernelGGL(k_scan_apply, dim3(PL.L.nblk), dim3(kScanThreads), 0, s, sh);
+  if (launch_scan(PL.L, sh, kNoSizes, s) != SBMT_OK) return SBMT_E_DEVICE;
   hipLaunchKernelGGL(k_pre_inserted, dim3((unsigned)nqb), dim3(256), 0, s, src, P, sh);
   if (triangles) hipLaunchKernelGGL(k_pre_triangles, dim3((unsigned)nqb), dim3(256), 0, s, src, P, sh);
   hipLaunchKernelGGL(k_pre_sizes, dim3(1), dim3(1), 0, s, src, P, sh, (int64_t*)(w + PL.off_out));
@@ -2779,9 +2912,7 @@ static sbmt_status pre_mesh_plan(sbmt_handle h, const PreCall& C, hipStream_t s)
   hipLaunchKernelGGL(k_pre_mesh_touch, dim3((unsigned)nwb), dim3(256), 0, s, src, P);
   // the touched owners' list: counts per row segment, their offsets, the list
   hipLaunchKernelGGL(k_pre_mesh_tcount, dim3((unsigned)((PL.L.nseg + 255) / 256)), dim3(256), 0, s, P, sh);
-  hipLaunchKernelGGL(k_scan_reduce, dim3(PL.L.nblk), dim3(kScanThreads), 0, s, sh);
-  hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(kScanThreads), 0, s, sh);
-  hipLaunchKernelGGL(k_scan_apply, dim3(PL.L.nblk), dim3(kScanThreads), 0, s, sh);
+  if (launch_scan(PL.L, sh, kNoSizes, s) != SBMT_OK) return SBMT_E_DEVICE;
   hipLaunchKernelGGL(k_pre_mesh_count, dim3((unsigned)nqb), dim3(256), 0, s, src, P, sh);
   hipLaunchKernelGGL(k_pre_mesh_probe_plain, pre_resident(h, (const void*)&k_pre_mesh_probe_plain), dim3(256), 0, s, src, P, sh);
   hipLaunchKernelGGL(k_pre_mesh_probe_owner, pre_resident(h, (const void*)&k_pre_mesh_probe_owner), dim3(256), 0, s, src, P, sh);
@@ -2790,9 +2921,7 @@ static sbmt_status pre_mesh_plan(sbmt_handle h, const PreCall& C, hipStream_t s)
   hipLaunchKernelGGL(k_pre_mesh_cut_count, pre_resident(h, (const void*)&k_pre_mesh_cut_count), dim3(256), 0, s, src, P, sh);
   // the output counts per row segment and their offsets
   hipLaunchKernelGGL(k_pre_mesh_segsum, dim3((unsigned)nqb), dim3(256), 0, s, src, P, sh);
-  hipLaunchKernelGGL(k_scan_reduce, dim3(PL.L.nblk), dim3(kScanThreads), 0, s, sh);
-  hipLaunchKernelGGL(k_scan_blocks, dim3(1), dim3(kScanThreads), 0, s, sh);
-  hipLaunchKernelGGL(k_scan_apply, dim3(PL.L.nblk), dim3(kScanThreads), 0, s, sh);
+  if (launch_scan(PL.L, sh, kNoSizes, s) != SBMT_OK) return SBMT_E_DEVICE;
   hipLaunchKernelGGL(k_pre_vscan_count, dim3((unsigned)PL.nvblk), dim3(256), 0, s, P);
   hipLaunchKernelGGL(k_pre_vscan_top, dim3(1), dim3(256), 0, s, P, PL.nvblk);
   return hipGetLastError() == hipSuccess ? SBMT_OK : SBMT_E_DEVICE;
