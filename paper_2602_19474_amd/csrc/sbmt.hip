@@ -664,9 +664,8 @@ __global__ void __launch_bounds__(kThreads, 8) k_count(Src src, const int64_t* _
 // k_slow_tiles, for calls of few tiles.  There three launches cost more than
 // waves that are not full (one sbmt_mesh_async: 10 tiles 43 -> 35 us, 225
 // 58 -> 46, 1302 84 -> 75, 2312 118 -> 112, 5208 the same, 9248 242 -> 255).
-template <class Src>
+template <class Src, int RB>
 __global__ void __launch_bounds__(kThreads, 4) k_count_small(Src src, const int64_t* __restrict__ tab, Shared sh) {
-  constexpr int RB = 8;
   __shared__ CountLds<RB> L;
   __shared__ int4 out[RB];
   int64_t local;
@@ -2150,8 +2149,11 @@ static sbmt_status launch_front(const CallLayout& L, const Src& src, const int64
   const int64_t ntile = L.tab[(size_t)(1 + rbi) * (L.n + 1) + L.n];
   if (ncb > 0x7fffffffLL || ntile > 0x7fffffffLL) return SBMT_E_INVALID_ARG;
   hipLaunchKernelGGL(k_coarsen<Src>, dim3((unsigned)ncb), dim3(256), 0, st, src, t0, sh);
-  if (kRBs[rbi] == 8 && ntile <= kSmallTiles) {
-    hipLaunchKernelGGL((k_count_small<Src>), dim3((unsigned)ntile), dim3(kThreads), 0, st, src, tt, sh);
+  if (kRBs[rbi] <= 8 && L.tab[(size_t)2 * (L.n + 1) + L.n] <= kSmallTiles) {
+    if (kRBs[rbi] == 4)
+      hipLaunchKernelGGL((k_count_small<Src, 4>), dim3((unsigned)ntile), dim3(kThreads), 0, st, src, tt, sh);
+    else
+      hipLaunchKernelGGL((k_count_small<Src, 8>), dim3((unsigned)ntile), dim3(kThreads), 0, st, src, tt, sh);
     return launch_scan(L, sh, to, st);
   }
   hipLaunchKernelGGL(k_segcount<Src>, dim3((unsigned)L.tab[(size_t)6 * (L.n + 1) + L.n]), dim3(256), 0, st, src,
@@ -2373,6 +2375,13 @@ sbmt_status sbmt_query(const sbmt_image* img, sbmt_layout* out) {
   return SBMT_OK;
 }
 
+// Tile height of a single image: 4 rows where all tiles run at once anyway, so
+// that a tile's chain of rows is half as long (one sbmt_mesh_async of 225 tiles of
+// 8 rows: 54 -> 41 us, of 740: 67.4 -> 65.7); else 8, which reads a row beyond
+// its own for eight and not for four (1302 tiles: 75.3 against 77.0).
+constexpr int kShortTiles = 1024;
+static int single_rbi(const CallLayout& L) { return L.tab[(size_t)2 * (L.n + 1) + L.n] <= kShortTiles ? 0 : 1; }
+
 static sbmt_status single_prepare(const sbmt_image* img, void* workspace, size_t ws_bytes, CallLayout* L) {
   sbmt_status st = make_call_layout(img, 1, 0, true, L);
   if (st != SBMT_OK) return st;
@@ -2387,10 +2396,11 @@ sbmt_status sbmt_plan(sbmt_handle h, const sbmt_image* img, void* workspace, siz
   sbmt_status st = single_prepare(img, workspace, ws_bytes, &L);
   if (st != SBMT_OK) return st;
   hipStream_t s = (hipStream_t)stream;
-  const Shared sh = shared_of(L, workspace, 1);
+  const int rbi = single_rbi(L);
+  const Shared sh = shared_of(L, workspace, rbi);
   OneSrc src;
   src.d = img_of(L, 0, *img, workspace, nullptr);
-  if ((st = launch_front(L, src, nullptr, sh, 1, sizes_to(L, sh, src.d, nullptr, h->pinned), s)) != SBMT_OK) return st;
+  if ((st = launch_front(L, src, nullptr, sh, rbi, sizes_to(L, sh, src.d, nullptr, h->pinned), s)) != SBMT_OK) return st;
   if (!scan_writes_sizes(L)) {
     if ((st = launch_sizes(L, src, sh, nullptr, s)) != SBMT_OK) return st;
     if (hipMemcpyAsync(h->pinned, sh.sizes, kSizeWords * sizeof(int64_t), hipMemcpyDeviceToHost, s) != hipSuccess)
@@ -2409,7 +2419,8 @@ sbmt_status sbmt_run(sbmt_handle h, const sbmt_image* img, void* workspace, size
   CallLayout L;
   sbmt_status st = single_prepare(img, workspace, ws_bytes, &L);
   if (st != SBMT_OK) return st;
-  const Shared sh = shared_of(L, workspace, 1);
+  const int rbi = single_rbi(L);
+  const Shared sh = shared_of(L, workspace, rbi);
   // the plan's totals bound every write; capacities are the totals themselves
   sbmt_outputs o;
   o.verts = verts;
@@ -2419,7 +2430,7 @@ sbmt_status sbmt_run(sbmt_handle h, const sbmt_image* img, void* workspace, size
   o.tri_cap = INT64_MAX;
   OneSrc src;
   src.d = img_of(L, 0, *img, workspace, &o);
-  return launch_emit(L, src, nullptr, sh, 1, (hipStream_t)stream);
+  return launch_emit(L, src, nullptr, sh, rbi, (hipStream_t)stream);
 }
 
 sbmt_status sbmt_mesh_async(sbmt_handle h, const sbmt_image* img, void* workspace, size_t ws_bytes, double* verts,
@@ -2430,7 +2441,8 @@ sbmt_status sbmt_mesh_async(sbmt_handle h, const sbmt_image* img, void* workspac
   sbmt_status st = single_prepare(img, workspace, ws_bytes, &L);
   if (st != SBMT_OK) return st;
   hipStream_t s = (hipStream_t)stream;
-  const Shared sh = shared_of(L, workspace, 1);
+  const int rbi = single_rbi(L);
+  const Shared sh = shared_of(L, workspace, rbi);
   sbmt_outputs o;
   o.verts = verts;
   o.tris = tris;
@@ -2439,8 +2451,8 @@ sbmt_status sbmt_mesh_async(sbmt_handle h, const sbmt_image* img, void* workspac
   o.tri_cap = tri_cap;
   OneSrc src;
   src.d = img_of(L, 0, *img, workspace, &o);
-  if ((st = launch_front(L, src, nullptr, sh, 1, sizes_to(L, sh, src.d, sizes_dev, nullptr), s)) != SBMT_OK) return st;
-  if ((st = launch_emit(L, src, nullptr, sh, 1, s)) != SBMT_OK) return st;
+  if ((st = launch_front(L, src, nullptr, sh, rbi, sizes_to(L, sh, src.d, sizes_dev, nullptr), s)) != SBMT_OK) return st;
+  if ((st = launch_emit(L, src, nullptr, sh, rbi, s)) != SBMT_OK) return st;
   return scan_writes_sizes(L) ? SBMT_OK : launch_sizes(L, src, sh, sizes_dev, s);
 }
 
