@@ -134,15 +134,25 @@ struct OneSrc {
 struct ManySrc {
   const Img* d;
   int n;
+  // The largest i with tab[i] <= b, for a uniform b and whole waves: 64 entries
+  // are compared at a time (one load where a binary search over 64 images waits
+  // for six, one after the other, at the start of every block).
   __device__ __forceinline__ int find(int64_t b, const int64_t* tab, int64_t& local) const {
-    int lo = 0, hi = n - 1;  // largest i with tab[i] <= b
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (tab[mid] <= b) lo = mid;
-      else hi = mid - 1;
+    const int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    int lo = 0, cnt = n;  // the candidates; tab[lo] <= b
+    for (;;) {
+      const int step = (cnt + 63) / 64, j = lane * step;
+      const int64_t t = tab[lo + min(j, cnt - 1)];
+      const int at = (int)__popcll(__ballot(j < cnt && t <= b)) - 1;
+      lo += at * step;
+      cnt = min(step, cnt - at * step);
+      if (cnt == 1) {
+        const uint32_t t0 = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)t, at);
+        const uint32_t t1 = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)t >> 32), at);
+        local = b - (int64_t)(((uint64_t)t1 << 32) | t0);
+        return lo;
+      }
     }
-    local = b - tab[lo];
-    return lo;
   }
   __device__ __forceinline__ const Img& img(int i) const { return d[i]; }
 };
@@ -191,34 +201,47 @@ __device__ __forceinline__ int wave_incl_scan_dpp(int x) {
 
 // ---------------------------------------------------------------------------
 // Coarse raster: bit (R + ring, C + ringC) = [2 * #fg pixels of block (R, C) >= s^2].
-// A block covers kCoarsenRows stored rows and 256 stored columns.  Its pixel
+// A block covers coarsen_rows stored rows and 256 stored columns.  Its pixel
 // rectangle is read with aligned 16-byte loads (a load never leaves the page
 // of the bytes it is for) and folded into per-pixel-row bit masks in LDS;
 // then one lane per sample counts its s x s block with popcounts and the
 // samples of a wave are packed by a ballot.  Samples outside the image (the
 // ring) are background.
-// Blocks per image: ceil(wpr / 8) x ceil((CH + 2 ring) / kCoarsenRows).
+// Blocks per image: ceil(wpr / 8) x ceil((CH + 2 ring) / coarsen_rows), then
+// those of its row and column tables (coarsen_blocks).
 // ---------------------------------------------------------------------------
-constexpr int kCoarsenRows = 8;
+// Stored rows per block by stride: 12 to 18 pixel rows whatever the stride (eight
+// rows at stride 6 were 48 pixel rows, few blocks and long ones).  With that, and
+// a mask word written by one thread where it was or-ed together by several:
+// 1024^2 at grid edge 1.5 10.4 -> 5.4 us, 64 images of 1024^2 at grid edges 1, 2
+// and 4 62 -> 54 us (nine tenths of it now instructions: a sample costs a shift
+// and a popcount per pixel row).
 constexpr int kCoarsenMaxS = 9;
-constexpr int kCoarsenWords = (256 * kCoarsenMaxS + 15 + kCoarsenMaxS + 31) / 32 + 2;  // mask words per pixel row
+constexpr int kCoarsenPixelRows = 18;
+__host__ __device__ constexpr int coarsen_rows(int s) { return s <= 2 ? 8 : (s <= 4 ? 4 : 2); }
+static_assert(9 * coarsen_rows(9) <= kCoarsenPixelRows && 6 * coarsen_rows(6) <= kCoarsenPixelRows &&
+              4 * coarsen_rows(4) <= kCoarsenPixelRows && 2 * coarsen_rows(2) <= kCoarsenPixelRows, "the masks' rows");
+constexpr int kCoarsenWords = (256 * kCoarsenMaxS + 15 + 32) / 32 + 2;  // mask words per pixel row
+
+// Bit j = byte j of the eight bytes a, b is nonzero: each nonzero byte becomes 1
+// and counts for its bit in a byte-wise dot product.
+__device__ __forceinline__ uint32_t nz8(uint32_t a, uint32_t b) {
+  const uint32_t ta = ((((a & 0x7f7f7f7fu) + 0x7f7f7f7fu) | a) >> 7) & 0x01010101u;
+  const uint32_t tb = ((((b & 0x7f7f7f7fu) + 0x7f7f7f7fu) | b) >> 7) & 0x01010101u;
+  return __builtin_amdgcn_udot4(ta, 0x08040201u, __builtin_amdgcn_udot4(tb, 0x80402010u, 0u, false), false);
+}
 
 // Stride 2 with 16-byte aligned rows: four lanes make one raster word, each
 // from one aligned 16-byte load of the two pixel rows of its 8 samples; a
 // 2 x 2 block is foreground iff at least two of its pixels are (both of a
 // pair, or one of each pair).
 __device__ __forceinline__ void coarsen_s2(const Img& d, const Geo& g, int bx, int ry) {
-  auto nz4 = [](uint32_t w) {  // bit j = byte j is nonzero
-    uint32_t t = (((w & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w) & 0x80808080u;
-    t >>= 7;
-    return (t | (t >> 7) | (t >> 14) | (t >> 21)) & 15u;
-  };
   auto load16 = [&](int y, int x) -> uint32_t {  // nonzero bits of pixels x .. x+15 of row y (0 outside)
     if (y < 0 || y >= g.H || x + 16 <= 0 || x >= g.W) return 0u;
     const uint8_t* row = d.bm + (int64_t)y * g.stride;
     if (x >= 0 && x + 16 <= g.W) {
       const uint4 v = *reinterpret_cast<const uint4*>(row + x);
-      return nz4(v.x) | (nz4(v.y) << 4) | (nz4(v.z) << 8) | (nz4(v.w) << 12);
+      return nz8(v.x, v.y) | (nz8(v.z, v.w) << 8);
     }
     uint32_t m = 0;  // the chunk at the row's end
     for (int j = 0; j < 16; ++j)
@@ -226,7 +249,7 @@ __device__ __forceinline__ void coarsen_s2(const Img& d, const Geo& g, int bx, i
     return m;
   };
   const int task = threadIdx.x >> 2, part = threadIdx.x & 3;
-  const int rr = ry * kCoarsenRows + (task >> 3), w = 8 * bx + (task & 7);  // stored row, raster word
+  const int rr = ry * coarsen_rows(2) + (task >> 3), w = 8 * bx + (task & 7);  // stored row, raster word
   const int C0 = 32 * w - kRingC + 8 * part, R = rr - kRing;                  // first coarse column, coarse row
   uint32_t bits = 0;
   if (R >= 0 && R < g.CH) {
@@ -243,13 +266,13 @@ __device__ __forceinline__ void coarsen_s2(const Img& d, const Geo& g, int bx, i
   if (part == 0 && rr < g.CH + 2 * kRing && w < g.wpr) d.bits[(int64_t)rr * g.wpr + w] = bits;
 }
 
-// The row table (kRowPad rows past the grid, too) and the column table (window
-// column and x reach of column i in rows of parity o) of an image, spread over
-// its coarsening blocks.
-__device__ __forceinline__ void geometry_tables(const Img& d, const Geo& g, int local, int nblocks) {
-  const int first = local * 256 + (int)threadIdx.x, step = nblocks * 256;
-  for (int k = first; k < g.NK + kRowPad; k += step) d.rows[k] = row_table_entry(g, k);
-  for (int j = first; j < 2 * g.NI; j += step) {
+// Entry t of the row table (kRowPad rows past the grid, too), then of the column
+// table (window column and x reach of column i in rows of parity o).
+__device__ __forceinline__ void geometry_table(const Img& d, const Geo& g, int t) {
+  const int k = t, j = t - (g.NK + kRowPad);
+  if (k < g.NK + kRowPad) {
+    d.rows[k] = row_table_entry(g, k);
+  } else if (j < 2 * g.NI) {
     const int i = j >> 1, o = j & 1;
     const int X = g.X0 + 4 * g.h * i + 2 * g.h * o, Clo = clo_of(g, X);
     int x0, x1;
@@ -260,7 +283,7 @@ __device__ __forceinline__ void geometry_tables(const Img& d, const Geo& g, int 
 
 template <class Src>
 __global__ void __launch_bounds__(256) k_coarsen(Src src, const int64_t* __restrict__ tab, Shared sh) {
-  __shared__ uint32_t mask[kCoarsenRows * kCoarsenMaxS][kCoarsenWords];
+  __shared__ uint32_t mask[kCoarsenPixelRows][kCoarsenWords];
   int64_t local;
   const int ii = src.find(blockIdx.x, tab, local);
   const Img& d = src.img(ii);
@@ -279,50 +302,52 @@ __global__ void __launch_bounds__(256) k_coarsen(Src src, const int64_t* __restr
        q += (int64_t)gridDim.x * blockDim.x)
     sh.segacc[q] = 0ull;
   if (blockIdx.x == 0 && threadIdx.x < kDenseLists) sh.dctr[threadIdx.x] = 0ull;
-  geometry_tables(d, g, (int)local, nbx * ((g.CH + 2 * kRing + kCoarsenRows - 1) / kCoarsenRows));
+  const int crows = coarsen_rows(g.s), nby = (g.CH + 2 * kRing + crows - 1) / crows;
+  if (ry >= nby) {  // the image's last blocks: its tables
+    geometry_table(d, g, ((int)local - nbx * nby) * 256 + (int)threadIdx.x);
+    return;
+  }
   if (g.s == 2 && (((uintptr_t)d.bm | (uintptr_t)g.stride) & 15u) == 0) {  // uniform per image
     coarsen_s2(d, g, (int)local % nbx, (int)local / nbx);
     return;
   }
   const int s = g.s;
-  const int rr0 = ry * kCoarsenRows;                 // first stored row
+  const int rr0 = ry * crows;                        // first stored row
   const int C0 = 256 * bx - kRingC;                  // first coarse column of the block
   const int R0 = rr0 - kRing;                        // first coarse row
   const int xa = s * max(C0, 0), xb = min(s * (C0 + 256), g.W);  // pixel columns
-  const int pa = s * max(R0, 0), pb = min(s * (R0 + kCoarsenRows), g.H);  // pixel rows
+  const int pa = s * max(R0, 0), pb = min(s * (R0 + crows), g.H);  // pixel rows
   const int npr = max(pb - pa, 0);
-  const int nw = (xb - xa + 15 + s + 31) / 32 + 2;
-  for (int t = threadIdx.x; t < npr * nw; t += blockDim.x) mask[t / nw][t - (t / nw) * nw] = 0u;
-  __syncthreads();
-  if (xb > xa && npr > 0) {
-    // 16-byte chunks covering bytes xa .. xb-1 of each pixel row; bit
-    // (x - xa + 15) of the row mask = pixel x is foreground
-    const int nchm = (xb - xa + 15) / 16 + 1;  // chunks per row, at most
-    for (int t = threadIdx.x; t < npr * nchm; t += blockDim.x) {
-      const int pr = t / nchm, q = t - pr * nchm;
-      const uint8_t* row = d.bm + (int64_t)(pa + pr) * g.stride;
-      const uintptr_t lo = ((uintptr_t)(row + xa)) & ~(uintptr_t)15;
-      const uintptr_t hi = ((uintptr_t)(row + xb - 1)) & ~(uintptr_t)15;
-      if (lo + 16 * (uintptr_t)q <= hi) {
-        const uint4 v = *reinterpret_cast<const uint4*>(lo + 16 * (uintptr_t)q);
-        const int rel = (int)((lo + 16 * (uintptr_t)q) - (uintptr_t)(row + xa));  // pixel of byte 0, minus xa
-        // bit j = byte j is nonzero (four bytes per word at once), then only
-        // the bytes of pixels xa .. xb-1 are kept
-        auto nz4 = [](uint32_t w) {
-          uint32_t t = (((w & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w) & 0x80808080u;
-          t >>= 7;
-          return (t | (t >> 7) | (t >> 14) | (t >> 21)) & 15u;
-        };
-        const int blo = max(0, -rel), bhi = min(16, xb - xa - rel);
-        const uint32_t inmask = bhi > blo ? (((1u << bhi) - 1u) & ~((1u << blo) - 1u)) : 0u;
-        const uint32_t bits = (nz4(v.x) | (nz4(v.y) << 4) | (nz4(v.z) << 8) | (nz4(v.w) << 12)) & inmask;
-        if (bits) {
-          const int p = rel + 15;  // >= 0
-          const uint64_t sh64 = (uint64_t)bits << (p & 31);
-          atomicOr(&mask[pr][p >> 5], (uint32_t)sh64);
-          if (sh64 >> 32) atomicOr(&mask[pr][(p >> 5) + 1], (uint32_t)(sh64 >> 32));
-        }
-      }
+  // a pixel row's mask starts at the aligned chunk that holds pixel xa: bit
+  // (x - xa + off) = pixel x is foreground, off = address of pixel xa mod 16.  A
+  // thread takes a chunk, its 16 bits go to LDS as they are; every chunk of a
+  // round is loaded before the first is looked at (one beyond the row's bytes is
+  // another of the row).
+  constexpr int kAtOnce = 3;
+  const int nch = (256 * s + 15 + 32) / 16;  // chunks a sample of the block can look at
+  const uint32_t inv = 0xffffffffu / (uint32_t)nch + 1u;  // t / nch = mulhi(t, inv) for t < 2^16
+  const int tasks = xb > xa ? npr * nch : 0;
+  for (int t0 = threadIdx.x; t0 < tasks; t0 += kAtOnce * 256) {
+    uint4 v[kAtOnce];
+    int pq[kAtOnce], lo[kAtOnce], hi[kAtOnce];
+#pragma unroll
+    for (int u = 0; u < kAtOnce; ++u) {
+      const int t = min(t0 + 256 * u, tasks - 1), pr = (int)__umulhi((uint32_t)t, inv), q = t - pr * nch;
+      const uintptr_t first = (uintptr_t)(d.bm + (int64_t)(pa + pr) * g.stride + xa);
+      const int off = (int)(first & 15), len = xb - xa;
+      const bool in = 16 * q < off + len;  // the chunk holds a byte of the row
+      v[u] = *reinterpret_cast<const uint4*>(first - off + (in ? 16 * q : 0));
+      pq[u] = (pr << 16) | q;
+      lo[u] = q == 0 ? off : 0;
+      hi[u] = in ? min(16, off + len - 16 * q) : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < kAtOnce; ++u) {
+      if (t0 + 256 * u >= tasks) break;
+      const uint32_t m = nz8(v[u].x, v[u].y) | (nz8(v[u].z, v[u].w) << 8);
+      // only the bytes of pixels xa .. xb-1
+      const uint32_t keep = hi[u] > lo[u] ? ((1u << hi[u]) - 1u) & (~0u << lo[u]) : 0u;
+      reinterpret_cast<uint16_t*>(mask[pq[u] >> 16])[pq[u] & 0xffff] = (uint16_t)(m & keep);
     }
   }
   __syncthreads();
@@ -330,19 +355,21 @@ __global__ void __launch_bounds__(256) k_coarsen(Src src, const int64_t* __restr
   const int cc = 256 * bx + threadIdx.x;  // stored column
   const int C = cc - kRingC;
   const int nrows = g.CH + 2 * kRing;
-  for (int r = 0; r < kCoarsenRows; ++r) {
+  const uint32_t smask = (1u << s) - 1u;
+  const uint32_t align0 = (uint32_t)((uintptr_t)(d.bm + (int64_t)pa * g.stride + xa) & 15), alignd = (uint32_t)(g.stride & 15);
+  for (int r = 0; r < crows; ++r) {
     const int rr = rr0 + r;
     if (rr >= nrows) break;
     const int R = rr - kRing;
     int fg = 0;
     if (C >= 0 && C < g.CW && R >= 0 && R < g.CH) {
-      const int x0 = s * C - xa + 15;  // bit of the block's first pixel
       int cnt = 0;
       for (int dr = 0; dr < s; ++dr) {
         const int pr = s * R + dr - pa;
         if (pa + pr >= g.H) break;
-        const uint64_t m = (uint64_t)mask[pr][x0 >> 5] | ((uint64_t)mask[pr][(x0 >> 5) + 1] << 32);
-        cnt += __builtin_popcountll((m >> (x0 & 31)) & ((1ull << s) - 1ull));
+        const int x = s * C - xa + (int)((align0 + (uint32_t)pr * alignd) & 15u);  // bit of the sample's first pixel
+        const uint32_t m = __builtin_amdgcn_alignbit(mask[pr][(x >> 5) + 1], mask[pr][x >> 5], (uint32_t)x & 31u);
+        cnt += __builtin_popcount(m & smask);
       }
       fg = 2 * cnt >= s * s;
     }
@@ -1940,6 +1967,11 @@ static sbmt_status make_geo(const sbmt_image* img, Geo* out, bool need_ptr) {
 static int rb_index(int rb) { return rb == 4 ? 0 : (rb == 8 ? 1 : (rb == 16 ? 2 : -1)); }
 static const int kRBs[3] = {4, 8, 16};
 
+static int64_t coarsen_blocks(const Geo& g) {
+  return (int64_t)((g.wpr + 7) / 8) * ((g.CH + 2 * kRing + coarsen_rows(g.s) - 1) / coarsen_rows(g.s)) +
+         (g.NK + kRowPad + 2LL * g.NI + 255) / 256;
+}
+
 // Workspace of a call on n images: shared scratch, then per-image regions.
 struct CallLayout {
   int n = 0;
@@ -1981,7 +2013,7 @@ static sbmt_status make_call_layout(const sbmt_image* imgs, int n, int64_t recor
     L.seg0[i] = L.nseg;
     L.nseg += (int64_t)g.NK * g.NCB;
     L.owners += (int64_t)g.NK * g.NI;
-    const int64_t cblk = (int64_t)((g.wpr + 7) / 8) * ((g.CH + 2 * kRing + kCoarsenRows - 1) / kCoarsenRows);
+    const int64_t cblk = coarsen_blocks(g);
     tab_row(L, 0)[i + 1] = tab_row(L, 0)[i] + cblk;
     for (int r = 0; r < 3; ++r) {
       const int64_t rows = (g.NK + kRBs[r] - 1) / kRBs[r];
