@@ -2814,7 +2814,8 @@ static PreArgs pre_args(const PreLayout& PL, char* w, double a, double b, double
   P.ovcap = 0;
   P.used = PL.off_used ? (uint8_t*)(w + PL.off_used) : nullptr;
   P.usedcap = PL.off_used ? PL.nown + PL.nmid : 0;
-  P.vmap = PL.off_vmap ? (int32_t*)(w + PL.off_vmap) : nullptr;
+  P.uword = PL.off_uword ? (PreUsed*)(w + PL.off_uword) : nullptr;
+  P.inside = PL.off_inside ? (uint64_t*)(w + PL.off_inside) : nullptr;
   P.vbsum = PL.off_vbsum ? (int64_t*)(w + PL.off_vbsum) : nullptr;
   P.nused = PL.off_nused ? (int64_t*)(w + PL.off_nused) : nullptr;
   P.tlist = PL.off_tlist ? (int32_t*)(w + PL.off_tlist) : nullptr;
@@ -2827,8 +2828,8 @@ static PreArgs pre_args(const PreLayout& PL, char* w, double a, double b, double
   P.ccap = PL.off_cstore ? PL.ccap : 0;
   return P;
 }
-// Steps 1-3 (the grid, with its triangles when `triangles`), then the sizes
-// record at PL.off_out.
+// Steps 1-3 (the grid, when `triangles` with every vertex and its triangles, else
+// only what moved), then the sizes record at PL.off_out.
 static sbmt_status pre_launch_grid(const PreLayout& PL, const OneSrc& src, const PreArgs& P, const Shared& sh, char* w,
                                    bool triangles, hipStream_t s) {
   const Geo& g = PL.L.g[0];
@@ -2840,16 +2841,21 @@ static sbmt_status pre_launch_grid(const PreLayout& PL, const OneSrc& src, const
   if ((int64_t)g.NK * nchunk > 0x7fffffffLL) return SBMT_E_INVALID_ARG;
   if (ncb > 0x7fffffffLL || nseg > 0x7fffffffLL || nwb > 0x7fffffffLL) return SBMT_E_INVALID_ARG;
   hipLaunchKernelGGL(k_coarsen<OneSrc>, dim3((unsigned)ncb), dim3(256), 0, s, src, (const int64_t*)nullptr, sh);
-  hipLaunchKernelGGL(k_pre_clear, dim3(1024), dim3(256), 0, s, P, PL.nmid);
-  hipLaunchKernelGGL(k_pre_lattice, dim3((unsigned)(g.NK * nchunk)), dim3(256), 0, s, src, P, nchunk);
+  hipLaunchKernelGGL(k_pre_clear, dim3(1024), dim3(256), 0, s, P, PL.nmid, PL.nown);
+  if (triangles) hipLaunchKernelGGL(k_pre_lattice, dim3((unsigned)(g.NK * nchunk)), dim3(256), 0, s, src, P, nchunk);
   hipLaunchKernelGGL(k_pre_snap, dim3((unsigned)nwb), dim3(256), 0, s, src, P);
   hipLaunchKernelGGL(k_pre_repel, dim3((unsigned)nwb), dim3(256), 0, s, src, P);
-  hipLaunchKernelGGL(k_pre_split, dim3((unsigned)nwb), dim3(256), 0, s, src, P);
-  hipLaunchKernelGGL(k_pre_count, dim3((unsigned)nqb), dim3(256), 0, s, src, P, sh);
+  if (triangles) {
+    hipLaunchKernelGGL(k_pre_split<true>, dim3((unsigned)nwb), dim3(256), 0, s, src, P);
+    hipLaunchKernelGGL(k_pre_count<true>, dim3((unsigned)nqb), dim3(256), 0, s, src, P, sh);
+  } else {
+    hipLaunchKernelGGL(k_pre_split<false>, dim3((unsigned)nwb), dim3(256), 0, s, src, P);
+    hipLaunchKernelGGL(k_pre_count<false>, dim3((unsigned)nqb), dim3(256), 0, s, src, P, sh);
+  }
   if (launch_scan(PL.L, sh, kNoSizes, s) != SBMT_OK) return SBMT_E_DEVICE;
   hipLaunchKernelGGL(k_pre_inserted, dim3((unsigned)nqb), dim3(256), 0, s, src, P, sh);
   if (triangles) hipLaunchKernelGGL(k_pre_triangles, dim3((unsigned)nqb), dim3(256), 0, s, src, P, sh);
-  hipLaunchKernelGGL(k_pre_sizes, dim3(1), dim3(1), 0, s, src, P, sh, (int64_t*)(w + PL.off_out));
+  hipLaunchKernelGGL(k_pre_sizes, dim3(1), dim3(64), 0, s, src, P, sh, (int64_t*)(w + PL.off_out));
   return hipGetLastError() == hipSuccess ? SBMT_OK : SBMT_E_DEVICE;
 }
 static sbmt_status pre_read_sizes(sbmt_handle h, const int64_t* dev, int n, int64_t* counts, hipStream_t s) {
@@ -2927,7 +2933,6 @@ static sbmt_status pre_mesh_prepare(sbmt_handle h, const sbmt_image* img, double
   PreArgs& P = o->P;
   P = pre_args(PL, o->w, a, b, c);
   P.verts = (double*)(o->w + PL.off_gverts);
-  P.on_polyline = (uint8_t*)(o->w + PL.off_onp);
   P.vcap = PL.nown + PL.nmid;
   P.overts = verts;
   P.ovcap = vert_cap;
@@ -2967,7 +2972,7 @@ static sbmt_status pre_mesh_plan(sbmt_handle h, const PreCall& C, hipStream_t s)
   hipLaunchKernelGGL(k_pre_mesh_segsum, dim3((unsigned)nqb), dim3(256), 0, s, src, P, sh);
   if (launch_scan(PL.L, sh, kNoSizes, s) != SBMT_OK) return SBMT_E_DEVICE;
   hipLaunchKernelGGL(k_pre_vscan_count, dim3((unsigned)PL.nvblk), dim3(256), 0, s, P);
-  hipLaunchKernelGGL(k_pre_vscan_top, dim3(1), dim3(256), 0, s, P, PL.nvblk);
+  hipLaunchKernelGGL(k_pre_vscan_top, dim3(1), dim3(1024), 0, s, P, PL.nvblk);
   return hipGetLastError() == hipSuccess ? SBMT_OK : SBMT_E_DEVICE;
 }
 // The planned output.
@@ -2977,11 +2982,11 @@ static sbmt_status pre_mesh_write(sbmt_handle h, const PreCall& C, hipStream_t s
   const Shared& sh = C.sh;
   const OneSrc& src = C.src;
   const int64_t nqb = (PL.L.nseg + 3) / 4;
-  hipLaunchKernelGGL(k_pre_vscan_apply, dim3((unsigned)PL.nvblk), dim3(256), 0, s, P);
-  hipLaunchKernelGGL(k_pre_mesh_vbase, dim3((unsigned)nqb), dim3(256), 0, s, src, P, sh);
+  hipLaunchKernelGGL(k_pre_vscan_apply, dim3((unsigned)((P.usedcap + 64 * kPreApplyWords - 1) / (64 * kPreApplyWords))),
+                     dim3(256), 0, s, src, P);
   hipLaunchKernelGGL(k_pre_mesh_triangles, dim3((unsigned)nqb), dim3(256), 0, s, src, P, sh);
   hipLaunchKernelGGL(k_pre_mesh_whole_tris, pre_resident(h, (const void*)&k_pre_mesh_whole_tris), dim3(256), 0, s, src, P);
-  hipLaunchKernelGGL(k_pre_cut_write, pre_resident(h, (const void*)&k_pre_cut_write), dim3(256), 0, s, P);
+  hipLaunchKernelGGL(k_pre_cut_write, pre_resident(h, (const void*)&k_pre_cut_write), dim3(256), 0, s, src, P);
   hipLaunchKernelGGL(k_pre_mesh_cut_rest, pre_resident(h, (const void*)&k_pre_mesh_cut_rest), dim3(256), 0, s, src, P);
   return hipGetLastError() == hipSuccess ? SBMT_OK : SBMT_E_DEVICE;
 }
