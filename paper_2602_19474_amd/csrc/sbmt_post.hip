@@ -22,6 +22,8 @@
 #include <stdint.h>
 #include <string.h>
 
+#include <algorithm>
+
 #include "../../include/sbmt.h"
 #include "../../include/sbmt_post.h"
 
@@ -169,10 +171,14 @@ __device__ __forceinline__ Part part_empty() {
   return p;
 }
 
-// Fixed-order tree over the workgroup's parts in LDS; the result is in ps[0].
-__device__ __forceinline__ void part_tree(Part* ps) {
+// Fixed-order tree over the workgroup's parts (thread i takes that of i + w, w =
+// 128, 64, .., 1), those handed over in LDS: half of them at once, so that the histogram,
+// not the reduction, decides the workgroup's LDS.  The result is thread 0's.
+__device__ __forceinline__ void part_tree(Part& p, Part* ps) {
   for (int w = kThreads / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) part_merge(ps[threadIdx.x], ps[threadIdx.x + w]);
+    if ((int)threadIdx.x >= w && (int)threadIdx.x < 2 * w) ps[threadIdx.x - w] = p;
+    __syncthreads();
+    if ((int)threadIdx.x < w) part_merge(p, ps[threadIdx.x]);
     __syncthreads();
   }
 }
@@ -180,7 +186,8 @@ __device__ __forceinline__ void part_tree(Part* ps) {
 __global__ void k_quality_init(sbmt_quality* __restrict__ out, unsigned long long* __restrict__ ghist,
                                SelState* __restrict__ st) {
   for (int i = threadIdx.x; i < kBins; i += blockDim.x) out->angle_hist[i] = 0;
-  for (int i = threadIdx.x; i < 2 << kMaxDigit; i += blockDim.x) ghist[i] = 0;
+  for (int i = 2 * threadIdx.x; i < 2 << kMaxDigit; i += 2 * blockDim.x)
+    *reinterpret_cast<ulonglong2*>(ghist + i) = make_ulonglong2(0ull, 0ull);
   if (threadIdx.x == 0) {
     st->prefix[0] = st->prefix[1] = 0;
     st->rank[0] = st->rank[1] = 0;
@@ -197,7 +204,7 @@ __global__ void __launch_bounds__(kThreads) k_quality(const double2* __restrict_
   // the top-digit histogram is flushed before the reduction reuses its LDS
   __shared__ union {
     unsigned int top_hist[1 << kTopDigit];  // first radix-select digit of the keys
-    Part ps[kThreads];
+    Part ps[kThreads / 2];
   } lds;
   __shared__ unsigned int hist[kBins];
   unsigned int* top_hist = lds.top_hist;
@@ -206,13 +213,29 @@ __global__ void __launch_bounds__(kThreads) k_quality(const double2* __restrict_
   for (int i = threadIdx.x; i < 1 << kTopDigit; i += kThreads) top_hist[i] = 0;
   __syncthreads();
   Part p = part_empty();
+  int n = 0, invalid = 0, nonpos = 0, sliver = 0, equi = 0;  // a thread's triangles
   unsigned int top = 0;  // bin kBins-1, the common one, counted in a register
   double shift = 0.0, s1 = 0.0, s2 = 0.0;
   const int64_t step = (int64_t)gridDim.x * kThreads;
-  for (int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x; t < nt; t += step) {
-    const int32_t ia = tris[3 * t], ib = tris[3 * t + 1], ic = tris[3 * t + 2];
+  // the next triangle's corners are asked for before this one's are used (20 M
+  // triangles 155 -> 139 us; the vertices' places and the keys are the rest of the
+  // traffic, 0.55 GB in all; at most 64 registers, for eight workgroups per compute
+  // unit, spill: 480 us)
+  int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  int32_t na = 0, nb = 0, nc = 0;
+  if (t < nt) {
+    na = tris[3 * t];
+    nb = tris[3 * t + 1];
+    nc = tris[3 * t + 2];
+  }
+  for (; t < nt; t += step) {
+    const int32_t ia = na, ib = nb, ic = nc;
+    const int64_t tn = t + step < nt ? t + step : t;
+    na = tris[3 * tn];
+    nb = tris[3 * tn + 1];
+    nc = tris[3 * tn + 2];
     if (ia < 0 || ib < 0 || ic < 0 || ia >= nv || ib >= nv || ic >= nv) {
-      ++p.invalid;
+      ++invalid;
       keys[t] = ~0ull;
       hist_add(top_hist, (1u << kTopDigit) - 1u);
       continue;
@@ -229,13 +252,13 @@ __global__ void __launch_bounds__(kThreads) k_quality(const double2* __restrict_
     keys[t] = key;
     hist_add(top_hist, (unsigned int)(key >> (64 - kTopDigit)));
     p.armax = p.armax > key ? p.armax : key;
-    p.nonpos += cross <= 0.0;
-    p.equi += lmax > 0.0 && lmax - lmin <= 1e-6 * lmax;
+    nonpos += cross <= 0.0;
+    equi += lmax > 0.0 && lmax - lmin <= 1e-6 * lmax;
     // the smallest angle is opposite the shortest edge (first of equal ones)
     const int j = l1 < l0 ? (l2 < l1 ? 2 : 1) : (l2 < l0 ? 2 : 0);
     const double den = j == 0 ? l1 * l2 : (j == 1 ? l2 * l0 : l0 * l1);
     const double q = den > 0.0 ? (cross * cross) / den : 0.0;
-    p.sliver += q < th.sliver;
+    sliver += q < th.sliver;
     if (q >= th.bin[kBins - 1]) {
       ++top;
     } else {
@@ -250,12 +273,17 @@ __global__ void __launch_bounds__(kThreads) k_quality(const double2* __restrict_
     }
     p.amin = fmin(p.amin, area);
     p.amax = fmax(p.amax, area);
-    if (p.n == 0) shift = area;
+    if (n == 0) shift = area;
     const double d = area - shift;
     s1 += d;
     s2 += d * d;
-    ++p.n;
+    ++n;
   }
+  p.n = n;
+  p.invalid = invalid;
+  p.nonpos = nonpos;
+  p.sliver = sliver;
+  p.equi = equi;
   if (p.n) {
     p.mean = shift + s1 / (double)p.n;
     p.m2 = fmax(s2 - s1 * s1 / (double)p.n, 0.0);
@@ -267,24 +295,19 @@ __global__ void __launch_bounds__(kThreads) k_quality(const double2* __restrict_
   if (threadIdx.x < kBins && hist[threadIdx.x])
     atomicAdd((unsigned long long*)&out->angle_hist[threadIdx.x], (unsigned long long)hist[threadIdx.x]);
   __syncthreads();
-  ps[threadIdx.x] = p;
-  __syncthreads();
-  part_tree(ps);
-  if (threadIdx.x == 0) parts[blockIdx.x] = ps[0];
+  part_tree(p, ps);
+  if (threadIdx.x == 0) parts[blockIdx.x] = p;
 }
 
 __global__ void __launch_bounds__(kThreads) k_quality_final(const double2* __restrict__ v,
                                                             const int32_t* __restrict__ tris,
                                                             const Part* __restrict__ parts, int nparts,
                                                             sbmt_quality* __restrict__ out, SelState* __restrict__ st) {
-  __shared__ Part ps[kThreads];
+  __shared__ Part ps[kThreads / 2];
   Part p = part_empty();
   for (int i = threadIdx.x; i < nparts; i += kThreads) part_merge(p, parts[i]);
-  ps[threadIdx.x] = p;
-  __syncthreads();
-  part_tree(ps);
+  part_tree(p, ps);
   if (threadIdx.x != 0) return;
-  p = ps[0];
   const double nan = __longlong_as_double(0x7ff8000000000000ll);
   out->n_triangles = p.n;
   out->n_invalid = p.invalid;
@@ -327,31 +350,36 @@ __global__ void __launch_bounds__(kThreads) k_quality_final(const double2* __res
 
 // One radix-select pass below the top digit: histogram of the digit at
 // `shift` over the keys whose higher digits equal each target's prefix.
-// Each thread keeps kSelUnroll key loads in flight.
+// Each thread keeps kSelUnroll key loads in flight; workgroups of 1024, two per
+// compute unit beside 64 KB of bins (of 256 threads they held too few loads, and
+// cleared and merged the bins in four times as many steps: 20 M keys 44 -> 26 us,
+// 6 TB/s).
 constexpr int kSelUnroll = 8;
-__global__ void __launch_bounds__(kThreads) k_select_hist(const unsigned long long* __restrict__ keys, int64_t n,
+constexpr int kSelThreads = 1024;
+__global__ void __launch_bounds__(kSelThreads) k_select_hist(const unsigned long long* __restrict__ keys, int64_t n,
                                                           const SelState* __restrict__ st, int shift, int digit,
                                                           unsigned long long* __restrict__ ghist) {
-  __shared__ unsigned int h[2][1 << kMaxDigit];
+  __shared__ __attribute__((aligned(16))) unsigned int h[2][1 << kMaxDigit];
   if (st->n == 0) return;  // uniform: nothing counted
   const int nb = 1 << digit;
   const int ntg = st->same ? 1 : 2;
-  for (int i = threadIdx.x; i < ntg * nb; i += kThreads) h[i / nb][i % nb] = 0;
+  for (int i = 4 * threadIdx.x; i < ntg << kMaxDigit; i += 4 * kSelThreads)
+    *reinterpret_cast<uint4*>(&h[0][0] + i) = make_uint4(0u, 0u, 0u, 0u);
   __syncthreads();
   const int hi = shift + digit;  // < 64: the top digit is counted by k_quality
   const unsigned long long pre0 = st->prefix[0] >> hi, pre1 = st->prefix[1] >> hi;
   const unsigned int mask = (unsigned int)nb - 1u;
-  const int64_t chunk = (int64_t)gridDim.x * kThreads * kSelUnroll;
-  for (int64_t base = (int64_t)blockIdx.x * kThreads * kSelUnroll + threadIdx.x; base < n; base += chunk) {
+  const int64_t chunk = (int64_t)gridDim.x * kSelThreads * kSelUnroll;
+  for (int64_t base = (int64_t)blockIdx.x * kSelThreads * kSelUnroll + threadIdx.x; base < n; base += chunk) {
     unsigned long long k[kSelUnroll];
 #pragma unroll
     for (int u = 0; u < kSelUnroll; ++u) {
-      const int64_t i = base + (int64_t)u * kThreads;
+      const int64_t i = base + (int64_t)u * kSelThreads;
       k[u] = i < n ? keys[i] : 0ull;
     }
 #pragma unroll
     for (int u = 0; u < kSelUnroll; ++u) {
-      if (base + (int64_t)u * kThreads >= n) break;
+      if (base + (int64_t)u * kSelThreads >= n) break;
       const unsigned long long kh = k[u] >> hi;
       const unsigned int bin = (unsigned int)(k[u] >> shift) & mask;
       if (kh == pre0) hist_add(h[0], bin);
@@ -359,64 +387,71 @@ __global__ void __launch_bounds__(kThreads) k_select_hist(const unsigned long lo
     }
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < ntg * nb; i += kThreads) {
-    const unsigned int c = h[i / nb][i % nb];
-    if (c) atomicAdd(&ghist[(i / nb) * (1 << kMaxDigit) + i % nb], (unsigned long long)c);
+  for (int i = 4 * threadIdx.x; i < ntg << kMaxDigit; i += 4 * kSelThreads) {
+    const uint4 c = *reinterpret_cast<const uint4*>(&h[0][0] + i);
+    if (c.x) atomicAdd(&ghist[i], (unsigned long long)c.x);
+    if (c.y) atomicAdd(&ghist[i + 1], (unsigned long long)c.y);
+    if (c.z) atomicAdd(&ghist[i + 2], (unsigned long long)c.z);
+    if (c.w) atomicAdd(&ghist[i + 3], (unsigned long long)c.w);
   }
 }
 
-// Finds the digit that holds each target rank (every thread sums its run of
-// bins held in registers, a scan over the threads locates the run, its thread
-// locates the bin), extends the prefixes and clears the global histogram;
-// after the last pass writes the two percentiles.
+// Finds the digit that holds each target rank (half of the workgroup per target:
+// every thread sums its run of bins held in registers, a scan over the threads
+// locates the run, its thread locates the bin), extends the prefixes and clears
+// the global histogram; after the last pass writes the two percentiles.  A chain of
+// latencies on one compute unit: 10 us with 256 threads that took the targets in
+// turn and scanned through 16 barriers, now 7.
+constexpr int kPickThreads = 1024;
 template <int D>
-__global__ void __launch_bounds__(kThreads) k_select_pick(unsigned long long* __restrict__ ghist,
-                                                          SelState* __restrict__ st, int shift, int last,
-                                                          sbmt_quality* __restrict__ out) {
-  constexpr int per = (1 << D) / kThreads;
-  __shared__ unsigned long long part[kThreads];
+__global__ void __launch_bounds__(kPickThreads) k_select_pick(unsigned long long* __restrict__ ghist,
+                                                              SelState* __restrict__ st, int shift, int last,
+                                                              sbmt_quality* __restrict__ out) {
+  constexpr int half = kPickThreads / 2, waves = half / 64, per = (1 << D) / half;
+  __shared__ unsigned long long part[2 * waves];
   __shared__ unsigned long long pick_bin[2], pick_below[2];
   if (st->n == 0) return;
   const int same = st->same;
+  const int tg = threadIdx.x / half, th = threadIdx.x % half, wv = threadIdx.x >> 6;
   if (threadIdx.x < 2) pick_bin[threadIdx.x] = pick_below[threadIdx.x] = 0;
-  for (int tg = 0; tg < 2; ++tg) {
-    const unsigned long long* hg = ghist + (same ? 0 : tg) * (1 << kMaxDigit);
-    unsigned long long c[per], sum = 0;
+  const unsigned long long* hg = ghist + (same ? 0 : tg) * (1 << kMaxDigit);
+  unsigned long long c[per], sum = 0;
+#pragma unroll
+  for (int j = 0; j < per; ++j) {
+    c[j] = hg[th * per + j];
+    sum += c[j];
+  }
+  unsigned long long incl = sum;
+  for (int off = 1; off < 64; off <<= 1) {
+    const unsigned long long add = __shfl_up(incl, off);
+    if ((int)(threadIdx.x & 63) >= off) incl += add;
+  }
+  if ((threadIdx.x & 63) == 63) part[wv] = incl;
+  __syncthreads();  // every thread has read its bins, too
+#pragma unroll
+  for (int w = 0; w < waves; ++w) incl += tg * waves + w < wv ? part[tg * waves + w] : 0ull;
+  const unsigned long long excl = incl - sum;
+  const unsigned long long r = (unsigned long long)st->rank[tg];
+  if (r >= excl && r < incl) {
+    unsigned long long below = excl;
+    int b = 0;
 #pragma unroll
     for (int j = 0; j < per; ++j) {
-      c[j] = hg[threadIdx.x * per + j];
-      sum += c[j];
-    }
-    part[threadIdx.x] = sum;
-    __syncthreads();
-    for (int off = 1; off < kThreads; off <<= 1) {
-      const unsigned long long add = (int)threadIdx.x >= off ? part[threadIdx.x - off] : 0ull;
-      __syncthreads();
-      part[threadIdx.x] += add;
-      __syncthreads();
-    }
-    const unsigned long long incl = part[threadIdx.x], excl = incl - sum;
-    const unsigned long long r = (unsigned long long)st->rank[tg];
-    if (r >= excl && r < incl) {
-      unsigned long long below = excl;
-      int b = 0;
-#pragma unroll
-      for (int j = 0; j < per; ++j) {
-        if (b == j && below + c[j] <= r) {
-          below += c[j];
-          b = j + 1;
-        }
+      if (b == j && below + c[j] <= r) {
+        below += c[j];
+        b = j + 1;
       }
-      pick_bin[tg] = (unsigned long long)(threadIdx.x * per + b);
-      pick_below[tg] = below;
     }
-    __syncthreads();
+    pick_bin[tg] = (unsigned long long)(th * per + b);
+    pick_below[tg] = below;
   }
-  for (int i = threadIdx.x; i < 2 << kMaxDigit; i += kThreads) ghist[i] = 0;
+  for (int i = 2 * threadIdx.x; i < 2 << kMaxDigit; i += 2 * kPickThreads)
+    *reinterpret_cast<ulonglong2*>(ghist + i) = make_ulonglong2(0ull, 0ull);
+  __syncthreads();
   if (threadIdx.x == 0) {
-    for (int tg = 0; tg < 2; ++tg) {
-      st->prefix[tg] |= pick_bin[tg] << shift;
-      st->rank[tg] -= (long long)pick_below[tg];
+    for (int t = 0; t < 2; ++t) {
+      st->prefix[t] |= pick_bin[t] << shift;
+      st->rank[t] -= (long long)pick_below[t];
     }
     st->same = st->prefix[0] == st->prefix[1];
     if (last) {
@@ -521,23 +556,24 @@ sbmt_status sbmt_mesh_quality_async(sbmt_handle h, const double* verts, int64_t 
   unsigned long long* keys = (unsigned long long*)(ws + L.keys);
   hipStream_t s = (hipStream_t)stream;
   const int nq = quality_blocks(n_triangles);
-  hipLaunchKernelGGL(k_quality_init, dim3(1), dim3(kThreads), 0, s, out_dev, ghist, st);
+  hipLaunchKernelGGL(k_quality_init, dim3(1), dim3(1024), 0, s, out_dev, ghist, st);
   hipLaunchKernelGGL(k_quality, dim3(nq), dim3(kThreads), 0, s, (const double2*)verts, n_vertices, tris,
                      n_triangles, thresholds(), keys, parts, ghist, out_dev);
   hipLaunchKernelGGL(k_quality_final, dim3(1), dim3(kThreads), 0, s, (const double2*)verts, tris, parts, nq,
                      out_dev, st);
-  const int nsel = grid_for((n_triangles + kSelUnroll - 1) / kSelUnroll, kSelectBlocks);
+  const int nsel = (int)std::min<int64_t>(std::max<int64_t>((n_triangles + kSelUnroll * kSelThreads - 1) / (kSelUnroll * kSelThreads), 1),
+                                         kSelectBlocks);
   static_assert(kShift[0] + kDigit[0] == 64 && kDigit[0] == kTopDigit, "top digit");
   static_assert(kDigit[1] == 13 && kDigit[2] == 13 && kDigit[3] == 13 && kDigit[4] == 13, "digits");
   for (int pass = 0; pass < kPasses; ++pass) {
     if (pass > 0)
-      hipLaunchKernelGGL(k_select_hist, dim3(nsel), dim3(kThreads), 0, s, keys, n_triangles, st, kShift[pass],
+      hipLaunchKernelGGL(k_select_hist, dim3(nsel), dim3(kSelThreads), 0, s, keys, n_triangles, st, kShift[pass],
                          kDigit[pass], ghist);
     const int last = pass == kPasses - 1 ? 1 : 0;
     if (kDigit[pass] == 12)
-      hipLaunchKernelGGL(k_select_pick<12>, dim3(1), dim3(kThreads), 0, s, ghist, st, kShift[pass], last, out_dev);
+      hipLaunchKernelGGL(k_select_pick<12>, dim3(1), dim3(kPickThreads), 0, s, ghist, st, kShift[pass], last, out_dev);
     else
-      hipLaunchKernelGGL(k_select_pick<13>, dim3(1), dim3(kThreads), 0, s, ghist, st, kShift[pass], last, out_dev);
+      hipLaunchKernelGGL(k_select_pick<13>, dim3(1), dim3(kPickThreads), 0, s, ghist, st, kShift[pass], last, out_dev);
   }
   if (hipGetLastError() != hipSuccess) return SBMT_E_DEVICE;
   return SBMT_OK;
