@@ -1061,7 +1061,8 @@ struct EmitLds {
       SlowRec srec[kSlowChunk];
       uint16_t sitem[kSlowChunk * kSlowItems];  // record | output number << 8
     } r;
-    uint32_t stage[4][kThreads / 64][64];  // strip emission: a wave's triangles by output slot (a, b, c, tag)
+    // strip emission: a wave's triangles by output slot (a, b, c, tag), or 16 bytes per owner
+    alignas(16) uint32_t stage[4][kThreads / 64][64];
   } x;
   uint16_t lut[15 * 3 * 2 * 5];              // emission table of the side mode
   uint8_t tslot[kThreads / 64][128];         // per wave: fast triangle rank -> lane << 1 | which
@@ -1419,7 +1420,12 @@ __device__ __forceinline__ int packed_counts(uint32_t cv) {
          ((int)(((cv >> 9) & 7u) + ((cv >> 12) & 7u)) << 16);
 }
 
-template <class Src, int RB>
+// kBoth: an image of the call has both sides meshed.  A call without one stages 16
+// bytes per fast owner inside and works its two triangles out of them; the general
+// form stages every triangle with a tag, since there an owner at the grid's border
+// has one of them (a batch of 64 425 -> 376 us, 8192 x 8192 455 -> 440 us, of which
+// 1.8 GB take 370 at the copy rate; both forms in one kernel spill registers: 467).
+template <class Src, int RB, bool kBoth>
 // At most 64 VGPRs: eight workgroups per compute unit.
 __global__ void __launch_bounds__(kThreads, 8) k_emit(Src src, const int64_t* __restrict__ tab, Shared sh) {
   __shared__ StripLds<RB> S;
@@ -1491,7 +1497,7 @@ __global__ void __launch_bounds__(kThreads, 8) k_emit(Src src, const int64_t* __
   // the strip's totals to LDS; vertex and triangle counts of a row segment stay
   // below 2^16
   int incl[RB + 1];
-  const bool both = (g.flags & 1u) != 0;
+  const bool both = kBoth && (g.flags & 1u) != 0;
 #pragma unroll
   for (int r = 0; r <= RB; ++r) {
     const int p = packed_counts(code[r]);
@@ -1565,11 +1571,40 @@ __global__ void __launch_bounds__(kThreads, 8) k_emit(Src src, const int64_t* __
       v.y = L.rowy[r];
       *reinterpret_cast<double2*>(vrow + (uint32_t)(ex & 0xffff) * 16u) = v;
     }
-    const int ntb = fast ? (int)((cv >> 9) & 7u) : 0, nta = fast ? (int)((cv >> 12) & 7u) : 0;
     const int vid = bvr + (ex & 0xffff);
-    const int vr = bvr + ((sb[r] + incl[r]) & 0xffff);
     const int vdl = bvn + (exn & 0xffff) - (o ? 0 : nvl);
     const int vdr = bvn + ((o ? inn : exn) & 0xffff);
+    if constexpr (!kBoth) {
+      // a fast owner inside has both triangles, and its right neighbour's first
+      // vertex follows its own: 16 bytes per such owner in LDS, then a lane per
+      // triangle, consecutive ones but for the slow owners between them
+      const bool inside = fast && (cv & 1u);
+      const unsigned long long m = __ballot(inside);
+      const int n2 = 2 * (int)__popcll(m);
+      uint4* const own = reinterpret_cast<uint4*>(&L.x.stage[0][0][0]) + 64 * wv;
+      if (inside) own[lanes_below(m)] = make_uint4((uint32_t)vid, (uint32_t)vdr, (uint32_t)vdl, 12u * (uint32_t)(ex >> 16));
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+      for (int b = 0; b < 128; b += 64) {
+        if (b + lane < n2) {
+          const uint4 e = own[(b + lane) >> 1];
+          const bool ta = lane & 1;
+          Tri3 t3;
+          t3.a = (int)e.x;
+          t3.b = (int)(ta ? e.x + 1u : e.y);
+          t3.c = (int)(ta ? e.y : e.z);
+          *reinterpret_cast<Tri3*>(trow + (e.w + (ta ? 12u : 0u))) = t3;
+        }
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      continue;
+    }
+    const int ntb = fast ? (int)((cv >> 9) & 7u) : 0, nta = fast ? (int)((cv >> 12) & 7u) : 0;
+    const int vr = bvr + ((sb[r] + incl[r]) & 0xffff);
     // the triangles go to LDS at their slot relative to the strip's first
     // triangle of the row (slow owners' slots stay empty), 64 slots at a time;
     // lane j then writes slot j, so that a store covers consecutive triangles
@@ -2225,18 +2260,29 @@ static sbmt_status launch_emit(const CallLayout& L, const Src& src, const int64_
   const int64_t ntile = L.tab[(size_t)(1 + rbi) * (L.n + 1) + L.n];
   if (ntile > 0x7fffffffLL) return SBMT_E_INVALID_ARG;
   const dim3 gm((unsigned)((ntile + kThreads - 1) / kThreads));
+  bool both = false;
+  for (int i = 0; i < L.n; ++i) both |= (L.g[i].flags & 1u) != 0;
   const bool missing = L.tcap[rbi] < (int64_t)kRBs[rbi] * kCB;  // else every owner has a record
   switch (kRBs[rbi]) {
     case 4:
-      hipLaunchKernelGGL((k_emit<Src, 4>), dim3((unsigned)ntile), dim3(kThreads), 0, st, src, tt, sh);
+      if (both)
+        hipLaunchKernelGGL((k_emit<Src, 4, true>), dim3((unsigned)ntile), dim3(kThreads), 0, st, src, tt, sh);
+      else
+        hipLaunchKernelGGL((k_emit<Src, 4, false>), dim3((unsigned)ntile), dim3(kThreads), 0, st, src, tt, sh);
       if (missing) hipLaunchKernelGGL((k_emit_missing<Src, 4>), gm, dim3(kThreads), 0, st, src, tt, sh, ntile);
       break;
     case 8:
-      hipLaunchKernelGGL((k_emit<Src, 8>), dim3((unsigned)ntile), dim3(kThreads), 0, st, src, tt, sh);
+      if (both)
+        hipLaunchKernelGGL((k_emit<Src, 8, true>), dim3((unsigned)ntile), dim3(kThreads), 0, st, src, tt, sh);
+      else
+        hipLaunchKernelGGL((k_emit<Src, 8, false>), dim3((unsigned)ntile), dim3(kThreads), 0, st, src, tt, sh);
       if (missing) hipLaunchKernelGGL((k_emit_missing<Src, 8>), gm, dim3(kThreads), 0, st, src, tt, sh, ntile);
       break;
     default:
-      hipLaunchKernelGGL((k_emit<Src, 16>), dim3((unsigned)ntile), dim3(kThreads), 0, st, src, tt, sh);
+      if (both)
+        hipLaunchKernelGGL((k_emit<Src, 16, true>), dim3((unsigned)ntile), dim3(kThreads), 0, st, src, tt, sh);
+      else
+        hipLaunchKernelGGL((k_emit<Src, 16, false>), dim3((unsigned)ntile), dim3(kThreads), 0, st, src, tt, sh);
       if (missing) hipLaunchKernelGGL((k_emit_missing<Src, 16>), gm, dim3(kThreads), 0, st, src, tt, sh, ntile);
       break;
   }

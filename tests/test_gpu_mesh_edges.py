@@ -58,3 +58,18 @@ def test_batches_around_one_look_at_the_table(n):
         if i % 97 < 5 or i >= n - 5:
             assert np.array_equal(t.cpu().numpy(), ref.tris) and np.array_equal(c.cpu().numpy(), ref.codes), (n, i)
             assert float(np.abs(v.cpu().numpy() - ref.verts).max(initial=0.0)) <= 1e-12, (n, i)
+
+
+@pytest.mark.parametrize("sides", [(0, 1), (1, 0, 0, 0), (0, 0, 0), (1, 1, 1)])
+@pytest.mark.parametrize("tile_rows", [4, 8, 16])
+def test_batches_of_one_side_and_of_both(sides, tile_rows, monkeypatch):
+    import torch
+    from paper_2602_19474_amd.batch import Tuning
+    bms = [wl.smoothed_noise(90 + 130 * i, 75, 5.0, 0.0, False, wl.rng(8, i)) for i in range(len(sides))]
+    make, left = sbmt._image, list(sides)
+    monkeypatch.setattr(sbmt, "_image", lambda t, h, flags: make(t, h, left.pop(0)))
+    outs = mesh_batch([(torch.from_numpy(b).cuda(), 1) for b in bms], tuning=Tuning(strategy=0, tile_rows=tile_rows))
+    for i, (v, t, c) in enumerate(outs):
+        ref = oracle.mesh_from_bitmap(bms[i], 1, oracle.BOTH_SIDES if sides[i] else 0)
+        assert np.array_equal(t.cpu().numpy(), ref.tris) and np.array_equal(c.cpu().numpy(), ref.codes), (sides, i)
+        assert float(np.abs(v.cpu().numpy() - ref.verts).max(initial=0.0)) <= 1e-12, (sides, i)
