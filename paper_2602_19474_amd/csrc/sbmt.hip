@@ -117,6 +117,7 @@ struct Shared {
   unsigned long long* band;         // [nbands] fused path look-back words
   int64_t tcap, nseg, nbands, dcap;
   int nblk, n;
+  bool tall;                        // coarsening blocks of more rows (coarsen_rows)
 };
 
 // Block -> image maps.  OneSrc carries the single image by value; ManySrc
@@ -210,17 +211,21 @@ __device__ __forceinline__ int wave_incl_scan_dpp(int x) {
 // Blocks per image: ceil(wpr / 8) x ceil((CH + 2 ring) / coarsen_rows), then
 // those of its row and column tables (coarsen_blocks).
 // ---------------------------------------------------------------------------
-// Stored rows per block by stride: 12 to 18 pixel rows whatever the stride (eight
-// rows at stride 6 were 48 pixel rows, few blocks and long ones).  With that, and
-// a mask word written by one thread where it was or-ed together by several:
-// 1024^2 at grid edge 1.5 10.4 -> 5.4 us, 64 images of 1024^2 at grid edges 1, 2
-// and 4 62 -> 54 us (nine tenths of it now instructions: a sample costs a shift
-// and a popcount per pixel row).
+// Stored rows per block by stride: 12 to 18 pixel rows, so that a small image's
+// blocks cover the chip; up to 36 in calls of at least kCoarsenTall such blocks (32
+// per compute unit), where a block's fixed chain of loads counts instead.  With
+// that, and a mask word written by one thread where it was or-ed together by
+// several: 1024^2 at grid edge 1.5 10.4 -> 5.3 us (with tall blocks 7.8), 64 images
+// of up to 1024^2 at grid edges 1, 2 and 4 62 -> 51 us (short 54), 256 of up to
+// 2048^2 221 -> 206 us together with the segment counts (short 229).
 constexpr int kCoarsenMaxS = 9;
-constexpr int kCoarsenPixelRows = 18;
-__host__ __device__ constexpr int coarsen_rows(int s) { return s <= 2 ? 8 : (s <= 4 ? 4 : 2); }
-static_assert(9 * coarsen_rows(9) <= kCoarsenPixelRows && 6 * coarsen_rows(6) <= kCoarsenPixelRows &&
-              4 * coarsen_rows(4) <= kCoarsenPixelRows && 2 * coarsen_rows(2) <= kCoarsenPixelRows, "the masks' rows");
+constexpr int kCoarsenPixelRows = 36;
+constexpr int kCoarsenTall = 8192;
+__host__ __device__ constexpr int coarsen_rows(int s, bool tall) {
+  return s <= 2 ? 8 : (tall ? (s <= 4 ? 8 : 4) : (s <= 4 ? 4 : 2));
+}
+static_assert(9 * coarsen_rows(9, true) <= kCoarsenPixelRows && 4 * coarsen_rows(4, true) <= kCoarsenPixelRows &&
+              2 * coarsen_rows(2, true) <= kCoarsenPixelRows, "the masks' rows");
 constexpr int kCoarsenWords = (256 * kCoarsenMaxS + 15 + 32) / 32 + 2;  // mask words per pixel row
 
 // Bit j = byte j of the eight bytes a, b is nonzero: each nonzero byte becomes 1
@@ -249,7 +254,7 @@ __device__ __forceinline__ void coarsen_s2(const Img& d, const Geo& g, int bx, i
     return m;
   };
   const int task = threadIdx.x >> 2, part = threadIdx.x & 3;
-  const int rr = ry * coarsen_rows(2) + (task >> 3), w = 8 * bx + (task & 7);  // stored row, raster word
+  const int rr = ry * coarsen_rows(2, false) + (task >> 3), w = 8 * bx + (task & 7);  // stored row, raster word
   const int C0 = 32 * w - kRingC + 8 * part, R = rr - kRing;                  // first coarse column, coarse row
   uint32_t bits = 0;
   if (R >= 0 && R < g.CH) {
@@ -302,7 +307,7 @@ __global__ void __launch_bounds__(256) k_coarsen(Src src, const int64_t* __restr
        q += (int64_t)gridDim.x * blockDim.x)
     sh.segacc[q] = 0ull;
   if (blockIdx.x == 0 && threadIdx.x < kDenseLists) sh.dctr[threadIdx.x] = 0ull;
-  const int crows = coarsen_rows(g.s), nby = (g.CH + 2 * kRing + crows - 1) / crows;
+  const int crows = coarsen_rows(g.s, sh.tall), nby = (g.CH + 2 * kRing + crows - 1) / crows;
   if (ry >= nby) {  // the image's last blocks: its tables
     geometry_table(d, g, ((int)local - nbx * nby) * 256 + (int)threadIdx.x);
     return;
@@ -2002,8 +2007,9 @@ static sbmt_status make_geo(const sbmt_image* img, Geo* out, bool need_ptr) {
 static int rb_index(int rb) { return rb == 4 ? 0 : (rb == 8 ? 1 : (rb == 16 ? 2 : -1)); }
 static const int kRBs[3] = {4, 8, 16};
 
-static int64_t coarsen_blocks(const Geo& g) {
-  return (int64_t)((g.wpr + 7) / 8) * ((g.CH + 2 * kRing + coarsen_rows(g.s) - 1) / coarsen_rows(g.s)) +
+static int64_t coarsen_blocks(const Geo& g, bool tall) {
+  const int rows = coarsen_rows(g.s, tall);
+  return (int64_t)((g.wpr + 7) / 8) * ((g.CH + 2 * kRing + rows - 1) / rows) +
          (g.NK + kRowPad + 2LL * g.NI + 255) / 256;
 }
 
@@ -2018,6 +2024,7 @@ struct CallLayout {
   int64_t tcap[3] = {0, 0, 0};  // records per count tile, per tile height
   int64_t dcap[3] = {0, 0, 0};  // entries per dense list, per tile height
   int nblk = 0;
+  bool tall = false;  // coarsening blocks of more rows
   size_t off_ctr, off_dctr, off_imgerr, off_sizes, off_segacc, off_desc, off_tab, off_cnt, off_slow, off_segoff, off_blk, off_rec,
       off_dense, off_tilen, off_band, off_halo, total;
   bool fused_ok = true;  // per-image counts fit the fused path's int32 bases and band width
@@ -2043,12 +2050,15 @@ static sbmt_status make_call_layout(const sbmt_image* imgs, int n, int64_t recor
     sbmt_status st = make_geo(&imgs[i], &L.g[i], need_ptr);
     if (st != SBMT_OK) return st;
   }
+  int64_t short_blocks = 0;
+  for (int i = 0; i < n; ++i) short_blocks += coarsen_blocks(L.g[i], false);
+  L.tall = short_blocks >= kCoarsenTall;
   for (int i = 0; i < n; ++i) {
     const Geo& g = L.g[i];
     L.seg0[i] = L.nseg;
     L.nseg += (int64_t)g.NK * g.NCB;
     L.owners += (int64_t)g.NK * g.NI;
-    const int64_t cblk = coarsen_blocks(g);
+    const int64_t cblk = coarsen_blocks(g, L.tall);
     tab_row(L, 0)[i + 1] = tab_row(L, 0)[i] + cblk;
     for (int r = 0; r < 3; ++r) {
       const int64_t rows = (g.NK + kRBs[r] - 1) / kRBs[r];
@@ -2141,6 +2151,7 @@ static sbmt_status make_call_layout(const sbmt_image* imgs, int n, int64_t recor
 static Shared shared_of(const CallLayout& L, void* ws, int rbi) {
   char* b = (char*)ws;
   Shared s;
+  s.tall = L.tall;
   s.seg_cnt = (int4*)(b + L.off_cnt);
   s.seg_slow = (unsigned long long*)(b + L.off_slow);
   s.seg_off = (longlong4*)(b + L.off_segoff);

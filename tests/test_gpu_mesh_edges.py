@@ -73,3 +73,17 @@ def test_batches_of_one_side_and_of_both(sides, tile_rows, monkeypatch):
         ref = oracle.mesh_from_bitmap(bms[i], 1, oracle.BOTH_SIDES if sides[i] else 0)
         assert np.array_equal(t.cpu().numpy(), ref.tris) and np.array_equal(c.cpu().numpy(), ref.codes), (sides, i)
         assert float(np.abs(v.cpu().numpy() - ref.verts).max(initial=0.0)) <= 1e-12, (sides, i)
+
+
+@pytest.mark.parametrize("h", [0.5, 1, 1.5, 2.5, 3, 5, 6])
+def test_coarsening_of_many_blocks(h):
+    import torch
+    g = wl.rng(9, int(2 * h))
+    bms = [(g.random(s) < 0.5).astype(np.uint8) for s in [(37, 700), (5, 1), (71, 90)]]
+    dev = [torch.from_numpy(b).cuda() for b in bms]
+    outs = mesh_batch([(dev[i % 3], h) for i in range(2600)])
+    refs = [oracle.mesh_from_bitmap(b, h) for b in bms]
+    for i in [*range(7), *range(1000, 1012), *range(2590, 2600)]:
+        v, t, c = outs[i]
+        assert np.array_equal(t.cpu().numpy(), refs[i % 3].tris) and np.array_equal(c.cpu().numpy(), refs[i % 3].codes)
+        assert float(np.abs(v.cpu().numpy() - refs[i % 3].verts).max(initial=0.0)) <= 1e-12 * h
