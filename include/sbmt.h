@@ -208,8 +208,9 @@ typedef struct {
   int32_t groups_per_cu; /* fused: resident workgroups per compute unit (0 = default) */
   int32_t reserved;
   int64_t record_cap;    /* slow-owner records in the workspace: 0 = default
-                            (half of the owners), > 0 = that many; owners
-                            beyond it are classified where they are needed */
+                            (half of the owners; every owner in calls of few
+                            tiles), > 0 = that many; owners beyond it are
+                            classified where they are needed */
 } sbmt_tuning;
 
 /* Host only.  tuning may be NULL (multi-kernel, 8-row tiles).  The fused
