@@ -146,7 +146,9 @@ typedef struct {
 
 /* Device pointers into an assembled workspace (valid while it lives):
  * row_off [n_v + 1] int64, col [nnz] int32, val [nnz] FP64, mass [n_v] FP64,
- * boundary [n_v] uint8 (1 = on the boundary). */
+ * boundary [n_v] uint8 (1 = on the boundary).  sbmt_laplacian_apply reads
+ * row_off, col and val; sbmt_heat_steps reads mass, boundary and a copy of the
+ * rows made by sbmt_laplacian_assemble. */
 typedef struct {
   const int64_t* row_off;
   const int32_t* col;

@@ -829,12 +829,18 @@ struct Op {  // what an application of the operator reads
   int64_t nsl, cap;
 };
 
-// (K u)_i in row order.  In slices the entries of a row are loaded kAhead at a
-// time, columns, weights, then the field values, so that a wave waits for
-// memory once per kAhead entries and not once per entry; the padding of a slice
+// (K u)_i in row order from the CSR rows.
+__device__ __forceinline__ double csr_row(const Op& op, int64_t i, double ui, const double* __restrict__ u) {
+  double s = 0.0;
+  for (int64_t e = op.row_off[i], end = op.row_off[i + 1]; e < end; ++e) s += op.val[e] * (ui - u[op.col[e]]);
+  return s;
+}
+// (K u)_i of a heat step, the same sum.  In slices the entries of a row are loaded
+// kAhead at a time, columns, weights, then the field values, so that a wave waits
+// for memory once per kAhead entries and not once per entry; the padding of a slice
 // is loaded but not summed.
 constexpr int kAhead = 4;
-__device__ __forceinline__ double apply_row(const Op& op, bool sliced, int64_t i, double ui, const double* __restrict__ u) {
+__device__ __forceinline__ double step_row(const Op& op, bool sliced, int64_t i, double ui, const double* __restrict__ u) {
   double s = 0.0;
   if (sliced) {
     const int64_t q = i / kSlice, s0 = op.slice_off[q];
@@ -856,17 +862,18 @@ __device__ __forceinline__ double apply_row(const Op& op, bool sliced, int64_t i
       for (int a = 0; a < kAhead; ++a) s = e + a < len ? s + wj[a] * (ui - uj[a]) : s;
     }
   } else {
-    for (int64_t e = op.row_off[i], end = op.row_off[i + 1]; e < end; ++e) s += op.val[e] * (ui - u[op.col[e]]);
+    s = csr_row(op, i, ui, u);
   }
   return s;
 }
 
+// Reads the CSR arrays and not the steps' copy of them: sbmt_laplacian_csr hands
+// those out, and what a program writes to them is what it applies.
 __global__ void __launch_bounds__(kThreads) k_apply(Op op, int64_t nv, const double* __restrict__ u,
                                                     double* __restrict__ y) {
-  const bool sliced = op.slice_off[op.nsl] <= op.cap;  // uniform
   const int64_t step = (int64_t)gridDim.x * kThreads;
   for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < nv; i += step)
-    y[i] = apply_row(op, sliced, i, u[i], u);
+    y[i] = csr_row(op, i, u[i], u);
 }
 
 __global__ void __launch_bounds__(kThreads) k_heat_step(Op op, int64_t nv, double dt_alpha,
@@ -876,7 +883,7 @@ __global__ void __launch_bounds__(kThreads) k_heat_step(Op op, int64_t nv, doubl
   for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < nv; i += step) {
     const double ui = u[i], m = op.mass[i];
     const bool held = op.bnd[i] != 0;
-    const double s = apply_row(op, sliced, i, ui, u);
+    const double s = step_row(op, sliced, i, ui, u);
     out[i] = held ? 0.0 : ui - (dt_alpha * s) / m;
   }
 }

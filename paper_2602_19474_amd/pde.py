@@ -43,7 +43,10 @@ class Laplacian:
         return self.ws.data_ptr(), self.ws.numel(), self.nv, self.nt
 
     def csr(self) -> dict:
-        """Views of the operator's arrays inside the workspace (row_off, col, val, mass, boundary)."""
+        """Views of the operator's arrays inside the workspace (row_off, col, val, mass, boundary).
+
+        ``apply`` reads row_off, col and val; ``heat_steps`` reads mass, boundary
+        and a copy of the rows made when the operator was assembled."""
         torch = _torch()
         c = _lib.Csr()
         _lib.check(_lib.lib().sbmt_laplacian_csr(*self._args(), ctypes.byref(c)), "sbmt_laplacian_csr")
