@@ -2614,8 +2614,12 @@ __global__ void __launch_bounds__(256) k_pre_cut_write(OneSrc src, PreArgs P) {
       const int64_t w = K.eo[e];
       const int es = (int)((head >> (8 + 4 * e)) & 15u);
       const uint32_t rw = pre_owner_counts(P, g, (uint32_t)w);
+      if (pre_rc_cross(rw, es) != cnt) {  // the edge and the triangle see other crossings
+        pre_error(P);
+        eb[e] = P.ovcap;  // no row: an owner without crossings has no base (rbase is not written there)
+        continue;
+      }
       eb[e] = NV + P.rbase[w] + pre_rc_before(rw, es);
-      if (pre_rc_cross(rw, es) != cnt) pre_error(P);  // the edge and the triangle see other crossings
     }
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
