@@ -344,7 +344,10 @@ sbmt_status sbmt_preprocess_mesh(sbmt_handle h, const sbmt_image* img, double a,
  * counted, without counting again: the same image, thresholds and workspace
  * (contents untouched in between), arguments, outputs and errors as there
  * (waits for `stream`).  A sizing call and this one do the work of one call
- * with outputs large enough. */
+ * with outputs large enough, and it may be repeated.  SBMT_E_INVALID_ARG, with
+ * nothing written and the counts 0, if the last call that planned or meshed on
+ * this workspace was not such a call for an image of this size, grid_h, flags
+ * and thresholds that returned SBMT_OK or SBMT_E_CAPACITY. */
 sbmt_status sbmt_preprocess_mesh_fill(sbmt_handle h, const sbmt_image* img, double a, double b, double c,
                                       void* workspace, size_t ws_bytes, double* verts, int64_t vert_cap, int32_t* tris,
                                       uint8_t* codes, int64_t tri_cap, int64_t* counts, void* stream);

@@ -2844,6 +2844,23 @@ sbmt_status sbmt_pre_query(const sbmt_image* img, size_t* workspace_bytes, int64
 }
 
 // Arguments of the preprocessing kernels over workspace w (layout PL).
+// What a plan leaves in its workspace (pre_planned): a word made of all that its
+// indices depend on, never 0, which is what the word is cleared to.
+constexpr int kPreStampWord = 2;  // of the call's eight counters (ctr), which k_coarsen clears; 1 is the persistent kernel's
+static uint64_t pre_stamp(const Geo& g, double a, double b, double c) {
+  uint64_t x[7] = {(uint64_t)(uint32_t)g.W | ((uint64_t)(uint32_t)g.H << 32), (uint64_t)(uint32_t)g.h | ((uint64_t)(uint32_t)g.q << 32),
+                   g.flags, 0x53424d5450524531ull, 0, 0, 0};
+  memcpy(x + 4, &a, 8);
+  memcpy(x + 5, &b, 8);
+  memcpy(x + 6, &c, 8);
+  uint64_t s = 0;
+  for (uint64_t v : x) {  // each word mixed in by two odd multiplications and shifts
+    s = (s ^ v) * 0x9e3779b97f4a7c15ull;
+    s = (s ^ (s >> 32)) * 0xd6e8feb86659fd93ull;
+    s ^= s >> 29;
+  }
+  return s ? s : 1;
+}
 static PreArgs pre_args(const PreLayout& PL, char* w, double a, double b, double c) {
   PreArgs P;
   P.a = a;
@@ -2883,6 +2900,8 @@ static PreArgs pre_args(const PreLayout& PL, char* w, double a, double b, double
   P.citem = PL.off_citem ? (uint64_t*)(w + PL.off_citem) : nullptr;
   P.cstore = PL.off_cstore ? (PreCut*)(w + PL.off_cstore) : nullptr;
   P.ccap = PL.off_cstore ? PL.ccap : 0;
+  P.stamp_at = (uint64_t*)(w + PL.L.off_ctr) + kPreStampWord;
+  P.stamp = pre_stamp(PL.L.g[0], a, b, c);
   return P;
 }
 // Steps 1-3 (the grid, when `triangles` with every vertex and its triangles, else
@@ -3029,7 +3048,7 @@ static sbmt_status pre_mesh_plan(sbmt_handle h, const PreCall& C, hipStream_t s)
   hipLaunchKernelGGL(k_pre_mesh_segsum, dim3((unsigned)nqb), dim3(256), 0, s, src, P, sh);
   if (launch_scan(PL.L, sh, kNoSizes, s) != SBMT_OK) return SBMT_E_DEVICE;
   hipLaunchKernelGGL(k_pre_vscan_count, dim3((unsigned)PL.nvblk), dim3(256), 0, s, P);
-  hipLaunchKernelGGL(k_pre_vscan_top, dim3(1), dim3(1024), 0, s, P, PL.nvblk);
+  hipLaunchKernelGGL(k_pre_vscan_top, dim3(1), dim3(1024), 0, s, P, sh, PL.nvblk);
   return hipGetLastError() == hipSuccess ? SBMT_OK : SBMT_E_DEVICE;
 }
 // The planned output.
@@ -3047,9 +3066,9 @@ static sbmt_status pre_mesh_write(sbmt_handle h, const PreCall& C, hipStream_t s
   hipLaunchKernelGGL(k_pre_mesh_cut_rest, pre_resident(h, (const void*)&k_pre_mesh_cut_rest), dim3(256), 0, s, src, P);
   return hipGetLastError() == hipSuccess ? SBMT_OK : SBMT_E_DEVICE;
 }
-static sbmt_status pre_mesh_finish(sbmt_handle h, const PreCall& C, int64_t* counts, hipStream_t s) {
+static sbmt_status pre_mesh_finish(sbmt_handle h, const PreCall& C, bool fill, int64_t* counts, hipStream_t s) {
   int64_t* out2 = (int64_t*)(C.w + C.PL.off_out2);
-  hipLaunchKernelGGL(k_pre_mesh_sizes, dim3(1), dim3(1), 0, s, C.P, C.sh, out2);
+  hipLaunchKernelGGL(k_pre_mesh_sizes, dim3(1), dim3(1), 0, s, C.P, C.sh, out2, fill);
   if (hipGetLastError() != hipSuccess) return SBMT_E_DEVICE;
   const sbmt_status st = pre_read_sizes(h, out2, 8, counts, s);
   return st != SBMT_OK ? st : (sbmt_status)counts[5];
@@ -3066,7 +3085,7 @@ sbmt_status sbmt_preprocess_mesh(sbmt_handle h, const sbmt_image* img, double a,
   if ((st = pre_mesh_plan(h, C, s)) != SBMT_OK) return st;
   // a sizing call has no row to write
   if ((vert_cap > 0 || tri_cap > 0) && (st = pre_mesh_write(h, C, s)) != SBMT_OK) return st;
-  return pre_mesh_finish(h, C, counts, s);
+  return pre_mesh_finish(h, C, false, counts, s);
 }
 
 sbmt_status sbmt_preprocess_mesh_fill(sbmt_handle h, const sbmt_image* img, double a, double b, double c,
@@ -3078,7 +3097,7 @@ sbmt_status sbmt_preprocess_mesh_fill(sbmt_handle h, const sbmt_image* img, doub
   if (st != SBMT_OK) return st;
   hipStream_t s = (hipStream_t)stream;
   if ((st = pre_mesh_write(h, C, s)) != SBMT_OK) return st;
-  return pre_mesh_finish(h, C, counts, s);
+  return pre_mesh_finish(h, C, true, counts, s);
 }
 
 const char* sbmt_status_string(sbmt_status s) {

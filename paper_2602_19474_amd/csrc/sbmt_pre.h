@@ -86,10 +86,20 @@ struct PreArgs {
   uint64_t* citem;       // [ccap]: list position * 4 + grid triangle of each slot
   PreCut* cstore;        // [ccap]: its output, kept by the count pass for the triangle pass
   int64_t ccap;
+  // the workspace's stamp: what a finished plan leaves there, and what this call's image and thresholds make it
+  uint64_t* stamp_at;
+  uint64_t stamp;
 };
 constexpr int kPreVScan = 16384;  // grid vertices per block of the compaction scan
 constexpr int kPreApplyWords = 16;  // words of 64 grid vertices per block that copies the used ones
 static_assert(kPreVScan % (64 * kPreApplyWords) == 0, "in one block of the scan");
+// Whether the workspace holds the plan of this image size, edge and thresholds.
+// The passes that write the mesh follow indices and bounds from the workspace, so
+// each looks at this first: they must not run after a plan that failed, over
+// another image's, or over memory that was never planned.  The stamp is one of the
+// words that every call's k_coarsen clears, and the last pass of a plan without an
+// error sets it.
+__device__ __forceinline__ bool pre_planned(const PreArgs& P) { return *P.stamp_at == P.stamp; }
 constexpr uint8_t kPreMoved = 8;
 constexpr int kPreTally = 8;
 constexpr int kPreCounts = kPreTally + 512;
@@ -2448,6 +2458,7 @@ __global__ void __launch_bounds__(256) k_pre_mesh_segsum(OneSrc src, PreArgs P, 
 __global__ void __launch_bounds__(256) k_pre_mesh_triangles(OneSrc src, PreArgs P, Shared sh) {
   __shared__ Tri3 stage[4][128];
   __shared__ uint8_t full[4][128];
+  if (!pre_planned(P)) return;  // uniform
   const Geo g = src.d.g;
   int64_t seg;
   int k, i0;
@@ -2537,6 +2548,7 @@ __global__ void __launch_bounds__(256) k_pre_mesh_triangles(OneSrc src, PreArgs 
 __global__ void __launch_bounds__(256) k_pre_mesh_whole_tris(OneSrc src, PreArgs P) {
   __shared__ int32_t dl[256 + kPreOwners];
   __shared__ int nd;
+  if (!pre_planned(P)) return;  // uniform
   const Geo g = src.d.g;
   if (threadIdx.x == 0) nd = 0;
   __syncthreads();
@@ -2586,6 +2598,7 @@ __global__ void __launch_bounds__(256) k_pre_mesh_whole_tris(OneSrc src, PreArgs
 // triangles of an edge write the same places), the triangles to theirs, all by
 // number: a crossing is the edge owner's first one of that edge plus its order.
 __global__ void __launch_bounds__(256) k_pre_cut_write(OneSrc src, PreArgs P) {
+  if (!pre_planned(P)) return;
   const Geo g = src.d.g;
   const int64_t n = min(P.counts[4], P.ccap);
   const int64_t NV = *P.nused;
@@ -2660,7 +2673,7 @@ __global__ void __launch_bounds__(256) k_pre_cut_write(OneSrc src, PreArgs P) {
 __global__ void __launch_bounds__(256, 4) k_pre_mesh_cut_rest(OneSrc src, PreArgs P) {
   __shared__ int64_t dl[512];
   __shared__ int nd;
-  if (P.counts[4] <= P.ccap && P.counts[5] == 0) return;  // uniform
+  if (!pre_planned(P) || (P.counts[4] <= P.ccap && P.counts[5] == 0)) return;  // uniform
   const Img& d = src.d;
   const Geo g = d.g;
   if (threadIdx.x == 0) nd = 0;
@@ -2727,8 +2740,18 @@ __global__ void __launch_bounds__(256) k_pre_vscan_count(PreArgs P) {
   if (v0 < NV) P.uword[v0 >> 6] = PreUsed{bits, before, 0};
   if (threadIdx.x == 255) P.vbsum[blockIdx.x] = before + n;
 }
-__global__ void __launch_bounds__(1024) k_pre_vscan_top(PreArgs P, int64_t nblk) { pre_scan_blocks(P.vbsum, nblk, P.nused); }
+// The mesh's vertices may be numbered, and no pass before this one saw an error.
+__device__ __forceinline__ int64_t pre_mesh_status(const PreArgs& P, const Shared& sh) {
+  if (*P.nused + sh.seg_off[sh.nseg].x > 0x7fffffffLL) return SBMT_E_INDEX_OVERFLOW;
+  if (P.gsizes[5] != SBMT_OK && P.gsizes[5] != SBMT_E_CAPACITY) return P.gsizes[5];  // (no room for triangles is meant there)
+  return P.counts[2] ? SBMT_E_PROTOCOL : SBMT_OK;
+}
+__global__ void __launch_bounds__(1024) k_pre_vscan_top(PreArgs P, Shared sh, int64_t nblk) {
+  pre_scan_blocks(P.vbsum, nblk, P.nused);
+  if (threadIdx.x == 0 && pre_mesh_status(P, sh) == SBMT_OK) *P.stamp_at = P.stamp;
+}
 __global__ void __launch_bounds__(256) k_pre_vscan_apply(OneSrc src, PreArgs P) {
+  if (!pre_planned(P)) return;
   const Geo g = src.d.g;
   const int64_t nlat = (int64_t)g.NK * g.NI;
   const int64_t NV = P.gsizes[0] < P.usedcap ? P.gsizes[0] : P.usedcap;
@@ -2765,7 +2788,14 @@ __global__ void __launch_bounds__(256) k_pre_vscan_apply(OneSrc src, PreArgs P) 
   }
 }
 
-__global__ void k_pre_mesh_sizes(PreArgs P, Shared sh, int64_t* out) {
+// The call's counts and status.  fill: a call that did not plan has counts only
+// where the workspace holds its plan.
+__global__ void k_pre_mesh_sizes(PreArgs P, Shared sh, int64_t* out, bool fill) {
+  if (fill && !pre_planned(P)) {
+    for (int q = 0; q < 8; ++q) out[q] = 0;
+    out[5] = SBMT_E_INVALID_ARG;
+    return;
+  }
   const longlong4 tot = sh.seg_off[sh.nseg];
   const int64_t NV = *P.nused;
   out[0] = NV + tot.x;        // vertices
@@ -2775,14 +2805,8 @@ __global__ void k_pre_mesh_sizes(PreArgs P, Shared sh, int64_t* out) {
   out[4] = P.gsizes[4];       // inserted
   out[6] = NV;                // grid vertices in the mesh
   out[7] = tot.z;             // cut grid triangles
-  int64_t st = P.gsizes[5];
-  if (st == SBMT_OK || st == SBMT_E_CAPACITY) {
-    if (P.counts[2]) st = SBMT_E_PROTOCOL;
-    else if (out[0] > P.ovcap || out[1] > P.otcap) st = SBMT_E_CAPACITY;
-    else st = SBMT_OK;
-  }
-  if (out[0] > 0x7fffffffLL) st = SBMT_E_INDEX_OVERFLOW;
-  out[5] = st;
+  const int64_t st = pre_mesh_status(P, sh);
+  out[5] = st == SBMT_OK && (out[0] > P.ovcap || out[1] > P.otcap) ? SBMT_E_CAPACITY : st;
 }
 
 // Workspace of the preprocessing: the meshing layout of the image, then the
