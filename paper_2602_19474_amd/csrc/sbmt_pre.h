@@ -142,7 +142,9 @@ __device__ __forceinline__ int floor_index(const Geo& g, double v) {
 }
 
 // thresholds widened by a relative and absolute margin far above the rounding
-// of the box bounds, so that a box never misses a candidate
+// of the box bounds, so that a box never misses a candidate; the distances to a
+// line that decide early are held to it, too (the distance that decides carries
+// the rounding of whole coordinates, 1e-12 px at 8192 px, whatever the threshold)
 __device__ __forceinline__ double widen(double r) { return r * (1.0 + 1e-12) + 1e-9; }
 // Segment j of marching-squares case cs of dual cell (R, C): end points in pixels.
 __device__ __forceinline__ void cell_segment(const Geo& g, int R, int C, uint32_t ms, int j, double& px, double& py,
@@ -388,7 +390,7 @@ __device__ int pre_repel_seg(const PreArgs& P, const Geo& g, double px, double p
   const double x0 = __builtin_fmin(px, qx) - cw, x1 = __builtin_fmax(px, qx) + cw;
   const double y0 = __builtin_fmin(py, qy) - cw, y1 = __builtin_fmax(py, qy) + cw;
   int n = 0;
-  const double ex = qx - px, ey = qy - py, reach = P.c * P.c * (ex * ex + ey * ey) * (1.0 + 1e-9);
+  const double ex = qx - px, ey = qy - py, reach = cw * cw * (ex * ex + ey * ey);
   for (int k = max(0, pre_row_floor(g, y0)); k <= min(g.NK - 1, pre_row_floor(g, y1)); ++k) {
     const double yv = lat_y(g, k);
     if (yv < y0 || yv > y1) continue;
@@ -397,7 +399,7 @@ __device__ int pre_repel_seg(const PreArgs& P, const Geo& g, double px, double p
       const double xv = lat_x(g, pre_lat_X(g, k, i));
       if (xv < x0 || xv > x1) continue;
       const double off = ex * (yv - py) - ey * (xv - px);
-      if (off * off > reach) continue;  // farther from the line than c
+      if (off * off > reach) continue;  // farther from the line than c, by more than rounding
       const int64_t v = (int64_t)k * g.NI + i;
       if (P.flags[v] & kPreSnapped) continue;
       double t;
@@ -449,7 +451,7 @@ __global__ void __launch_bounds__(256) k_pre_repel(OneSrc src, PreArgs P) {
 // error (b < a/2 excludes both).
 template <bool kAll>
 __device__ void pre_split_one(const PreArgs& P, const Geo& g, int64_t id, double mx, double my) {
-  const double r = widen(P.a + P.b), rr = r / pre_hx(g);
+  const double r = widen(P.a + P.b), rr = r / pre_hx(g), bw = widen(P.b);
   int nh = 0;
   int64_t hv = -1;
   int he = 0;
@@ -473,7 +475,7 @@ __device__ void pre_split_one(const PreArgs& P, const Geo& g, int64_t id, double
         const double2 U = pre_place<kAll>(P, g, v, k, i, kAll ? 0u : P.flags[v]),
                       Wv = pre_place<kAll>(P, g, vw, kw, iw, kAll ? 0u : P.flags[vw]);
         const double dx = Wv.x - U.x, dy = Wv.y - U.y, off = dx * (my - U.y) - dy * (mx - U.x);
-        if (off * off > P.b * P.b * (dx * dx + dy * dy) * (1.0 + 1e-9)) continue;  // farther from the line than b
+        if (off * off > bw * bw * (dx * dx + dy * dy)) continue;  // farther from the line than b, by more than rounding
         // both orientations, as the side's two triangles see it
         if (seg_dist_d(mx, my, U.x, U.y, Wv.x, Wv.y, nullptr) < P.b ||
             seg_dist_d(mx, my, Wv.x, Wv.y, U.x, U.y, nullptr) < P.b) {
