@@ -296,26 +296,30 @@ __device__ __forceinline__ void count_row(const int32_t* __restrict__ tris, int6
   boundary = mate != (1u << (2 * deg)) - 1u;
 }
 
-// The heavy vertices, a wave each.  Up to 32 triangles a row's candidates lie
-// in the wave's lanes (lane p: candidate p of the sorted triangles); a vertex
-// of more goes through its list in memory.  This one collects and sorts the
-// lists, counts the rows and flags the boundary.  The list's place takes the
-// slots' (they are copied).
-constexpr int kWaveRow = 32;
-__device__ __forceinline__ int32_t lane_neighbour(const int32_t* __restrict__ tris, const int32_t* __restrict__ list,
-                                                  int32_t i, int32_t d, int lane) {
-  int32_t n = -1, p = -1;
-  if (lane < 2 * d) tri_neighbours(tris, list[lane >> 1], i, n, p);
-  return (lane & 1) ? p : n;
+// The heavy vertices, a wave each: 64 of a row's candidates (candidate p: the next
+// or the previous neighbour in triangle p / 2 of the sorted list) lie in the wave's
+// lanes at a time, and the others pass by 64 at a time, lane by lane.  This one
+// collects and sorts the lists, counts the rows and flags the boundary.  The list's
+// place takes the slots' (they are copied).
+// The work is quadratic in a row's triangles, so what bounds it is how many lanes
+// share it: assembling 100000 vertices of 40 triangles of random vertices took 14.7 ms
+// with a lane per vertex, 177 with everything beyond 32 triangles left to lane 0, now
+// 4.1; 20000 vertices of 100 triangles 45, 858, now 12; 50000 closed fans of 40
+// triangles 21.9, 31.8, now 1.8.
+__device__ __forceinline__ int32_t candidate(const int32_t* __restrict__ tris, const int32_t* list, int32_t i, int32_t d,
+                                             int32_t p) {
+  int32_t n = -1, q = -1;
+  if (p < 2 * (int64_t)d) tri_neighbours(tris, list[p >> 1], i, n, q);
+  return (p & 1) ? q : n;
 }
 __global__ void __launch_bounds__(kThreads) k_heavy_count(const int32_t* __restrict__ tris,
                                                           const int32_t* __restrict__ deg,
                                                           int32_t* __restrict__ slots,
                                                           const uint32_t* __restrict__ head,
                                                           const uint32_t* __restrict__ next,
-                                                          const int32_t* __restrict__ heavy, int32_t* __restrict__ inc,
-                                                          int32_t* __restrict__ row_len, uint8_t* __restrict__ bnd,
-                                                          Info* __restrict__ info) {
+                                                          const int32_t* __restrict__ heavy, int32_t* inc,
+                                                          int32_t* scratch, int32_t* __restrict__ row_len,
+                                                          uint8_t* __restrict__ bnd, Info* __restrict__ info) {
   const int64_t n = (int64_t)info->n_heavy, step = (int64_t)gridDim.x * (kThreads / 64);
   const int lane = threadIdx.x & 63;
   for (int64_t h = (int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6); h < n; h += step) {
@@ -324,60 +328,54 @@ __global__ void __launch_bounds__(kThreads) k_heavy_count(const int32_t* __restr
     if (lane == 0) at = atomicAdd(&info->heavy_used, (unsigned long long)d);
     at = __shfl(at, 0);
     int32_t* const list = inc + at;
-    // the chained triangles are written before the slots: lane 0 walks the chain
+    // the chained triangles after the slots' (a link's corners and the heads before
+    // it are asked for together: one wait a link)
     int32_t m = kSlots;
     for (uint32_t c = head[i]; c && m < d; ++m) {
       const int64_t t = (int64_t)c - 1;
+      const Tri x = *reinterpret_cast<const Tri*>(tris + 3 * t);
+      const uint32_t c0 = next[3 * t], c1 = next[3 * t + 1], c2 = next[3 * t + 2];
       if (lane == 0) list[m] = (int32_t)t;
-      c = next[3 * t + (tris[3 * t] == i ? 0 : (tris[3 * t + 1] == i ? 1 : 2))];
+      c = x.a == i ? c0 : (x.b == i ? c1 : c2);
     }
     if (lane < kSlots) list[lane] = slots[(int64_t)kSlots * i + lane];
     __threadfence_block();
+    // sorted: triangles are distinct, a place is the number of smaller ones (up to
+    // 64 are all read before the first is put in place, more go through `scratch`,
+    // the same range of it as of `inc`)
+    int32_t* const to = d <= 64 ? list : scratch + at;
+    for (int32_t p0 = 0; p0 < d; p0 += 64) {
+      const bool is = lane < d - p0;
+      const int32_t t = is ? list[p0 + lane] : 0x7fffffff;
+      int32_t place = 0;
+      for (int32_t q0 = 0; q0 < d; q0 += 64) {
+        const int32_t x = q0 == p0 ? t : (lane < d - q0 ? list[q0 + lane] : 0x7fffffff);
+        for (int q = 0; q < min(64, d - q0); ++q) place += __builtin_amdgcn_readlane(x, q) < t;
+      }
+      if (is) to[place] = t;
+    }
+    __threadfence_block();
+    if (to != list) {
+      for (int32_t p = lane; p < d; p += 64) list[p] = to[p];
+      __threadfence_block();
+    }
     int32_t uniq = 0;
     bool boundary = false;
-    if (d <= kWaveRow) {
-      const int32_t t = lane < d ? list[lane] : 0x7fffffff;
-      int place = 0;  // triangles are distinct: a place is the number of smaller ones
-      for (int e = 0; e < d; ++e) place += __builtin_amdgcn_readlane(t, e) < t;
-      if (lane < d) list[place] = t;
-      __threadfence_block();
-      const int32_t j = lane_neighbour(tris, list, i, d, lane);
+    for (int32_t p0 = 0; p0 < 2 * d; p0 += 64) {
+      const bool is = lane < 2 * d - p0;
+      const int32_t j = candidate(tris, list, i, d, p0 + lane);
       int mult = 0;
-      bool first = lane < 2 * d;
-      for (int q = 0; q < 2 * d; ++q) {
-        const bool eq = __builtin_amdgcn_readlane(j, q) == j;
-        mult += eq;
-        first = first && !(eq && q < lane);
-      }
-      uniq = (int)__popcll(__ballot(first));
-      boundary = __ballot(lane < 2 * d && mult == 1) != 0ull;
-    } else if (lane == 0) {
-      for (int32_t p = 1; p < d; ++p) {  // insertion sort
-        const int32_t x = list[p];
-        int32_t q = p - 1;
-        while (q >= 0 && list[q] > x) {
-          list[q + 1] = list[q];
-          --q;
+      bool first = is;
+      for (int32_t q0 = 0; q0 < 2 * d; q0 += 64) {
+        const int32_t x = q0 == p0 ? j : candidate(tris, list, i, d, q0 + lane);
+        for (int q = 0; q < min(64, 2 * d - q0); ++q) {
+          const bool eq = __builtin_amdgcn_readlane(x, q) == j;
+          mult += eq;
+          first = first && !(eq && q0 + q < p0 + lane);
         }
-        list[q + 1] = x;
       }
-      for (int32_t p = 0; p < 2 * d; ++p) {
-        int32_t jp[2];
-        tri_neighbours(tris, list[p / 2], i, jp[0], jp[1]);
-        const int32_t j = (p & 1) ? jp[1] : jp[0];
-        int mult = 0;
-        bool first = true;
-        for (int32_t q = 0; q < 2 * d; ++q) {
-          int32_t jq[2];
-          tri_neighbours(tris, list[q / 2], i, jq[0], jq[1]);
-          if (((q & 1) ? jq[1] : jq[0]) == j) {
-            ++mult;
-            if (q < p) first = false;
-          }
-        }
-        uniq += first;
-        boundary |= mult == 1;
-      }
+      uniq += (int32_t)__popcll(__ballot(first));
+      boundary = boundary || __ballot(is && mult == 1) != 0ull;
     }
     if (lane == 0) {
       row_len[i] = uniq;
@@ -689,6 +687,29 @@ __global__ void __launch_bounds__(64, 4) k_rows_fill(
   }
 }
 
+// Candidate p of heavy vertex i: its weight, its neighbour j and its triangle's share
+// of the mass.
+__device__ __forceinline__ double candidate_weight(const double2* __restrict__ v, const int32_t* __restrict__ tris,
+                                                   const int32_t* __restrict__ list, int32_t i, int32_t d, int32_t p,
+                                                   int32_t& j, double& share) {
+  j = -1;
+  share = 0.0;
+  if (p >= 2 * (int64_t)d) return 0.0;
+  const Tri x = *reinterpret_cast<const Tri*>(tris + 3 * (int64_t)list[p >> 1]);
+  const int32_t id[3] = {x.a, x.b, x.c};
+  double c[3];
+  share = (0.5 * tri_weights(v, id, c)) / 3.0;
+  const int k = x.a == i ? 0 : (x.b == i ? 1 : 2), z = (p & 1) ? (k + 1) % 3 : (k + 2) % 3;  // opposite the edge
+  j = (p & 1) ? (k == 0 ? x.c : (k == 1 ? x.a : x.b)) : (k == 0 ? x.b : (k == 1 ? x.c : x.a));
+  return z == 0 ? c[0] : (z == 1 ? c[1] : c[2]);
+}
+// x of lane q (uniform).
+__device__ __forceinline__ double lane_value(double x, int q) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, q);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), q);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
 // The heavy vertices' rows, from their sorted lists, a wave each.
 __global__ void __launch_bounds__(kThreads) k_heavy_fill(const double2* __restrict__ v, const int32_t* __restrict__ tris,
                                                          const int32_t* __restrict__ deg,
@@ -715,65 +736,35 @@ __global__ void __launch_bounds__(kThreads) k_heavy_fill(const double2* __restri
     o.r0 = row_off[i];
     o.s0 = slice_off[i / kSlice] + i % kSlice;
     double m = 0.0, diag = 0.0, offs = 0.0;
-    if (d <= kWaveRow) {
-      // lane p: neighbour and weight of candidate p, and its triangle's share of the mass
-      const int32_t j = lane_neighbour(tris, list, i, d, lane);
-      double w = 0.0, share = 0.0;
-      if (lane < 2 * d) {
-        const int64_t t = list[lane >> 1];
-        const int32_t id[3] = {tris[3 * t], tris[3 * t + 1], tris[3 * t + 2]};
-        double c[3];
-        share = (0.5 * tri_weights(v, id, c)) / 3.0;
-        const int k = id[0] == i ? 0 : (id[1] == i ? 1 : 2), z = (lane & 1) ? (k + 1) % 3 : (k + 2) % 3;
-        w = z == 0 ? c[0] : (z == 1 ? c[1] : c[2]);
-      }
+    int e0 = 0;  // entries so far
+    for (int32_t p0 = 0; p0 < 2 * d; p0 += 64) {
+      // lane l: neighbour and weight of candidate p0 + l, and its triangle's share of the mass
+      int32_t j;
+      double share;
+      double w = candidate_weight(v, tris, list, i, d, p0 + lane, j, share);
       const double own = w;
-      bool first = lane < 2 * d;
-      for (int q = 0; q < 2 * d; ++q) {
-        const double wq = __shfl(own, q);
-        if (__builtin_amdgcn_readlane(j, q) == j) {
-          w = q > lane ? w + wq : w;
-          first = first && q >= lane;
-        }
-      }
-      for (int e = 0; e < d; ++e) m += __shfl(share, 2 * e);
-      const unsigned long long rows = __ballot(first);
-      const int e = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(rows >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)rows, 0u));
-      if (first) put_entry(o, e, j, w);
-      for (unsigned long long r = rows; r; r &= r - 1) {
-        const double x = __shfl(w, __builtin_ctzll(r));
-        diag += x;
-        offs += fabs(x);
-      }
-    } else if (lane == 0) {
-      const int64_t r0 = o.r0;
-      int32_t len = 0;
-      for (int32_t p = 0; p < d; ++p) {
-        const int64_t t = list[p];
-        const int32_t id[3] = {tris[3 * t], tris[3 * t + 1], tris[3 * t + 2]};
-        double c[3];
-        m += (0.5 * tri_weights(v, id, c)) / 3.0;
-        const int k = id[0] == i ? 0 : (id[1] == i ? 1 : 2);
-        const int32_t js[2] = {id[(k + 1) % 3], id[(k + 2) % 3]};
-        const double cs[2] = {c[(k + 2) % 3], c[(k + 1) % 3]};
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          int32_t e = 0;
-          while (e < len && col[r0 + e] != js[q]) ++e;
-          if (e == len) {
-            col[r0 + e] = js[q];
-            val[r0 + e] = cs[q];
-            ++len;
-          } else {
-            val[r0 + e] += cs[q];
+      bool first = lane < 2 * d - p0;
+      for (int32_t q0 = 0; q0 < 2 * d; q0 += 64) {
+        int32_t x = j;
+        double wx = own, sx;
+        if (q0 != p0) wx = candidate_weight(v, tris, list, i, d, q0 + lane, x, sx);
+        for (int q = 0; q < min(64, 2 * d - q0); ++q) {
+          const double wq = lane_value(wx, q);
+          if (__builtin_amdgcn_readlane(x, q) == j) {
+            w = q0 + q > p0 + lane ? w + wq : w;
+            first = first && q0 + q >= p0 + lane;
           }
         }
       }
-      for (int32_t e = 0; e < len; ++e) {
-        const double w = val[r0 + e];
-        diag += w;
-        offs += fabs(w);
-        put_entry(o, e, col[r0 + e], w);
+      for (int e = 0; e < min(64, 2 * d - p0); e += 2) m += lane_value(share, e);
+      const unsigned long long rows = __ballot(first);
+      const int e = e0 + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(rows >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)rows, 0u));
+      if (first) put_entry(o, e, j, w);
+      e0 += (int)__popcll(rows);
+      for (unsigned long long r = rows; r; r &= r - 1) {
+        const double x = lane_value(w, __builtin_ctzll(r));
+        diag += x;
+        offs += fabs(x);
       }
     }
     if (lane == 0) {
@@ -1036,7 +1027,8 @@ sbmt_status sbmt_laplacian_assemble(sbmt_handle h, const double* verts, int64_t 
     hipLaunchKernelGGL(k_incident, dim3(xcd_blocks((n_triangles + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, tris, n_triangles, n_vertices,
                        deg, slots, head, next, heavy, dinfo);
     hipLaunchKernelGGL(k_heavy_count, hgrid, dim3(kThreads), 0, s, tris, (const int32_t*)deg, slots,
-                       (const uint32_t*)head, (const uint32_t*)next, (const int32_t*)heavy, inc, row_len, bnd, dinfo);
+                       (const uint32_t*)head, (const uint32_t*)next, (const int32_t*)heavy, inc, col /* not yet written */, row_len, bnd,
+                       dinfo);
   }
   if (n_vertices > 0)
     hipLaunchKernelGGL(k_rows_count, dim3(xcd_blocks(L.nblk)), dim3(kThreads), 0, s, tris, n_vertices,
