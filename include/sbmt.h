@@ -48,8 +48,11 @@
  *    warm.
  *  - The workspace holds the coarse raster, a two-byte code per lattice
  *    vertex, a four-byte word per lattice vertex for the persistent batch
- *    kernel, and 16-byte records of the owners classified exactly (by
- *    default room for half of the owners).
+ *    kernel, and 16-byte records of the owners classified exactly: by
+ *    default room for half of the owners, and for every owner up to 2^20
+ *    (16 MB), so that calls of few tiles need no pass for owners without a
+ *    record.  A workspace for an image is large enough for one that is no
+ *    wider and no higher, too.
  *
  * Errors
  *  - Every call returns an sbmt_status.  Arguments are validated before any

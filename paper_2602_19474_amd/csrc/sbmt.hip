@@ -78,7 +78,8 @@ constexpr int kSlowBlocks = 2048;              // dense slow pass: blocks of its
 constexpr int kDenseLists = 64;                // dense slow lists (tile mod 64), each with its own counter
 constexpr int kSizeWords = SBMT_SIZE_WORDS;    // per-image sizes record
 constexpr int kSmallTiles = 4096;           // calls of at most so many 8-row tiles take k_count_small
-constexpr int kFullRecordTiles = 512;          // calls of at most so many have a record for every owner (16 MB)
+constexpr int kFullRecordTiles = 512;          // calls of at most so many have a record for every owner
+constexpr int64_t kFullRecords = kFullRecordTiles * 8LL * kCB;  // and at most so many records (16 MB)
 constexpr int kScanOwnPrefix = 512;            // scan blocks whose prefix each block adds up itself
 constexpr int kSegSlots = 64;                  // partial segment counts per image (spread atomics)
 constexpr int kRowPad = 20;                    // row-table entries past the last grid row (tile and halo rows)
@@ -2077,11 +2078,25 @@ static sbmt_status make_call_layout(const sbmt_image* imgs, int n, int64_t recor
   // about a third at grid_h = 4 on fine structures); an explicit cap is
   // shared evenly by the tiles
   for (int r = 0; r < 3; ++r) L.ntiles_max = std::max(L.ntiles_max, tab_row(L, 1 + r)[n]);
+  int64_t rec_floor = 0, dense_floor = 0;  // entries, whatever the rule needs
   if (record_cap == 0) {
-    // a call of few tiles gets a record for every owner, and needs no pass for
+    // a call of few tiles gets a record for every owner (of 16-row tiles, which
+    // cover more rows than there are, up to kFullRecords), and needs no pass for
     // owners without one
-    const int part = tab_row(L, 2)[n] <= kFullRecordTiles ? 1 : 2;
-    for (int r = 0; r < 3; ++r) L.rcap = std::max(L.rcap, tab_row(L, 1 + r)[n] * (int64_t)(kRBs[r] * kCB / part));
+    int64_t full = 0, half = 0;
+    for (int r = 0; r < 3; ++r) {
+      const int64_t nt = tab_row(L, 1 + r)[n], per = kRBs[r] * kCB;
+      full = std::max(full, nt * per);
+      half = std::max(half, nt * (per / 2));
+      // (64 lists of up to kFullRecords, and of a tile more each where 16-row tiles
+      // share those)
+      dense_floor = std::max(dense_floor, std::min(std::min<int64_t>(nt, kDenseLists) * ((nt + kDenseLists - 1) / kDenseLists) * per,
+                                                   kFullRecords + (r == 2 ? kFullRecords / 4 : 0)));
+    }
+    // the room of a call of more tiles is not less: a workspace for an image is one
+    // for every smaller image, too
+    rec_floor = std::min(full, kFullRecords);
+    L.rcap = tab_row(L, 2)[n] <= kFullRecordTiles ? rec_floor : half;
   } else if (record_cap < 0) {
     // room for every owner of a persistent-kernel band tile (its rows and halo row)
     for (int r = 0; r < 2; ++r) L.rcap = std::max(L.rcap, tab_row(L, 1 + r)[n] * (int64_t)((kRBs[r] + 1) * kCB));
@@ -2092,11 +2107,12 @@ static sbmt_status make_call_layout(const sbmt_image* imgs, int n, int64_t recor
   for (int r = 0; r < 3; ++r) {
     const int64_t nt = tab_row(L, 1 + r)[n];
     L.tcap[r] = L.rcap / std::max<int64_t>(nt, 1);
-    // tile t feeds list t mod kDenseLists: at most ceil(nt / kDenseLists) tiles a list
-    L.dcap[r] = (nt + kDenseLists - 1) / kDenseLists * L.tcap[r];
+    // tile t feeds list t mod kDenseLists: at most ceil(nt / kDenseLists) tiles a
+    // list, of which none queues more than its owners
+    L.dcap[r] = (nt + kDenseLists - 1) / kDenseLists * std::min<int64_t>(L.tcap[r], kRBs[r] * kCB);
   }
   // lists in use: min(tiles, kDenseLists); at most rcap + (kDenseLists - 1) tcap entries
-  int64_t dmax = 0;
+  int64_t dmax = dense_floor;
   for (int r = 0; r < 3; ++r)
     dmax = std::max(dmax, std::min<int64_t>(tab_row(L, 1 + r)[n], kDenseLists) * L.dcap[r]);
   L.nblk = (int)((L.nseg + kScanChunk - 1) / kScanChunk);
@@ -2124,7 +2140,7 @@ static sbmt_status make_call_layout(const sbmt_image* imgs, int n, int64_t recor
   L.off_blk = off;
   off = align256(off + (size_t)L.nblk * sizeof(longlong4));
   L.off_rec = off;
-  off = align256(off + (size_t)L.rcap * sizeof(SlowRec));
+  off = align256(off + (size_t)std::max(L.rcap, rec_floor) * sizeof(SlowRec));
   L.off_dense = off;
   off = align256(off + (size_t)dmax * sizeof(uint32_t));
   L.off_tilen = off;

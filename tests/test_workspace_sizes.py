@@ -1,0 +1,53 @@
+"""Workspace sizes of the queries (host only).
+
+A program that meshes images of several sizes keeps one workspace, as large as the
+largest needs: it has to do for the smaller ones, whichever number of records the
+library gives them (calls of up to 512 tiles have one for every owner).
+"""
+from __future__ import annotations
+
+import pytest
+
+import paper_2602_19474_amd as sbmt
+
+
+def _bytes(w, h, grid_h):
+    return sbmt.query(w, h, grid_h).workspace_bytes
+
+
+def _tiles(w, h, grid_h):
+    q = sbmt.query(w, h, grid_h)
+    return (q.grid_rows + 7) // 8 * ((q.grid_cols + 255) // 256)
+
+
+@pytest.mark.parametrize("grid_h", [0.5, 1, 2, 4])
+def test_a_workspace_does_for_smaller_images(grid_h):
+    s = int(grid_h * 32)
+    # squares, then rows and columns of one image size, across the step at 512 tiles
+    for name, size in (("square", lambda j: (s * j, s * j)), ("wide", lambda j: (8 * s * j, s // 2)),
+                       ("tall", lambda j: (s, 8 * s * j)), ("short", lambda j: (64 * s * j, 2))):
+        last, j = 0, 1
+        while _tiles(*size(j), grid_h) <= 800 and max(size(j)) < 1 << 20:
+            b = _bytes(*size(j), grid_h)
+            assert b >= last, (name, size(j))
+            last, j = b, j + 1
+        assert j > 10
+    # one column, one row more at the step itself
+    h = 940 * grid_h
+    w = next(w for w in range(int(700 * grid_h), int(2000 * grid_h)) if _tiles(w, int(h), grid_h) > 512)
+    for dw in range(4):
+        for dh in range(-4, 5):
+            assert _bytes(w + dw, int(h) + dh, grid_h) >= _bytes(w + dw - 1, int(h) + dh, grid_h)
+            assert _bytes(w + dw, int(h) + dh, grid_h) >= _bytes(w + dw, int(h) + dh - 1, grid_h)
+
+
+def test_record_room_of_calls_of_few_tiles():
+    """A record of 16 bytes for every owner, 16 MiB of them at most: 512 tiles that
+    hold a few rows each take no more."""
+    for w, h in ((64, 64), (850, 850), (120000, 4), (130000, 2)):
+        assert _tiles(w, h, 1) <= 512
+        owners = _tiles(w, h, 1) * 2048
+        q = sbmt.query(w, h, 1)
+        # records, dense lists (4 bytes an entry), 25 bytes per owner of the lattice, the raster, a little
+        assert _bytes(w, h, 1) <= 2 * 20 * owners + 26 * q.grid_rows * q.grid_cols + (1 << 16)
+        assert _bytes(w, h, 1) <= 21 * (1 << 20) + 26 * q.grid_rows * q.grid_cols
