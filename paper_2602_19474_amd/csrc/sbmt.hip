@@ -112,14 +112,21 @@ struct Shared {
   int64_t* sizes;                   // [n][kSizeWords] n_vertices, n_triangles, n_cut, status, n_segments
   unsigned long long* segacc;       // [n][kSegSlots] partial boundary-segment counts
   SlowRec* rec;                     // slow-owner records, tcap per count tile
-  uint32_t* dense;                  // [kDenseLists][dcap] indices into rec of the queued slow owners
+  uint32_t* dense;                  // [tiles][tcap] indices into rec of the queued slow owners, list by list (dense_list)
   unsigned long long* dctr;         // [kDenseLists] entries of each list
   int* tile_n;                      // [count tiles] slow owners queued by each tile
   unsigned long long* band;         // [nbands] fused path look-back words
-  int64_t tcap, nseg, nbands, dcap;
+  int64_t tcap, nseg, nbands, ntile;
   int nblk, n;
   bool tall;                        // coarsening blocks of more rows (coarsen_rows)
 };
+
+// First entry of dense list l: the lists lie end to end, each with the room of its
+// tiles' records (l, l + kDenseLists, ...), so that all of them take as many entries
+// as there are records.
+__device__ __forceinline__ int64_t dense_list(const Shared& sh, int l) {
+  return (l * (sh.ntile / kDenseLists) + min((int64_t)l, sh.ntile % kDenseLists)) * sh.tcap;
+}
 
 // Block -> image maps.  OneSrc carries the single image by value; ManySrc
 // reads the image table of the workspace and a per-kernel prefix table of
@@ -624,7 +631,7 @@ __device__ __forceinline__ void count_tile(const Img& d, const Geo& g, int ii, i
     sh.tile_n[tile] = L.n2;
     // list tile mod kDenseLists, so that no counter takes every tile's atomic
     if (kMode == kCountDense && L.n2)
-      L.dbase = (unsigned)((tile & (kDenseLists - 1)) * sh.dcap +
+      L.dbase = (unsigned)(dense_list(sh, (int)(tile & (kDenseLists - 1))) +
                            (int64_t)atomicAdd(&sh.dctr[tile & (kDenseLists - 1)],
                                               (unsigned long long)min((int64_t)L.n2, sh.tcap)));
   }
@@ -727,7 +734,8 @@ __global__ void __launch_bounds__(kThreads, 4) k_count_small(Src src, const int6
 // ---------------------------------------------------------------------------
 template <class Src, int RB>
 __global__ void __launch_bounds__(kThreads, 8) k_slow_dense(Src src, Shared sh) {
-  __shared__ int64_t pre[kDenseLists + 1];
+  __shared__ int64_t pre[kDenseLists + 1], at[kDenseLists];
+  if (threadIdx.x >= 64 && threadIdx.x < 64 + kDenseLists) at[threadIdx.x - 64] = dense_list(sh, (int)threadIdx.x - 64);
   if (threadIdx.x == 0) {
     int64_t t = 0;
     for (int l = 0; l < kDenseLists; ++l) {
@@ -745,7 +753,7 @@ __global__ void __launch_bounds__(kThreads, 8) k_slow_dense(Src src, Shared sh) 
       if (pre[mid] <= j) lo = mid;
       else hi = mid - 1;
     }
-    const uint32_t idx = sh.dense[lo * sh.dcap + (j - pre[lo])];
+    const uint32_t idx = sh.dense[at[lo] + (j - pre[lo])];
     const SlowRec P = sh.rec[idx];
     const int k = (int)((P.x >> 24) & 0xffffffu), c = (int)(P.x & 0xffffffu), ii = (int)(P.x >> 48);
     const Img& d = src.img(ii);
@@ -2023,7 +2031,6 @@ struct CallLayout {
   std::vector<int64_t> tab;           // [1 + 3 + 3][n + 1]: coarsen blocks, tiles per RB, bands per RB
   int64_t nseg = 0, owners = 0, rcap = 0, nbands_max = 0, halo_words = 0, ntiles_max = 0;
   int64_t tcap[3] = {0, 0, 0};  // records per count tile, per tile height
-  int64_t dcap[3] = {0, 0, 0};  // entries per dense list, per tile height
   int nblk = 0;
   bool tall = false;  // coarsening blocks of more rows
   size_t off_ctr, off_dctr, off_imgerr, off_sizes, off_segacc, off_desc, off_tab, off_cnt, off_slow, off_segoff, off_blk, off_rec,
@@ -2078,7 +2085,7 @@ static sbmt_status make_call_layout(const sbmt_image* imgs, int n, int64_t recor
   // about a third at grid_h = 4 on fine structures); an explicit cap is
   // shared evenly by the tiles
   for (int r = 0; r < 3; ++r) L.ntiles_max = std::max(L.ntiles_max, tab_row(L, 1 + r)[n]);
-  int64_t rec_floor = 0, dense_floor = 0;  // entries, whatever the rule needs
+  int64_t rec_floor = 0;  // room for at least so many records
   if (record_cap == 0) {
     // a call of few tiles gets a record for every owner (of 16-row tiles, which
     // cover more rows than there are, up to kFullRecords), and needs no pass for
@@ -2088,10 +2095,6 @@ static sbmt_status make_call_layout(const sbmt_image* imgs, int n, int64_t recor
       const int64_t nt = tab_row(L, 1 + r)[n], per = kRBs[r] * kCB;
       full = std::max(full, nt * per);
       half = std::max(half, nt * (per / 2));
-      // (64 lists of up to kFullRecords, and of a tile more each where 16-row tiles
-      // share those)
-      dense_floor = std::max(dense_floor, std::min(std::min<int64_t>(nt, kDenseLists) * ((nt + kDenseLists - 1) / kDenseLists) * per,
-                                                   kFullRecords + (r == 2 ? kFullRecords / 4 : 0)));
     }
     // the room of a call of more tiles is not less: a workspace for an image is one
     // for every smaller image, too
@@ -2107,14 +2110,7 @@ static sbmt_status make_call_layout(const sbmt_image* imgs, int n, int64_t recor
   for (int r = 0; r < 3; ++r) {
     const int64_t nt = tab_row(L, 1 + r)[n];
     L.tcap[r] = L.rcap / std::max<int64_t>(nt, 1);
-    // tile t feeds list t mod kDenseLists: at most ceil(nt / kDenseLists) tiles a
-    // list, of which none queues more than its owners
-    L.dcap[r] = (nt + kDenseLists - 1) / kDenseLists * std::min<int64_t>(L.tcap[r], kRBs[r] * kCB);
   }
-  // lists in use: min(tiles, kDenseLists); at most rcap + (kDenseLists - 1) tcap entries
-  int64_t dmax = dense_floor;
-  for (int r = 0; r < 3; ++r)
-    dmax = std::max(dmax, std::min<int64_t>(tab_row(L, 1 + r)[n], kDenseLists) * L.dcap[r]);
   L.nblk = (int)((L.nseg + kScanChunk - 1) / kScanChunk);
   size_t off = 0;
   L.off_ctr = off;
@@ -2140,9 +2136,10 @@ static sbmt_status make_call_layout(const sbmt_image* imgs, int n, int64_t recor
   L.off_blk = off;
   off = align256(off + (size_t)L.nblk * sizeof(longlong4));
   L.off_rec = off;
-  off = align256(off + (size_t)std::max(L.rcap, rec_floor) * sizeof(SlowRec));
+  const int64_t recs = std::max(L.rcap, rec_floor);
+  off = align256(off + (size_t)recs * sizeof(SlowRec));
   L.off_dense = off;
-  off = align256(off + (size_t)dmax * sizeof(uint32_t));
+  off = align256(off + (size_t)recs * sizeof(uint32_t));  // the dense lists: tiles x tcap entries
   L.off_tilen = off;
   off = align256(off + (size_t)L.ntiles_max * sizeof(int));
   L.off_band = off;
@@ -2179,7 +2176,7 @@ static Shared shared_of(const CallLayout& L, void* ws, int rbi) {
   s.rec = (SlowRec*)(b + L.off_rec);
   s.dense = (uint32_t*)(b + L.off_dense);
   s.dctr = (unsigned long long*)(b + L.off_dctr);
-  s.dcap = L.dcap[rbi];
+  s.ntile = L.tab[(size_t)(1 + rbi) * (L.n + 1) + L.n];
   s.band = (unsigned long long*)(b + L.off_band);
   s.tile_n = (int*)(b + L.off_tilen);
   s.tcap = L.tcap[rbi];

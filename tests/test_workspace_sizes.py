@@ -23,11 +23,11 @@ def _tiles(w, h, grid_h):
 @pytest.mark.parametrize("grid_h", [0.5, 1, 2, 4])
 def test_a_workspace_does_for_smaller_images(grid_h):
     s = int(grid_h * 32)
-    # squares, then rows and columns of one image size, across the step at 512 tiles
+    # squares, wide and tall images, across the step at 512 tiles and far beyond
     for name, size in (("square", lambda j: (s * j, s * j)), ("wide", lambda j: (8 * s * j, s // 2)),
                        ("tall", lambda j: (s, 8 * s * j)), ("short", lambda j: (64 * s * j, 2))):
         last, j = 0, 1
-        while _tiles(*size(j), grid_h) <= 800 and max(size(j)) < 1 << 20:
+        while _tiles(*size(j), grid_h) <= 6000 and max(size(j)) < 1 << 20:
             b = _bytes(*size(j), grid_h)
             assert b >= last, (name, size(j))
             last, j = b, j + 1
