@@ -2879,11 +2879,12 @@ static sbmt_status pre_layout(const sbmt_image* img, bool need_ptr, PreLayout* P
     off = align256(off + (size_t)P->nown * 4);
     P->off_rtbase = off;
     off = align256(off + (size_t)P->nown * 8);
-    // kept outputs of the cut grid triangles: room for one in 16 owners
+    // kept outputs of the cut grid triangles (136 bytes each): room for one in 16
+    // owners, in images of few owners for more, but not beyond their base triangles
     P->ntouched = 8LL * g.NK * g.NCB;
     P->off_touched = off;
     off = align256(off + (size_t)P->ntouched * 4);
-    P->ccap = std::max<int64_t>(65536, P->nown / 16);
+    P->ccap = std::min<int64_t>(2 * P->nown, std::max<int64_t>(65536, P->nown / 16));
     P->off_cbase = off;
     off = align256(off + (size_t)P->nown * 4);
     P->off_citem = off;

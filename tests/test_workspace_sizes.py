@@ -51,3 +51,24 @@ def test_record_room_of_calls_of_few_tiles():
         # records, dense lists (4 bytes an entry), 25 bytes per owner of the lattice, the raster, a little
         assert _bytes(w, h, 1) <= 2 * 20 * owners + 26 * q.grid_rows * q.grid_cols + (1 << 16)
         assert _bytes(w, h, 1) <= 21 * (1 << 20) + 26 * q.grid_rows * q.grid_cols
+
+
+def test_mesh_of_alg3_room_of_small_images():
+    """The cut grid triangles' slots: none beyond two for every owner, so a small
+    image does not take the room of a large one."""
+    import ctypes
+
+    from paper_2602_19474_amd import _lib
+    L = _lib.lib()
+    last = 0
+    for n in (1, 16, 64, 100, 150, 200, 512, 900, 1500):
+        img = _lib.Image()
+        img.width = img.height = img.row_stride = n
+        img.grid_h = 1.0
+        b, bound = ctypes.c_size_t(), ctypes.c_int64()
+        assert L.sbmt_pre_mesh_query(ctypes.byref(img), ctypes.byref(b), ctypes.byref(bound)) == 0
+        q = sbmt.query(n, n, 1)
+        # what the call keeps per owner, 200 bytes at most; two slots of 136; a little
+        assert b.value <= q.workspace_bytes + 472 * q.grid_rows * q.grid_cols + (1 << 16), n
+        assert b.value >= last
+        last = b.value
