@@ -98,7 +98,8 @@ static_assert(kPreVScan % (64 * kPreApplyWords) == 0, "in one block of the scan"
 // each looks at this first: they must not run after a plan that failed, over
 // another image's, or over memory that was never planned.  The stamp is one of the
 // words that every call's k_coarsen clears, and the last pass of a plan without an
-// error sets it.
+// error sets it.  The passes take a count or a bound of 0 without it rather than
+// return, so that its load and the first ones of the pass wait together.
 __device__ __forceinline__ bool pre_planned(const PreArgs& P) { return *P.stamp_at == P.stamp; }
 constexpr uint8_t kPreMoved = 8;
 constexpr int kPreTally = 8;
@@ -2460,12 +2461,12 @@ __global__ void __launch_bounds__(256) k_pre_mesh_segsum(OneSrc src, PreArgs P, 
 __global__ void __launch_bounds__(256) k_pre_mesh_triangles(OneSrc src, PreArgs P, Shared sh) {
   __shared__ Tri3 stage[4][128];
   __shared__ uint8_t full[4][128];
-  if (!pre_planned(P)) return;  // uniform
   const Geo g = src.d.g;
   int64_t seg;
   int k, i0;
   if (!pre_segment(g, sh, seg, k, i0)) return;  // wave-uniform
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const unsigned long long planned = pre_planned(P) ? ~0ull : 0ull;
   const longlong4 off = sh.seg_off[seg];
   const int64_t t0 = off.y;
   int64_t vacc = off.x;
@@ -2478,7 +2479,7 @@ __global__ void __launch_bounds__(256) k_pre_mesh_triangles(OneSrc src, PreArgs 
   for (int j = 0; j < 4; ++j) rts[j] = rcs[j] & kPrePlain ? P.rtri[(int64_t)k * g.NI + i0 + lane + 64 * j] : 0u;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const unsigned long long ins = inw[j], tou = tow[j];
+    const unsigned long long ins = inw[j] & planned, tou = tow[j] & planned;
     if ((ins | tou) == 0ull) continue;
     const int i = i0 + 64 * j + lane;
     const int64_t v = (int64_t)k * g.NI + i;
@@ -2550,11 +2551,11 @@ __global__ void __launch_bounds__(256) k_pre_mesh_triangles(OneSrc src, PreArgs 
 __global__ void __launch_bounds__(256) k_pre_mesh_whole_tris(OneSrc src, PreArgs P) {
   __shared__ int32_t dl[256 + kPreOwners];
   __shared__ int nd;
-  if (!pre_planned(P)) return;  // uniform
   const Geo g = src.d.g;
   if (threadIdx.x == 0) nd = 0;
   __syncthreads();
-  const int64_t T = P.counts[3];
+  int64_t T = P.counts[3];
+  if (!pre_planned(P)) T = 0;
   for (int64_t base = (int64_t)blockIdx.x * 256;; base += (int64_t)gridDim.x * 256) {
     const bool more = base < T;  // uniform
     const int64_t it = base + threadIdx.x;
@@ -2600,10 +2601,10 @@ __global__ void __launch_bounds__(256) k_pre_mesh_whole_tris(OneSrc src, PreArgs
 // triangles of an edge write the same places), the triangles to theirs, all by
 // number: a crossing is the edge owner's first one of that edge plus its order.
 __global__ void __launch_bounds__(256) k_pre_cut_write(OneSrc src, PreArgs P) {
-  if (!pre_planned(P)) return;
   const Geo g = src.d.g;
-  const int64_t n = min(P.counts[4], P.ccap);
+  int64_t n = min(P.counts[4], P.ccap);
   const int64_t NV = *P.nused;
+  if (!pre_planned(P)) n = 0;
   double2* const Vout = reinterpret_cast<double2*>(P.overts);
   for (int64_t slot = (int64_t)blockIdx.x * 256 + threadIdx.x; slot < n; slot += (int64_t)gridDim.x * 256) {
     const PreCut& K = P.cstore[slot];
@@ -2675,7 +2676,8 @@ __global__ void __launch_bounds__(256) k_pre_cut_write(OneSrc src, PreArgs P) {
 __global__ void __launch_bounds__(256, 4) k_pre_mesh_cut_rest(OneSrc src, PreArgs P) {
   __shared__ int64_t dl[512];
   __shared__ int nd;
-  if (!pre_planned(P) || (P.counts[4] <= P.ccap && P.counts[5] == 0)) return;  // uniform
+  const int64_t slots = P.counts[4], not_kept = P.counts[5];
+  if ((slots <= P.ccap && not_kept == 0) || !pre_planned(P)) return;  // uniform
   const Img& d = src.d;
   const Geo g = d.g;
   if (threadIdx.x == 0) nd = 0;
@@ -2753,10 +2755,10 @@ __global__ void __launch_bounds__(1024) k_pre_vscan_top(PreArgs P, Shared sh, in
   if (threadIdx.x == 0 && pre_mesh_status(P, sh) == SBMT_OK) *P.stamp_at = P.stamp;
 }
 __global__ void __launch_bounds__(256) k_pre_vscan_apply(OneSrc src, PreArgs P) {
-  if (!pre_planned(P)) return;
   const Geo g = src.d.g;
   const int64_t nlat = (int64_t)g.NK * g.NI;
-  const int64_t NV = P.gsizes[0] < P.usedcap ? P.gsizes[0] : P.usedcap;
+  int64_t NV = P.gsizes[0] < P.usedcap ? P.gsizes[0] : P.usedcap;
+  if (!pre_planned(P)) NV = 0;
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   constexpr int kPer = kPreApplyWords / 4;
   const int64_t w0 = (int64_t)blockIdx.x * kPreApplyWords + wv * kPer;
