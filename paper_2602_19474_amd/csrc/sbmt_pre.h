@@ -26,10 +26,13 @@
 // A cut grid triangle's output.  Its points are numbered 0..2 the corners, 3..6
 // the ends of its one or two pieces that are crossings of its edges, 7 the
 // polyline vertex inside.
-constexpr int kPreKeep = 4;  // output triangles kept
-constexpr uint32_t kPreNotKept = 0xffu;
+// At most four output triangles: it holds two segments at most, so either up to four
+// crossings lie on its boundary (seven points there with the corners: five triangles
+// on both sides of the polyline together) or two and a vertex inside (five points and
+// one inside: five triangles), and one at least is background.
+constexpr int kPreKeep = 4;
 struct PreCut {
-  uint32_t head;      // bits 0..7 triangles (or kPreNotKept); 8 + 4 e: edge slot of edge e at its owner
+  uint32_t head;      // bits 0..7 triangles; 8 + 4 e: edge slot of edge e at its owner
   uint32_t ends;      // end k at bits 8 k: edge (bits 0, 1), order along the edge from its lower-numbered corner (2, 3),
                       // 7: it is a crossing
   uint32_t tri[2];    // two triangles each, 9 bits a triangle: three points of three bits
@@ -57,7 +60,7 @@ struct PreArgs {
   uint8_t* flags;        // per lattice vertex: bits 0-2 owned side E0-E2 split, 3 moved, 4 claimed, 5 snapped
   int32_t* split;        // [NK NI][3]: midpoint splitting side E0, E1, E2 (written where split)
   int64_t* ins_base;     // [NK NI]: first inserted vertex of the owner (written where it has one)
-  int64_t* counts;       // [8 + 512]: [2] error, [3] touched owners, [4] cut triangles, [5] some not kept (mesh); from kPreTally 256 counters of snapped, then of repelled vertices
+  int64_t* counts;       // [8 + 512]: [2] error, [3] touched owners, [4] cut triangles (mesh); from kPreTally 256 counters of snapped, then of repelled vertices
   uint32_t* touched;     // [NK][8 NCB]: bit per owner, those a segment can reach (mesh)
   int64_t ntouched;      // its words
   int32_t* snap_mid;     // [NK NI]: the polyline vertex a lattice vertex snapped to (written where snapped)
@@ -118,14 +121,6 @@ __device__ __forceinline__ int sample_at(const Img& d, const Geo& g, int R, int 
 }
 // Sample (R, C) sits at pixel (s C + (s-1)/2, s R + (s-1)/2); the offset:
 __device__ __forceinline__ double sample_off(const Geo& g) { return 0.5 * (g.s - 1); }
-// Midpoint (R, C, vert) in pixels, and whether it is a polyline vertex.
-__device__ __forceinline__ bool mid_point(const Img& d, const Geo& g, int R, int C, int vert, double& x, double& y) {
-  const double half = 0.5 * g.s;
-  x = (double)g.s * C + sample_off(g) + (vert ? 0.0 : half);
-  y = (double)g.s * R + sample_off(g) + (vert ? half : 0.0);
-  if (R < -1 || R > g.CH || C < -1 || C > g.CW) return false;
-  return sample_at(d, g, R, C) != sample_at(d, g, vert ? R + 1 : R, vert ? C : C + 1);
-}
 __device__ __forceinline__ double euclid_d(double dx, double dy) { return __builtin_sqrt(dx * dx + dy * dy); }
 // distance from (x, y) to segment P -> Q and the parameter of the closest point
 __device__ __forceinline__ double seg_dist_d(double x, double y, double px, double py, double qx, double qy, double* tp) {
@@ -134,9 +129,6 @@ __device__ __forceinline__ double seg_dist_d(double x, double y, double px, doub
   t = t < 0.0 ? 0.0 : (t > 1.0 ? 1.0 : t);
   if (tp) *tp = t;
   return euclid_d(x - (px + t * dx), y - (py + t * dy));
-}
-__device__ __forceinline__ int nearest_index(const Geo& g, double v) {
-  return (int)__builtin_floor((v - sample_off(g)) / g.s + 0.5);
 }
 __device__ __forceinline__ int floor_index(const Geo& g, double v) {
   return (int)__builtin_floor((v - sample_off(g)) / g.s);
@@ -1149,382 +1141,11 @@ __device__ __forceinline__ uint32_t pre_owner_counts(const PreArgs& P, const Geo
   return (P.touched[(int64_t)k * 8 * g.NCB + (i >> 5)] >> (i & 31u)) & 1u ? P.rcount[w] : 0u;
 }
 
-// A point of a triangle's subdivision: kind 0 grid vertex a; 1 crossing of
-// grid edge (a, b), a < b, by segment s; 2 polyline vertex a strictly inside
-// (s: the segment ending there).  ct: position along the chain.
-struct PrePt {
-  int32_t kind;
-  int32_t a, b;
-  int32_t s;
-  double x, y, ct;
-};
-__device__ __forceinline__ bool pre_same(const PrePt& p, const PrePt& q) {
-  return p.kind == q.kind && p.a == q.a && p.b == q.b && p.s == q.s;
-}
 struct PreSub {
   PreSeg S;
   double t0, t1;
   int e0, e1, c0, c1;
 };
-
-// Cuts grid triangle T by the polyline and triangulates its foreground faces,
-// calling out(p0, p1, p2, code) per output triangle (code 0: the grid
-// triangle kept whole, 1: a piece of a cut one).  Returns the number of
-// polyline vertices strictly inside T (0 or 1) and sets *inner to it.  With
-// kDefer, a cut triangle only sets *cut and returns -1 once its pieces are
-// known (callers gather those and come back to them on full waves).
-// With kCount, a foreground face of m points is reported as m - 2 triangles
-// fanned from its first point: the same count and the same points as the
-// template's triangles, without the template rule and its checks (for
-// passes that only count; the pass that writes the triangles applies them).
-template <bool kDefer = false, bool kCount = false, class Out>
-__device__ int pre_tri_mesh(const Img& d, const Geo& g, const PreArgs& P, const PreGT& T, Out out, PrePt* inner,
-                            bool* cut = nullptr, const PreBits* Bits = nullptr) {
-  const int64_t NLAT = (int64_t)g.NK * g.NI;
-  double minx = T.c[0].x, maxx = T.c[0].x, miny = T.c[0].y, maxy = T.c[0].y;
-  for (int j = 1; j < 3; ++j) {
-    minx = fmin(minx, T.c[j].x);
-    maxx = fmax(maxx, T.c[j].x);
-    miny = fmin(miny, T.c[j].y);
-    maxy = fmax(maxy, T.c[j].y);
-  }
-  PreSub subs[3];
-  int nsub = 0, edge_side = -1;
-  bool bad = false;
-  pre_segs_in_box(d, g, minx - 1e-9, maxx + 1e-9, miny - 1e-9, maxy + 1e-9, [&](const PreSeg& S) {
-    if (fmax(S.px, S.qx) < minx - 1e-9 || fmin(S.px, S.qx) > maxx + 1e-9 || fmax(S.py, S.qy) < miny - 1e-9 ||
-        fmin(S.py, S.qy) > maxy + 1e-9)
-      return;
-    // clip against the three edge half-planes (inside = left of each edge)
-    double t0 = 0.0, t1 = 1.0;
-    int e0 = -1, e1 = -1;
-    for (int e = 0; e < 3; ++e) {
-      const PreGV& A = T.c[e];
-      const PreGV& B = T.c[(e + 1) % 3];
-      // an end of the segment that is a corner of this edge lies on its line
-      const double fp = (A.bnd == S.jp || B.bnd == S.jp) ? 0.0 : (B.x - A.x) * (S.py - A.y) - (B.y - A.y) * (S.px - A.x);
-      const double fq = (A.bnd == S.jq || B.bnd == S.jq) ? 0.0 : (B.x - A.x) * (S.qy - A.y) - (B.y - A.y) * (S.qx - A.x);
-      if (fp < 0 && fq < 0) return;
-      if (fp >= 0 && fq >= 0) continue;
-      const double t = fp / (fp - fq);
-      if (fp < 0) {
-        if (t > t0) {
-          t0 = t;
-          e0 = e;
-        }
-      } else if (t < t1) {
-        t1 = t;
-        e1 = e;
-      }
-    }
-    if (!(t1 > t0)) return;
-    PreSub sb;
-    sb.S = S;
-    sb.t0 = t0;
-    sb.t1 = t1;
-    sb.e0 = e0;
-    sb.e1 = e1;
-    sb.c0 = sb.c1 = -1;
-    for (int j = 0; j < 3; ++j) {
-      if (T.c[j].bnd == S.jp && t0 == 0.0) {
-        sb.c0 = j;
-        sb.e0 = -1;
-      }
-      if (T.c[j].bnd == S.jq && t1 == 1.0) {
-        sb.c1 = j;
-        sb.e1 = -1;
-      }
-    }
-    if (sb.c0 >= 0 && sb.c1 >= 0) {
-      // the segment joins two corners: it lies on their edge, and the
-      // triangle lies on the side of its third corner
-      const PreGV& T3 = T.c[3 - sb.c0 - sb.c1];
-      edge_side = ((S.qx - S.px) * (T3.y - S.py) - (S.qy - S.py) * (T3.x - S.px)) > 0 ? 1 : 0;
-      return;
-    }
-    if (!kDefer && nsub < 3) subs[nsub] = sb;  // (a probe only needs to know that there is one)
-    ++nsub;
-  }, Bits);
-  if (nsub == 0) {
-    // uncut: side from a segment along an edge, a lattice corner off the
-    // polyline, else the centroid
-    int fg = edge_side;
-    for (int j = 0; j < 3 && fg < 0; ++j)
-      if (T.c[j].id < NLAT && T.c[j].bnd < 0) fg = pre_inside_point(d, g, T.c[j].x, T.c[j].y, Bits);
-    if (fg < 0) {
-      double cx = 0, cy = 0;
-      for (int j = 0; j < 3; ++j) {
-        cx += T.c[j].x / 3;
-        cy += T.c[j].y / 3;
-      }
-      fg = pre_inside_point(d, g, cx, cy, Bits);
-    }
-    if (fg) {
-      PrePt p[3];
-      for (int j = 0; j < 3; ++j) p[j] = PrePt{0, T.c[j].id, 0, -1, T.c[j].x, T.c[j].y, 0.0};
-      out(p[0], p[1], p[2], 0);
-    }
-    return 0;
-  }
-  if (cut) *cut = true;
-  if (kDefer) return -1;
-  if (nsub > 2) {  // more than two segments in one triangle
-    pre_error(P);
-    return 0;
-  }
-  if (nsub == 2) {  // chain order
-    if (subs[1].S.jq == subs[0].S.jp) {
-      const PreSub tmp = subs[0];
-      subs[0] = subs[1];
-      subs[1] = tmp;
-    }
-    if (subs[0].S.jq != subs[1].S.jp) {
-      pre_error(P);
-      return 0;
-    }
-  }
-  // Points of the subdivision in a pool (corners first); pieces, the boundary
-  // cycle and the faces refer to them by index.
-  PrePt pool[8];
-  int np = 3;
-  for (int j = 0; j < 3; ++j) pool[j] = PrePt{0, T.c[j].id, 0, -1, T.c[j].x, T.c[j].y, 0.0};
-  auto cross_pt = [&](int e, const PreSeg& S) {
-    const PreGV& A = T.c[e];
-    const PreGV& B = T.c[(e + 1) % 3];
-    const PreGV& L = A.id < B.id ? A : B;
-    const PreGV& H = A.id < B.id ? B : A;
-    PrePt p;
-    p.kind = 1;
-    p.a = L.id;
-    p.b = H.id;
-    p.s = S.jp;
-    pre_crossing_xy(S, L, H, p.x, p.y);
-    p.ct = 0.0;
-    return p;
-  };
-  // pieces: the chain inside the triangle, from boundary to boundary
-  uint8_t pc[2][3];
-  int pn[2] = {0, 0}, npc = 0, ncur = 0;
-  uint8_t cur[3];
-  int inner_at = -1;
-  for (int q = 0; q < nsub; ++q) {
-    const PreSub& sb = subs[q];
-    int st, en;
-    if (sb.c0 >= 0) {
-      st = sb.c0;
-    } else {
-      pool[np] = sb.e0 >= 0 ? cross_pt(sb.e0, sb.S) : PrePt{2, sb.S.jp, 0, sb.S.jp, sb.S.px, sb.S.py, 0.0};
-      pool[np].ct = (double)q + sb.t0;
-      st = np++;
-    }
-    if (ncur == 0) {
-      cur[ncur++] = (uint8_t)st;
-      // a corner point carries the chain position of the piece end it is (a
-      // corner is a piece end at most once: checked with the cycle below)
-      if (st < 3) pool[st].ct = (double)q + sb.t0;
-    } else if (!(pool[st].kind == 2 && pool[cur[ncur - 1]].kind == 2 && pool[st].a == pool[cur[ncur - 1]].a)) {
-      pre_error(P);  // pieces do not join
-      return 0;
-    } else {
-      --np;  // the joint is the previous end
-    }
-    if (sb.c1 >= 0) {
-      en = sb.c1;
-      pool[en].ct = (double)q + sb.t1;
-    } else {
-      pool[np] = sb.e1 >= 0 ? cross_pt(sb.e1, sb.S) : PrePt{2, sb.S.jq, 0, sb.S.jp, sb.S.qx, sb.S.qy, 0.0};
-      pool[np].ct = (double)q + sb.t1;
-      en = np++;
-    }
-    cur[ncur++] = (uint8_t)en;
-    if (pool[en].kind != 2) {
-      for (int z = 0; z < ncur; ++z) pc[npc][z] = cur[z];
-      pn[npc++] = ncur;
-      ncur = 0;
-    }
-  }
-  if (ncur != 0) {  // a piece ends inside the triangle
-    pre_error(P);
-    return 0;
-  }
-  int ninner = 0;
-  for (int z = 3; z < np; ++z)
-    if (pool[z].kind == 2) {
-      ++ninner;
-      inner_at = z;
-    }
-  if (ninner > 1) {
-    pre_error(P);
-    return 0;
-  }
-  if (inner_at >= 0) *inner = pool[inner_at];
-  // boundary cycle: the corners and the piece ends on each edge, in order
-  uint8_t cyc[8];
-  int8_t cpiece[8], cend[8];
-  double cpos[8];
-  int n = 0;
-  for (int j = 0; j < 3; ++j) {
-    cyc[n] = (uint8_t)j;
-    cpiece[n] = -1;
-    cend[n] = -1;
-    cpos[n] = 3.0 * j;
-    ++n;
-  }
-  for (int q = 0; q < npc; ++q)
-    for (int end = 0; end < 2; ++end) {
-      const int pi = end == 0 ? pc[q][0] : pc[q][pn[q] - 1];
-      const PrePt& p = pool[pi];
-      if (p.kind == 0) {
-        if (cpiece[pi] >= 0) {  // two pieces at one corner
-          pre_error(P);
-          return 0;
-        }
-        cpiece[pi] = (int8_t)q;
-        cend[pi] = (int8_t)end;
-        continue;
-      }
-      double pos = -1.0;
-      for (int e = 0; e < 3; ++e) {
-        const PreGV& A = T.c[e];
-        const PreGV& B = T.c[(e + 1) % 3];
-        if (p.kind == 1 && (A.id < B.id ? A.id : B.id) == p.a && (A.id < B.id ? B.id : A.id) == p.b) {
-          const double L2 = (B.x - A.x) * (B.x - A.x) + (B.y - A.y) * (B.y - A.y);
-          const double t = ((p.x - A.x) * (B.x - A.x) + (p.y - A.y) * (B.y - A.y)) / L2;
-          if (!(t > 0 && t < 1)) {
-            pre_error(P);
-            return 0;
-          }
-          pos = 3.0 * e + 1.0 + t;
-        }
-      }
-      if (pos < 0.0) {  // piece end not on the triangle
-        pre_error(P);
-        return 0;
-      }
-      cyc[n] = (uint8_t)pi;
-      cpiece[n] = (int8_t)q;
-      cend[n] = (int8_t)end;
-      cpos[n] = pos;
-      ++n;
-    }
-  for (int a = 1; a < n; ++a)  // insertion sort by position
-    for (int b = a; b > 0 && cpos[b] < cpos[b - 1]; --b) {
-      const uint8_t t0 = cyc[b];
-      cyc[b] = cyc[b - 1];
-      cyc[b - 1] = t0;
-      const int8_t t1 = cpiece[b];
-      cpiece[b] = cpiece[b - 1];
-      cpiece[b - 1] = t1;
-      const int8_t t2 = cend[b];
-      cend[b] = cend[b - 1];
-      cend[b - 1] = t2;
-      const double t3 = cpos[b];
-      cpos[b] = cpos[b - 1];
-      cpos[b - 1] = t3;
-    }
-  // faces: walk the cycle; at a piece end reached along the boundary, follow the piece
-  uint32_t used = 0;
-  for (int st = 0; st < n; ++st) {
-    if ((used >> st) & 1u) continue;
-    uint8_t face[16];
-    int m = 0, side = -1, at = st;
-    for (int guard = 0; guard < 64; ++guard) {
-      if ((used >> at) & 1u) break;
-      used |= 1u << at;
-      if (m < 16) face[m] = cyc[at];
-      ++m;
-      const int nx = (at + 1) % n;
-      if (cpiece[nx] >= 0) {
-        const int q = cpiece[nx];
-        const bool fwd = cend[nx] == 0;
-        const int s2 = fwd ? 1 : 0;
-        if (side >= 0 && side != s2) {  // a face on both sides of the chain
-          pre_error(P);
-          return 0;
-        }
-        side = s2;
-        if (fwd) {
-          for (int z = 0; z + 1 < pn[q]; ++z) {
-            if (m < 16) face[m] = pc[q][z];
-            ++m;
-          }
-        } else {
-          for (int z = pn[q] - 1; z > 0; --z) {
-            if (m < 16) face[m] = pc[q][z];
-            ++m;
-          }
-        }
-        int oth = -1;
-        for (int z = 0; z < n; ++z)
-          if (cpiece[z] == q && cend[z] != cend[nx]) oth = z;
-        if (oth < 0) {
-          pre_error(P);
-          return 0;
-        }
-        at = oth;
-        if (at == st) break;
-        continue;
-      }
-      at = nx;
-      if (at == st) break;
-    }
-    if (side != 1) continue;
-    if (m < 3 || m > 16) {  // degenerate face
-      pre_error(P);
-      return 0;
-    }
-    if (kCount) {
-      for (int t = 1; t + 1 < m; ++t) out(pool[face[0]], pool[face[t]], pool[face[t + 1]], 1);
-      continue;
-    }
-    // the template rule on this foreground face
-    int apex = -1;
-    for (int j = 0; j < m; ++j)
-      if (pool[face[j]].kind == 2) apex = j;
-    if (apex < 0 && m == 4 && npc == 2) {
-      bool corners = false;
-      for (int j = 0; j < m; ++j) corners = corners || face[j] < 3;
-      if (!corners) {
-        // the middle quadrilateral between two chords: diagonal joining their exits
-        const int x1 = pc[0][pn[0] - 1], x2 = pc[1][pn[1] - 1];
-        for (int j = 0; j < m; ++j)
-          if (face[j] == x1) apex = j;
-        if (apex < 0 || face[(apex + 2) % 4] != x2) {
-          pre_error(P);  // nested exits not opposite
-          return 0;
-        }
-      }
-    }
-    if (apex < 0) {
-      // the earliest chain point: a piece point (corners only as piece ends)
-      double best = 1e300;
-      for (int j = 0; j < m; ++j) {
-        const int pi = face[j];
-        bool in_piece = false;
-        for (int q = 0; q < npc; ++q)
-          for (int z = 0; z < pn[q]; ++z) in_piece = in_piece || pc[q][z] == pi;
-        if (!in_piece) continue;
-        if (pool[pi].ct < best) {
-          best = pool[pi].ct;
-          apex = j;
-        }
-      }
-    }
-    if (apex < 0) {
-      pre_error(P);
-      return 0;
-    }
-    for (int t = 1; t + 1 < m; ++t) {
-      const PrePt& a = pool[face[apex]];
-      const PrePt& b = pool[face[(apex + t) % m]];
-      const PrePt& c = pool[face[(apex + t + 1) % m]];
-      if (!((b.x - a.x) * (c.y - a.y) - (b.y - a.y) * (c.x - a.x) > 0.0)) pre_error(P);
-      out(a, b, c, 1);
-    }
-  }
-  return ninner;
-
-}
 
 // Owners whose slot triangles a segment can reach: every segment marks the
 // owners whose slot box on the lattice, widened by a + b (the moves and the
@@ -1601,127 +1222,10 @@ __device__ __forceinline__ bool pre_owner_tri(const PreArgs& P, const Geo& g, in
   return true;
 }
 
-// The crossings of edge slot q of owner (k, i) (cq of them, by position
-// along the edge from its lower-numbered end), from mesh index `first`.
-__device__ void pre_slot_vertices(const Img& d, const Geo& g, const PreArgs& P, int k, int i, int q, int cq,
-                                  int64_t first) {
-  double2* Vout = reinterpret_cast<double2*>(P.overts);
-  const PreSlots S = pre_owner_slots(P, g, k, i);
-  PreBits Bits;
-  pre_owner_bits(d, g, P, k, i, Bits);
-  PreGV A, B;
-  pre_edge_slot(P, g, k, i, S, q, A, B);
-  const PreGV& L = A.id < B.id ? A : B;
-  const PreGV& H = A.id < B.id ? B : A;
-  double te[3], xs[3], ys[3];
-  int m = 0;
-  pre_edge_crossings(d, g, L, H, [&](const PreSeg& Sg, double t) {
-    if (m >= 3) return;
-    te[m] = t;
-    pre_crossing_xy(Sg, L, H, xs[m], ys[m]);
-    for (int z = m++; z > 0 && te[z - 1] > te[z]; --z) {  // by position along the edge
-      const double a = te[z], bx = xs[z], by = ys[z];
-      te[z] = te[z - 1];
-      xs[z] = xs[z - 1];
-      ys[z] = ys[z - 1];
-      te[z - 1] = a;
-      xs[z - 1] = bx;
-      ys[z - 1] = by;
-    }
-  }, &Bits);
-  for (int z = 0; z < cq && z < m; ++z)
-    if (first + z < P.ovcap) Vout[first + z] = make_double2(xs[z], ys[z]);
-}
-// The polyline vertex strictly inside grid triangle z of owner (k, i), at
-// mesh index `at`.
-__device__ void pre_inner_vertex(const Img& d, const Geo& g, const PreArgs& P, int k, int i, int z, int64_t at) {
-  const PreSlots S = pre_owner_slots(P, g, k, i);
-  PreGT T;
-  if (!pre_owner_tri(P, g, k, i, S, z, T)) return;
-  PreBits Bits;
-  pre_owner_bits(d, g, P, k, i, Bits);
-  PrePt in;
-  if (pre_tri_mesh<false, true>(d, g, P, T, [](const PrePt&, const PrePt&, const PrePt&, int) {}, &in, nullptr,
-                                &Bits) &&
-      at < P.ovcap)
-    reinterpret_cast<double2*>(P.overts)[at] = make_double2(in.x, in.y);
-}
-
 // The slot of cut grid triangle z of list position t in the kept outputs.
 __device__ __forceinline__ int64_t pre_cut_slot(const PreArgs& P, int64_t t, int z, uint32_t rt) {
   return (int64_t)P.cbase[t] + __builtin_popcount((rt >> 28) & ((1u << z) - 1u));
 }
-
-// Output triangles of grid triangle z of a touched owner, from position pos.
-__device__ void pre_owner_triangle(const Img& d, const Geo& g, const PreArgs& P, int k, int i, int z, uint32_t rc,
-                                   uint32_t rt, int64_t pos, int64_t NV) {
-  const int64_t v = (int64_t)k * g.NI + i;
-  const PreSlots S = pre_owner_slots(P, g, k, i);
-  PreBits Bits;
-  pre_owner_bits(d, g, P, k, i, Bits);
-  PreGT TT;
-  if (!pre_owner_tri(P, g, k, i, S, z, TT)) return;
-  const int64_t vbase = (pre_rc_before(rc, 8) + pre_rc_inner(rc)) ? P.rbase[v] : 0;
-  const int64_t inner_id = NV + vbase + pre_rc_before(rc, 8) + __builtin_popcount((rt >> 24) & ((1u << z) - 1u));
-  // per edge of the triangle: its owner's first crossing id and the
-  // crossings' segments in order along the edge (at most three)
-  int64_t ebase[3];
-  int32_t eseg[3][3];
-  int ecnt[3];
-  for (int e = 0; e < 3; ++e) {
-    const PreGV& A = TT.c[e];
-    const PreGV& B = TT.c[(e + 1) % 3];
-    const PreGV& L = A.id < B.id ? A : B;
-    const PreGV& H = A.id < B.id ? B : A;
-    const uint32_t rw = pre_owner_counts(P, g, (uint32_t)TT.eo[e]);
-    ecnt[e] = pre_rc_cross(rw, TT.es[e]);
-    ebase[e] = 0;
-    if (!ecnt[e]) continue;
-    ebase[e] = NV + P.rbase[TT.eo[e]] + pre_rc_before(rw, TT.es[e]);
-    double te[3];
-    int m = 0;
-    pre_edge_crossings(d, g, L, H, [&](const PreSeg& Sg, double t) {
-      if (m >= 3) return;
-      te[m] = t;
-      eseg[e][m] = Sg.jp;
-      for (int z = m++; z > 0 && te[z - 1] > te[z]; --z) {
-        const double t1 = te[z];
-        te[z] = te[z - 1];
-        te[z - 1] = t1;
-        const int32_t s1 = eseg[e][z];
-        eseg[e][z] = eseg[e][z - 1];
-        eseg[e][z - 1] = s1;
-      }
-    }, &Bits);
-    if (m != ecnt[e]) pre_error(P);
-    ecnt[e] = min(m, ecnt[e]);
-  }
-  auto id_of = [&](const PrePt& p) -> int64_t {
-    if (p.kind == 0) return pre_vertex(P, p.a);
-    if (p.kind == 2) return inner_id;
-    for (int e = 0; e < 3; ++e) {
-      const int64_t lo = TT.c[e].id < TT.c[(e + 1) % 3].id ? TT.c[e].id : TT.c[(e + 1) % 3].id;
-      const int64_t hi = TT.c[e].id < TT.c[(e + 1) % 3].id ? TT.c[(e + 1) % 3].id : TT.c[e].id;
-      if (lo != p.a || hi != p.b) continue;
-      for (int r = 0; r < ecnt[e]; ++r)
-        if (eseg[e][r] == p.s) return ebase[e] + r;
-    }
-    pre_error(P);
-    return 0;
-  };
-  PrePt in;
-  (void)pre_tri_mesh(d, g, P, TT, [&](const PrePt& a, const PrePt& b, const PrePt& c, int code) {
-    if (pos < P.otcap) {
-      int32_t* o = P.otris + 3 * pos;
-      o[0] = (int32_t)id_of(a);
-      o[1] = (int32_t)id_of(b);
-      o[2] = (int32_t)id_of(c);
-      P.ocodes[pos] = (uint8_t)code;
-    }
-    ++pos;
-  }, &in, nullptr, &Bits);
-}
-
 
 // The touched owners of each row segment (their list offsets come from a
 // scan), a thread each.
@@ -1811,31 +1315,6 @@ __device__ __forceinline__ void pre_add_counts(const PreArgs& P, int64_t v, int 
   atomicOr(&P.rtri[v], ((uint32_t)nt << (6 * z)) | ((uint32_t)nin << (24 + z)));
   atomicAdd(&P.rcount[v], ((uint32_t)nin << 16) | ((uint32_t)nt << 19) | (1u << 27));
 }
-// A cut grid triangle without a slot, by the general subdivision.
-__device__ __forceinline__ void pre_mesh_cut_tri_count(const Img& d, const Geo& g, const PreArgs& P, int64_t t, int z) {
-  int kk, ii;
-  pre_tl_owner(g, P, t, kk, ii);
-  const PreSlots S = pre_owner_slots(P, g, kk, ii);
-  PreGT Tg;
-  if (!pre_owner_tri(P, g, kk, ii, S, z, Tg)) return;
-  PreBits Bits;
-  pre_owner_bits(d, g, P, kk, ii, Bits);
-  int nt = 0;
-  PrePt in;
-  bool cut = false;
-  const int nin = pre_tri_mesh(d, g, P, Tg, [&](const PrePt& a, const PrePt& b, const PrePt& c, int) {
-    ++nt;
-    if (a.kind == 0) P.used[a.a] = 1;
-    if (b.kind == 0) P.used[b.a] = 1;
-    if (c.kind == 0) P.used[c.a] = 1;
-  }, &in, &cut, &Bits);
-  if (nt > 63) {
-    pre_error(P);
-    nt = 63;
-  }
-  pre_add_counts(P, (int64_t)kk * g.NI + ii, z, nt, nin ? 1 : 0);
-}
-
 // Counts of the touched owners.  The plain ones (both base triangles there and
 // no split side: nine in ten) take k_pre_mesh_probe_plain, one lane per owner:
 // its four corners and its raster words are loaded once, together, and every
@@ -1906,7 +1385,7 @@ __device__ __forceinline__ int pre_clip(const PreSeg& S, const double2 (&c)[3], 
   }
   return 1;
 }
-// Whether an uncut triangle of lattice corners lies in the foreground: by a
+// Whether an uncut grid triangle lies in the foreground: by a
 // segment along an edge (side), a corner off the polyline, else its centroid.
 __device__ __forceinline__ int pre_uncut_side(const Img& d, const Geo& g, const double2 (&c)[3], const int32_t (&bnd)[3],
                                               int side, const PreBits& B) {
@@ -2045,20 +1524,26 @@ __global__ void __launch_bounds__(256) k_pre_mesh_probe_owner(OneSrc src, PreArg
           const int z = (int)threadIdx.x & 3;
           PreGT Tg;
           if (!pre_owner_tri(P, g, kk, ii, S, z, Tg)) continue;
-          int nt = 0;
-          PrePt in;
-          bool cut = false;
-          const int nin = pre_tri_mesh<true>(d, g, P, Tg, [&](const PrePt& a, const PrePt& b, const PrePt& c, int) {
-            ++nt;
-            if (a.kind == 0) P.used[a.a] = 1;
-            if (b.kind == 0) P.used[b.a] = 1;
-            if (c.kind == 0) P.used[c.a] = 1;
-          }, &in, &cut, &Bits);
-          if (nin < 0) {  // cut: the cut triangles' pass takes it
+          const double2 c[3] = {make_double2(Tg.c[0].x, Tg.c[0].y), make_double2(Tg.c[1].x, Tg.c[1].y),
+                                make_double2(Tg.c[2].x, Tg.c[2].y)};
+          const int32_t bnd[3] = {Tg.c[0].bnd, Tg.c[1].bnd, Tg.c[2].bnd};
+          int cut = 0, side = -1;
+          const double m = 1e-9;
+          pre_segs_in_box(d, g, fmin(c[0].x, fmin(c[1].x, c[2].x)) - m, fmax(c[0].x, fmax(c[1].x, c[2].x)) + m,
+                          fmin(c[0].y, fmin(c[1].y, c[2].y)) - m, fmax(c[0].y, fmax(c[1].y, c[2].y)) + m,
+                          [&](const PreSeg& Sg) {
+            double fp[3], fq[3];
+#pragma unroll
+            for (int e = 0; e < 3; ++e) pre_half(Sg, c[e], c[(e + 1) % 3], bnd[e], bnd[(e + 1) % 3], fp[e], fq[e]);
+            cut |= pre_clip(Sg, c, bnd, fp, fq, side);
+          }, &Bits);
+          if (cut) {  // the cut triangles' pass takes it
             atomicOr(&rt[q], 1u << (28 + z));
-          } else {  // uncut: at most one triangle, no inner vertex
-            atomicOr(&rt[q], (uint32_t)nt << (6 * z));
-            atomicAdd(&rc[q], (uint32_t)nt << 19);
+          } else if (pre_uncut_side(d, g, c, bnd, side, Bits)) {
+#pragma unroll
+            for (int j = 0; j < 3; ++j) P.used[Tg.c[j].id] = 1;
+            atomicOr(&rt[q], 1u << (6 * z));
+            atomicAdd(&rc[q], 1u << 19);
           }
         } else {
           const int e = (int)threadIdx.x & 7;
@@ -2154,240 +1639,261 @@ __global__ void __launch_bounds__(256) k_pre_cut_slots(PreArgs P, Shared sh) {
   }
 }
 
-// The cut grid triangles that have a slot, one lane each: the same subdivision
-// as pre_tri_mesh's, on point numbers of three bits in packed words (the
-// boundary cycle, the faces) and the points' places in LDS, so that it needs no
-// scratch memory: the general form keeps its points, pieces and faces in
-// local arrays, 0.9 KB a lane, and moved 3.5 GB through memory for 2.3 M
-// triangles (1.70 ms on the 8192 x 8192 image; this one 0.42 ms).  Up to
-// kPreKeep triangles are kept for k_pre_cut_write, with the crossings' edges,
-// order and places.
+// A cut grid triangle subdivided, on point numbers of three bits in packed words (the
+// boundary cycle, the faces) and the points' places in LDS: points, pieces and faces
+// in local arrays took 0.9 KB of scratch memory a lane and moved 3.5 GB through
+// memory for 2.3 M triangles (1.70 ms on the 8192 x 8192 image; this 0.42 ms).
+struct PreCutWork {
+  uint32_t head, ends, tri[2];  // as in PreCut
+  int32_t id[3], eo[3];
+  uint32_t corners;  // those that an output triangle uses
+  int nt;            // output triangles
+  uint32_t crossed;  // ends that are crossings; bit 4: a vertex inside
+};
+// Triangle z of owner (kk, ii): its output to K, the places of crossing k and of
+// the vertex inside to pt[3 + k] and pt[7] at threadIdx.x.  false: there is no such
+// triangle.  After an error (raised) K is empty.
+__device__ __forceinline__ bool pre_cut_subdivide(const Img& d, const Geo& g, const PreArgs& P, int kk, int ii, int z,
+                                                  double2 (*pt)[256], PreCutWork& K) {
+  K.head = K.ends = K.tri[0] = K.tri[1] = K.corners = K.crossed = 0u;
+  K.nt = 0;
+  const PreSlots S = pre_owner_slots(P, g, kk, ii);
+  PreBits Bits;
+  pre_owner_bits(d, g, P, kk, ii, Bits);
+  PreGT T;
+  if (!pre_owner_tri(P, g, kk, ii, S, z, T)) return false;  // (a cut bit is set for triangles that are there only)
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    K.id[j] = T.c[j].id;
+    K.eo[j] = T.eo[j];
+  }
+  const double2 c[3] = {make_double2(T.c[0].x, T.c[0].y), make_double2(T.c[1].x, T.c[1].y), make_double2(T.c[2].x, T.c[2].y)};
+  const int32_t bnd[3] = {T.c[0].bnd, T.c[1].bnd, T.c[2].bnd};
+  // 1. the segments inside, clipped
+  PreSub s0, s1;
+  int nsub = 0;
+  const double m = 1e-9;
+  pre_segs_in_box(d, g, fmin(c[0].x, fmin(c[1].x, c[2].x)) - m, fmax(c[0].x, fmax(c[1].x, c[2].x)) + m,
+                  fmin(c[0].y, fmin(c[1].y, c[2].y)) - m, fmax(c[0].y, fmax(c[1].y, c[2].y)) + m, [&](const PreSeg& Sg) {
+    double fp[3], fq[3];
+#pragma unroll
+    for (int e = 0; e < 3; ++e) pre_half(Sg, c[e], c[(e + 1) % 3], bnd[e], bnd[(e + 1) % 3], fp[e], fq[e]);
+    PreSub sb;
+    int side = -1;
+    if (!pre_clip(Sg, c, bnd, fp, fq, side, &sb)) return;
+    if (nsub == 0) s0 = sb;
+    if (nsub == 1) s1 = sb;
+    ++nsub;
+  }, &Bits);
+  bool bad = nsub < 1 || nsub > 2;
+  if (nsub == 2) {  // chain order
+    if (s1.S.jq == s0.S.jp) {
+      const PreSub x = s0;
+      s0 = s1;
+      s1 = x;
+    }
+    bad = bad || s0.S.jq != s1.S.jp;
+  }
+  // 2. the pieces' ends: a corner, a crossing of an edge, or (between the two
+  // segments of one piece) the polyline vertex inside
+  const bool in0 = s0.c1 < 0 && s0.e1 < 0, in1 = nsub == 2 && s1.c0 < 0 && s1.e0 < 0;
+  const bool one = nsub == 1 || in0;  // one piece
+  const bool inner = nsub == 2 && in0;
+  bad = bad || (s0.c0 < 0 && s0.e0 < 0) || (nsub == 1 ? in0 : (in0 != in1 || (s1.c1 < 0 && s1.e1 < 0)));
+  if (bad) {  // more than two segments, or a piece that does not join or ends inside
+    pre_error(P);
+    return true;
+  }
+  const PreSeg& sl = inner ? s1.S : s0.S;  // of end 1
+  const int ec[4] = {s0.c0, inner ? s1.c1 : s0.c1, one ? -1 : s1.c0, one ? -1 : s1.c1};
+  const int ee[4] = {s0.c0 >= 0 ? -1 : s0.e0, inner ? (s1.c1 >= 0 ? -1 : s1.e1) : (s0.c1 >= 0 ? -1 : s0.e1),
+                     one || s1.c0 >= 0 ? -1 : s1.e0, one || s1.c1 >= 0 ? -1 : s1.e1};
+#pragma unroll
+  for (int j = 0; j < 3; ++j) pt[j][threadIdx.x] = c[j];
+  if (inner) pt[7][threadIdx.x] = make_double2(s0.S.qx, s0.S.qy);
+  double te[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    te[k] = 0.0;
+    if (ee[k] < 0) continue;
+    const PreSeg& Sg = k == 0 ? s0.S : (k == 1 ? sl : s1.S);
+    const PreGV A = pre_sel3(T.c[0], T.c[1], T.c[2], ee[k]);
+    const PreGV B = pre_sel3(T.c[1], T.c[2], T.c[0], ee[k]);
+    double2 q;
+    pre_crossing_xy(Sg, A.id < B.id ? A : B, A.id < B.id ? B : A, q.x, q.y);
+    pt[3 + k][threadIdx.x] = q;
+    const double L2 = (B.x - A.x) * (B.x - A.x) + (B.y - A.y) * (B.y - A.y);
+    te[k] = ((q.x - A.x) * (B.x - A.x) + (q.y - A.y) * (B.y - A.y)) / L2;
+    bad = bad || !(te[k] > 0 && te[k] < 1);
+  }
+  // 3. the boundary cycle: the corners and the crossings on each edge in order;
+  // nibble x of cyc: the point at place x, of cend: the end that sits there + 1,
+  // nibble k of place: where end k sits
+  uint32_t cyc = 0, cend = 0, place = 0, ends = 0;
+  int on[3] = {0, 0, 0};  // crossings per edge
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+#pragma unroll
+    for (int e = 0; e < 3; ++e) on[e] += ee[k] == e;
+  const int first[3] = {0, 1 + on[0], 2 + on[0] + on[1]};  // place of corner e
+#pragma unroll
+  for (int j = 0; j < 3; ++j) cyc |= (uint32_t)j << (4 * first[j]);
+  const int n = 3 + on[0] + on[1] + on[2];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    if (ee[k] < 0 && ec[k] < 0) continue;
+    int at;
+    if (ec[k] >= 0) {
+      at = pre_sel3(first[0], first[1], first[2], ec[k]);
+      bad = bad || ((cend >> (4 * at)) & 15u) != 0u;  // two pieces at one corner
+    } else {
+      int rank = 0;
+#pragma unroll
+      for (int o = 0; o < 4; ++o) rank += o != k && ee[o] == ee[k] && (te[o] < te[k] || (te[o] == te[k] && o < k));
+      const int cnt = pre_sel3(on[0], on[1], on[2], ee[k]);
+      at = pre_sel3(first[0], first[1], first[2], ee[k]) + 1 + rank;
+      cyc |= (uint32_t)(3 + k) << (4 * at);
+      const int32_t ia = pre_sel3(T.c[0].id, T.c[1].id, T.c[2].id, ee[k]), ib = pre_sel3(T.c[1].id, T.c[2].id, T.c[0].id, ee[k]);
+      ends |= (0x80u | (uint32_t)ee[k] | ((uint32_t)(ia < ib ? rank : cnt - 1 - rank) << 2)) << (8 * k);
+    }
+    cend |= (uint32_t)(k + 1) << (4 * at);
+    place |= (uint32_t)at << (4 * k);
+  }
+  // 4. faces: walk the cycle; at a piece end reached along the boundary, follow
+  // the piece; the foreground ones by the template rule
+  uint32_t used = 0;
+  int nt = 0;
+  for (int st = 0; st < n && !bad; ++st) {
+    if ((used >> st) & 1u) continue;
+    uint64_t face = 0;  // nibble j: point j of the face
+    int fm = 0, side = -1, at = st;
+    for (int guard = 0; guard < 16; ++guard) {
+      if ((used >> at) & 1u) break;
+      used |= 1u << at;
+      face |= (uint64_t)((cyc >> (4 * at)) & 15u) << (4 * fm);
+      ++fm;
+      const int nx = at + 1 == n ? 0 : at + 1;
+      const int k = (int)((cend >> (4 * nx)) & 15u) - 1;
+      if (k >= 0) {
+        const int s2 = (k & 1) ? 0 : 1;
+        if (side >= 0 && side != s2) bad = true;  // a face on both sides of the chain
+        side = s2;
+        face |= (uint64_t)((cyc >> (4 * nx)) & 15u) << (4 * fm);
+        ++fm;
+        if (inner) {
+          face |= 7ull << (4 * fm);
+          ++fm;
+        }
+        at = (int)((place >> (4 * (k ^ 1))) & 15u);
+      } else {
+        at = nx;
+      }
+      if (at == st || fm > 12) break;
+    }
+    if (side != 1 || bad) continue;
+    if (fm < 3) {  // degenerate face
+      bad = true;
+      continue;
+    }
+    int apex = -1, low = 8;
+    bool has_corner = false;
+    for (int j = 0; j < fm; ++j) {
+      const int q = (int)(face >> (4 * j)) & 15;
+      has_corner = has_corner || q < 3;
+      // the earliest chain point: the lowest end; the inner vertex before all
+      int o = q == 7 ? -1 : q - 3;
+      if (q < 3) {
+        const int w = (int)((cend >> (4 * pre_sel3(first[0], first[1], first[2], q))) & 15u);
+        o = w ? w - 1 : 8;
+      }
+      if (o < low) {
+        low = o;
+        apex = j;
+      }
+    }
+    if (!inner && fm == 4 && !one && !has_corner) {
+      // the middle quadrilateral between two chords: diagonal joining their exits
+      apex = -1;
+      for (int j = 0; j < 4; ++j)
+        if (((face >> (4 * j)) & 15u) == 4u) apex = j;
+      if (apex < 0 || ((face >> (4 * ((apex + 2) & 3))) & 15u) != 6u) bad = true;  // nested exits not opposite
+    }
+    if (apex < 0) bad = true;
+    if (bad) continue;
+    const int pa = (int)(face >> (4 * apex)) & 15;
+    const double2 a = pt[pa][threadIdx.x];
+    for (int j = 1; j + 1 < fm; ++j) {
+      const int jb = apex + j >= fm ? apex + j - fm : apex + j, jc = jb + 1 == fm ? 0 : jb + 1;
+      const int pb = (int)(face >> (4 * jb)) & 15, pc = (int)(face >> (4 * jc)) & 15;
+      const double2 b = pt[pb][threadIdx.x], e = pt[pc][threadIdx.x];
+      if (!((b.x - a.x) * (e.y - a.y) - (b.y - a.y) * (e.x - a.x) > 0.0)) pre_error(P);
+      const uint32_t w = (uint32_t)(pa | (pb << 3) | (pc << 6)) << (9 * (nt & 1));
+      K.tri[0] |= nt < 2 ? w : 0u;
+      K.tri[1] |= nt >= 2 && nt < kPreKeep ? w : 0u;
+      K.corners |= (1u << pa) | (1u << pb) | (1u << pc);
+      ++nt;
+    }
+  }
+  if (bad || nt > kPreKeep) {
+    pre_error(P);
+    K.tri[0] = K.tri[1] = K.corners = 0u;
+    return true;
+  }
+  K.nt = nt;
+  K.head = (uint32_t)nt | ((uint32_t)T.es[0] << 8) | ((uint32_t)T.es[1] << 12) | ((uint32_t)T.es[2] << 16) |
+           (inner ? 1u << 20 : 0u);
+  K.ends = ends;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) K.crossed |= ee[k] >= 0 ? 1u << k : 0u;
+  if (inner) K.crossed |= 16u;
+  return true;
+}
+// Its counts, and the corners it uses.
+__device__ __forceinline__ void pre_cut_counted(const PreArgs& P, int64_t v, int z, const PreCutWork& K) {
+#pragma unroll
+  for (int j = 0; j < 3; ++j)
+    if ((K.corners >> j) & 1u) P.used[K.id[j]] = 1;
+  pre_add_counts(P, v, z, K.nt, (int)(K.crossed >> 4));
+}
+// The cut grid triangles that have a slot, one lane each.  Their triangles are kept
+// for k_pre_cut_write, with the crossings' edges, order and places.
 __global__ void __launch_bounds__(256, 3) k_pre_cut_make(OneSrc src, PreArgs P) {
   __shared__ double2 pt[8][256];
   const Img& d = src.d;
   const Geo g = d.g;
-  const int me = threadIdx.x;
   const int64_t n_items = min(P.counts[4], P.ccap);
-  for (int64_t slot = (int64_t)blockIdx.x * 256 + me; slot < n_items; slot += (int64_t)gridDim.x * 256) {
+  for (int64_t slot = (int64_t)blockIdx.x * 256 + threadIdx.x; slot < n_items; slot += (int64_t)gridDim.x * 256) {
     const uint64_t item = P.citem[slot];
     const int z = (int)(item & 3u);
     int kk, ii;
     pre_tl_owner(g, P, (int64_t)(item >> 2), kk, ii);
-    const int64_t v = (int64_t)kk * g.NI + ii;
-    const PreSlots S = pre_owner_slots(P, g, kk, ii);
-    PreBits Bits;
-    pre_owner_bits(d, g, P, kk, ii, Bits);
-    PreGT T;
+    PreCutWork W;
+    const bool there = pre_cut_subdivide(d, g, P, kk, ii, z, pt, W);
+    if (there) pre_cut_counted(P, (int64_t)kk * g.NI + ii, z, W);
     PreCut& K = P.cstore[slot];
-    if (!pre_owner_tri(P, g, kk, ii, S, z, T)) {  // (a cut bit is set for triangles that are there only)
-      K.head = 0;
-      K.ends = 0;
-      continue;
-    }
-    const double2 c[3] = {make_double2(T.c[0].x, T.c[0].y), make_double2(T.c[1].x, T.c[1].y), make_double2(T.c[2].x, T.c[2].y)};
-    const int32_t bnd[3] = {T.c[0].bnd, T.c[1].bnd, T.c[2].bnd};
-    // 1. the segments inside, clipped
-    PreSub s0, s1;
-    int nsub = 0;
-    const double m = 1e-9;
-    pre_segs_in_box(d, g, fmin(c[0].x, fmin(c[1].x, c[2].x)) - m, fmax(c[0].x, fmax(c[1].x, c[2].x)) + m,
-                    fmin(c[0].y, fmin(c[1].y, c[2].y)) - m, fmax(c[0].y, fmax(c[1].y, c[2].y)) + m, [&](const PreSeg& Sg) {
-      double fp[3], fq[3];
-#pragma unroll
-      for (int e = 0; e < 3; ++e) pre_half(Sg, c[e], c[(e + 1) % 3], bnd[e], bnd[(e + 1) % 3], fp[e], fq[e]);
-      PreSub sb;
-      int side = -1;
-      if (!pre_clip(Sg, c, bnd, fp, fq, side, &sb)) return;
-      if (nsub == 0) s0 = sb;
-      if (nsub == 1) s1 = sb;
-      ++nsub;
-    }, &Bits);
-    bool bad = nsub < 1 || nsub > 2;
-    if (nsub == 2) {  // chain order
-      if (s1.S.jq == s0.S.jp) {
-        const PreSub x = s0;
-        s0 = s1;
-        s1 = x;
-      }
-      bad = bad || s0.S.jq != s1.S.jp;
-    }
-    // 2. the pieces' ends: a corner, a crossing of an edge, or (between the two
-    // segments of one piece) the polyline vertex inside
-    const bool in0 = s0.c1 < 0 && s0.e1 < 0, in1 = nsub == 2 && s1.c0 < 0 && s1.e0 < 0;
-    const bool one = nsub == 1 || in0;  // one piece
-    const bool inner = nsub == 2 && in0;
-    bad = bad || (s0.c0 < 0 && s0.e0 < 0) || (nsub == 1 ? in0 : (in0 != in1 || (s1.c1 < 0 && s1.e1 < 0)));
-    if (bad) {  // more than two segments, or a piece that does not join or ends inside
-      pre_error(P);
-      pre_add_counts(P, v, z, 0, 0);
-      K.head = 0;
-      K.ends = 0;
-      continue;
-    }
-    const PreSeg& sl = inner ? s1.S : s0.S;  // of end 1
-    const int ec[4] = {s0.c0, inner ? s1.c1 : s0.c1, one ? -1 : s1.c0, one ? -1 : s1.c1};
-    const int ee[4] = {s0.c0 >= 0 ? -1 : s0.e0, inner ? (s1.c1 >= 0 ? -1 : s1.e1) : (s0.c1 >= 0 ? -1 : s0.e1),
-                       one || s1.c0 >= 0 ? -1 : s1.e0, one || s1.c1 >= 0 ? -1 : s1.e1};
-#pragma unroll
-    for (int j = 0; j < 3; ++j) pt[j][me] = c[j];
-    if (inner) pt[7][me] = make_double2(s0.S.qx, s0.S.qy);
-    double te[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      te[k] = 0.0;
-      if (ee[k] < 0) continue;
-      const PreSeg& Sg = k == 0 ? s0.S : (k == 1 ? sl : s1.S);
-      const PreGV A = pre_sel3(T.c[0], T.c[1], T.c[2], ee[k]);
-      const PreGV B = pre_sel3(T.c[1], T.c[2], T.c[0], ee[k]);
-      double2 q;
-      pre_crossing_xy(Sg, A.id < B.id ? A : B, A.id < B.id ? B : A, q.x, q.y);
-      pt[3 + k][me] = q;
-      const double L2 = (B.x - A.x) * (B.x - A.x) + (B.y - A.y) * (B.y - A.y);
-      te[k] = ((q.x - A.x) * (B.x - A.x) + (q.y - A.y) * (B.y - A.y)) / L2;
-      bad = bad || !(te[k] > 0 && te[k] < 1);
-    }
-    // 3. the boundary cycle: the corners and the crossings on each edge in order;
-    // nibble x of cyc: the point at place x, of cend: the end that sits there + 1,
-    // nibble k of place: where end k sits
-    uint32_t cyc = 0, cend = 0, place = 0, ends = 0;
-    int on[3] = {0, 0, 0};  // crossings per edge
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-#pragma unroll
-      for (int e = 0; e < 3; ++e) on[e] += ee[k] == e;
-    const int first[3] = {0, 1 + on[0], 2 + on[0] + on[1]};  // place of corner e
-#pragma unroll
-    for (int j = 0; j < 3; ++j) cyc |= (uint32_t)j << (4 * first[j]);
-    const int n = 3 + on[0] + on[1] + on[2];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      if (ee[k] < 0 && ec[k] < 0) continue;
-      int at;
-      if (ec[k] >= 0) {
-        at = pre_sel3(first[0], first[1], first[2], ec[k]);
-        bad = bad || ((cend >> (4 * at)) & 15u) != 0u;  // two pieces at one corner
-      } else {
-        int rank = 0;
-#pragma unroll
-        for (int o = 0; o < 4; ++o) rank += o != k && ee[o] == ee[k] && (te[o] < te[k] || (te[o] == te[k] && o < k));
-        const int cnt = pre_sel3(on[0], on[1], on[2], ee[k]);
-        at = pre_sel3(first[0], first[1], first[2], ee[k]) + 1 + rank;
-        cyc |= (uint32_t)(3 + k) << (4 * at);
-        const int32_t ia = pre_sel3(T.c[0].id, T.c[1].id, T.c[2].id, ee[k]), ib = pre_sel3(T.c[1].id, T.c[2].id, T.c[0].id, ee[k]);
-        ends |= (0x80u | (uint32_t)ee[k] | ((uint32_t)(ia < ib ? rank : cnt - 1 - rank) << 2)) << (8 * k);
-      }
-      cend |= (uint32_t)(k + 1) << (4 * at);
-      place |= (uint32_t)at << (4 * k);
-    }
-    // 4. faces: walk the cycle; at a piece end reached along the boundary, follow
-    // the piece; the foreground ones by the template rule
-    uint32_t used = 0, corners = 0, tri[2] = {0, 0};
-    int nt = 0;
-    for (int st = 0; st < n && !bad; ++st) {
-      if ((used >> st) & 1u) continue;
-      uint64_t face = 0;  // nibble j: point j of the face
-      int fm = 0, side = -1, at = st;
-      for (int guard = 0; guard < 16; ++guard) {
-        if ((used >> at) & 1u) break;
-        used |= 1u << at;
-        face |= (uint64_t)((cyc >> (4 * at)) & 15u) << (4 * fm);
-        ++fm;
-        const int nx = at + 1 == n ? 0 : at + 1;
-        const int k = (int)((cend >> (4 * nx)) & 15u) - 1;
-        if (k >= 0) {
-          const int s2 = (k & 1) ? 0 : 1;
-          if (side >= 0 && side != s2) bad = true;  // a face on both sides of the chain
-          side = s2;
-          face |= (uint64_t)((cyc >> (4 * nx)) & 15u) << (4 * fm);
-          ++fm;
-          if (inner) {
-            face |= 7ull << (4 * fm);
-            ++fm;
-          }
-          at = (int)((place >> (4 * (k ^ 1))) & 15u);
-        } else {
-          at = nx;
-        }
-        if (at == st || fm > 12) break;
-      }
-      if (side != 1 || bad) continue;
-      if (fm < 3) {  // degenerate face
-        bad = true;
-        continue;
-      }
-      int apex = -1, low = 8;
-      bool has_corner = false;
-      for (int j = 0; j < fm; ++j) {
-        const int q = (int)(face >> (4 * j)) & 15;
-        has_corner = has_corner || q < 3;
-        // the earliest chain point: the lowest end; the inner vertex before all
-        int o = q == 7 ? -1 : q - 3;
-        if (q < 3) {
-          const int w = (int)((cend >> (4 * pre_sel3(first[0], first[1], first[2], q))) & 15u);
-          o = w ? w - 1 : 8;
-        }
-        if (o < low) {
-          low = o;
-          apex = j;
-        }
-      }
-      if (!inner && fm == 4 && !one && !has_corner) {
-        // the middle quadrilateral between two chords: diagonal joining their exits
-        apex = -1;
-        for (int j = 0; j < 4; ++j)
-          if (((face >> (4 * j)) & 15u) == 4u) apex = j;
-        if (apex < 0 || ((face >> (4 * ((apex + 2) & 3))) & 15u) != 6u) bad = true;  // nested exits not opposite
-      }
-      if (apex < 0) bad = true;
-      if (bad) continue;
-      const int pa = (int)(face >> (4 * apex)) & 15;
-      const double2 a = pt[pa][me];
-      for (int j = 1; j + 1 < fm; ++j) {
-        const int jb = apex + j >= fm ? apex + j - fm : apex + j, jc = jb + 1 == fm ? 0 : jb + 1;
-        const int pb = (int)(face >> (4 * jb)) & 15, pc = (int)(face >> (4 * jc)) & 15;
-        const double2 b = pt[pb][me], e = pt[pc][me];
-        if (!((b.x - a.x) * (e.y - a.y) - (b.y - a.y) * (e.x - a.x) > 0.0)) pre_error(P);
-        const uint32_t w = (uint32_t)(pa | (pb << 3) | (pc << 6)) << (9 * (nt & 1));
-        tri[0] |= nt < 2 ? w : 0u;
-        tri[1] |= nt >= 2 && nt < kPreKeep ? w : 0u;
-        corners |= (1u << pa) | (1u << pb) | (1u << pc);
-        ++nt;
-      }
-    }
-    if (bad) {
-      pre_error(P);
-      nt = 0;
-      corners = 0;
-    }
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-      if ((corners >> j) & 1u) P.used[T.c[j].id] = 1;
-    pre_add_counts(P, v, z, nt, inner && !bad ? 1 : 0);
-    const bool keep = nt <= kPreKeep;
-    if (!keep) P.counts[5] = 1;
-    K.head = (keep ? (uint32_t)nt : kPreNotKept) | ((uint32_t)T.es[0] << 8) | ((uint32_t)T.es[1] << 12) | ((uint32_t)T.es[2] << 16) |
-             (inner && !bad ? 1u << 20 : 0u);
-    K.ends = bad ? 0u : ends;
-    K.tri[0] = tri[0];
-    K.tri[1] = tri[1];
+    K.head = W.head;
+    K.ends = W.ends;
+    if (W.head == 0u) continue;  // nothing to write
+    K.tri[0] = W.tri[0];
+    K.tri[1] = W.tri[1];
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
-      K.id[j] = T.c[j].id;
-      K.eo[j] = T.eo[j];
+      K.id[j] = W.id[j];
+      K.eo[j] = W.eo[j];
     }
 #pragma unroll
     for (int k = 0; k < 4; ++k)
-      if (ee[k] >= 0) K.pos[k] = pt[3 + k][me];
-    if (inner) K.pos[4] = pt[7][me];
+      if ((W.crossed >> k) & 1u) K.pos[k] = pt[3 + k][threadIdx.x];
+    if (W.crossed & 16u) K.pos[4] = pt[7][threadIdx.x];
   }
 }
 
-// The cut grid triangles beyond the slots (there are none on ordinary meshes:
-// the room is one for every sixteen owners), gathered per block and counted on
-// full blocks by the general subdivision.  Held to 128 VGPRs (four waves per
-// SIMD): spilling more to scratch costs less than the latency two waves per
-// SIMD leave uncovered.
-__global__ void __launch_bounds__(256, 4) k_pre_mesh_cut_count(OneSrc src, PreArgs P, Shared sh) {
+// The cut grid triangles beyond the slots, gathered per block and counted on full
+// blocks; nothing of them is kept (k_pre_mesh_cut_rest subdivides them again).
+// There are none on smooth shapes, where the room, one for every sixteen owners,
+// does; on noise of one to three pixels most have no slot.
+__global__ void __launch_bounds__(256, 3) k_pre_mesh_cut_count(OneSrc src, PreArgs P, Shared sh) {
+  __shared__ double2 pt[8][256];
   __shared__ int64_t dl[512];
   __shared__ int nd;
   if (P.counts[4] <= P.ccap) return;  // uniform
@@ -2399,7 +1905,13 @@ __global__ void __launch_bounds__(256, 4) k_pre_mesh_cut_count(OneSrc src, PreAr
   pre_dense(4 * T, dl, &nd, [&](int64_t it) -> bool {
     const uint32_t rt = P.rtri[P.tlist[it >> 2]];
     return ((rt >> (28 + (it & 3))) & 1u) && pre_cut_slot(P, it >> 2, (int)(it & 3), rt) >= P.ccap;
-  }, [&](int64_t it) { pre_mesh_cut_tri_count(d, g, P, it >> 2, (int)(it & 3)); });
+  }, [&](int64_t it) {
+    int kk, ii;
+    pre_tl_owner(g, P, it >> 2, kk, ii);
+    PreCutWork W;
+    if (pre_cut_subdivide(d, g, P, kk, ii, (int)(it & 3), pt, W))
+      pre_cut_counted(P, (int64_t)kk * g.NI + ii, (int)(it & 3), W);
+  });
 }
 
 // What is known of a row segment's owners, every load before the first use: the
@@ -2596,88 +2108,95 @@ __global__ void __launch_bounds__(256) k_pre_mesh_whole_tris(OneSrc src, PreArgs
     if (!more) break;
   }
 }
-// Output of the cut grid triangles kept in their slots, one lane each: the
-// crossings' and the inner vertex's places go to their mesh vertices (the two
-// triangles of an edge write the same places), the triangles to theirs, all by
-// number: a crossing is the edge owner's first one of that edge plus its order.
+// Output of cut grid triangle z of owner v (head, ends, t01, t23, kid, keo as in
+// PreCut; place(k) the place of crossing k, 4: of the vertex inside): the crossings'
+// and the inner vertex's places go to their mesh vertices (the two triangles of an
+// edge write the same places), the triangles to theirs, all by number: a crossing is
+// the edge owner's first one of that edge plus its order.
+template <class Place>
+__device__ __forceinline__ void pre_cut_output(const PreArgs& P, const Geo& g, int64_t NV, int64_t v, int z, uint32_t head,
+                                               uint32_t ends, uint32_t t01, uint32_t t23, const int32_t (&kid)[3],
+                                               const int32_t (&keo)[3], Place place) {
+  double2* const Vout = reinterpret_cast<double2*>(P.overts);
+  const int kn = (int)(head & 255u);
+  const uint32_t rc = P.rcount[v], rt = P.rtri[v];
+  int32_t cid[3];  // corners in the mesh (one that no triangle uses has no number, and none is looked at)
+  int64_t id[4];
+#pragma unroll
+  for (int j = 0; j < 3; ++j) cid[j] = pre_vertex(P, kid[j]);
+  int64_t eb[3];
+#pragma unroll
+  for (int e = 0; e < 3; ++e) {
+    int cnt = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) cnt += ((ends >> (8 * k)) & 0x83u) == (0x80u | (uint32_t)e);
+    eb[e] = 0;
+    if (!cnt) continue;
+    const int64_t w = keo[e];
+    const int es = (int)((head >> (8 + 4 * e)) & 15u);
+    const uint32_t rw = pre_owner_counts(P, g, (uint32_t)w);
+    if (pre_rc_cross(rw, es) != cnt) {  // the edge and the triangle see other crossings
+      pre_error(P);
+      eb[e] = P.ovcap;  // no row: an owner without crossings has no base (rbase is not written there)
+      continue;
+    }
+    eb[e] = NV + P.rbase[w] + pre_rc_before(rw, es);
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const uint32_t x = (ends >> (8 * k)) & 255u;
+    id[k] = pre_sel3(eb[0], eb[1], eb[2], (int)(x & 3u)) + ((x >> 2) & 3u);
+    if ((x & 0x80u) && id[k] < P.ovcap) Vout[id[k]] = place(k);
+  }
+  int64_t inner = 0;
+  if ((head >> 20) & 1u) {
+    inner = NV + P.rbase[v] + pre_rc_before(rc, 8) + __builtin_popcount((rt >> 24) & ((1u << z) - 1u));
+    if (inner < P.ovcap) Vout[inner] = place(4);
+  }
+  int before = 0;
+  for (int z2 = 0; z2 < z; ++z2) before += (int)((rt >> (6 * z2)) & 63u);
+  const int64_t pos = P.rtbase[v] + before;
+  auto num = [&](uint32_t p) -> int32_t {
+    const int32_t c = pre_sel3(cid[0], cid[1], cid[2], (int)(p & 3u));
+    const int32_t x01 = (int32_t)(p == 3u ? id[0] : id[1]), x23 = (int32_t)(p == 5u ? id[2] : id[3]);
+    return p < 3u ? c : (p == 7u ? (int32_t)inner : (p < 5u ? x01 : x23));
+  };
+  for (int j = 0; j < kn; ++j) {
+    if (pos + j >= P.otcap) break;
+    const uint32_t w = ((j < 2 ? t01 : t23) >> (9 * (j & 1))) & 511u;
+    Tri3 t3;
+    t3.a = num(w & 7u);
+    t3.b = num((w >> 3) & 7u);
+    t3.c = num(w >> 6);
+    *reinterpret_cast<Tri3*>(P.otris + 3 * (pos + j)) = t3;
+    P.ocodes[pos + j] = 1;
+  }
+}
+// The cut grid triangles kept in their slots, one lane each.
 __global__ void __launch_bounds__(256) k_pre_cut_write(OneSrc src, PreArgs P) {
   const Geo g = src.d.g;
   int64_t n = min(P.counts[4], P.ccap);
   const int64_t NV = *P.nused;
   if (!pre_planned(P)) n = 0;
-  double2* const Vout = reinterpret_cast<double2*>(P.overts);
   for (int64_t slot = (int64_t)blockIdx.x * 256 + threadIdx.x; slot < n; slot += (int64_t)gridDim.x * 256) {
     const PreCut& K = P.cstore[slot];
     const uint32_t head = K.head, ends = K.ends;
     const int kn = (int)(head & 255u);
-    if ((uint32_t)kn == kPreNotKept || (kn == 0 && ends == 0u)) continue;
+    if (kn == 0 && ends == 0u) continue;
     const uint64_t item = P.citem[slot];
-    const int z = (int)(item & 3u);
-    const int64_t v = P.tlist[item >> 2];
-    const uint32_t rc = P.rcount[v], rt = P.rtri[v];
-    int32_t cid[3];  // corners in the mesh (one that no triangle uses has no number, and none is looked at)
-    int64_t id[4];
-#pragma unroll
-    for (int j = 0; j < 3; ++j) cid[j] = pre_vertex(P, K.id[j]);
-    int64_t eb[3];
-#pragma unroll
-    for (int e = 0; e < 3; ++e) {
-      int cnt = 0;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) cnt += ((ends >> (8 * k)) & 0x83u) == (0x80u | (uint32_t)e);
-      eb[e] = 0;
-      if (!cnt) continue;
-      const int64_t w = K.eo[e];
-      const int es = (int)((head >> (8 + 4 * e)) & 15u);
-      const uint32_t rw = pre_owner_counts(P, g, (uint32_t)w);
-      if (pre_rc_cross(rw, es) != cnt) {  // the edge and the triangle see other crossings
-        pre_error(P);
-        eb[e] = P.ovcap;  // no row: an owner without crossings has no base (rbase is not written there)
-        continue;
-      }
-      eb[e] = NV + P.rbase[w] + pre_rc_before(rw, es);
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const uint32_t x = (ends >> (8 * k)) & 255u;
-      id[k] = pre_sel3(eb[0], eb[1], eb[2], (int)(x & 3u)) + ((x >> 2) & 3u);
-      if ((x & 0x80u) && id[k] < P.ovcap) Vout[id[k]] = K.pos[k];
-    }
-    int64_t inner = 0;
-    if ((head >> 20) & 1u) {
-      inner = NV + P.rbase[v] + pre_rc_before(rc, 8) + __builtin_popcount((rt >> 24) & ((1u << z) - 1u));
-      if (inner < P.ovcap) Vout[inner] = K.pos[4];
-    }
-    int before = 0;
-    for (int z2 = 0; z2 < z; ++z2) before += (int)((rt >> (6 * z2)) & 63u);
-    const int64_t pos = P.rtbase[v] + before;
-    const uint32_t t01 = K.tri[0], t23 = K.tri[1];
-    auto num = [&](uint32_t p) -> int32_t {
-      const int32_t c = pre_sel3(cid[0], cid[1], cid[2], (int)(p & 3u));
-      const int32_t x01 = (int32_t)(p == 3u ? id[0] : id[1]), x23 = (int32_t)(p == 5u ? id[2] : id[3]);
-      return p < 3u ? c : (p == 7u ? (int32_t)inner : (p < 5u ? x01 : x23));
-    };
-    for (int j = 0; j < kn; ++j) {
-      if (pos + j >= P.otcap) break;
-      const uint32_t w = ((j < 2 ? t01 : t23) >> (9 * (j & 1))) & 511u;
-      Tri3 t3;
-      t3.a = num(w & 7u);
-      t3.b = num((w >> 3) & 7u);
-      t3.c = num(w >> 6);
-      *reinterpret_cast<Tri3*>(P.otris + 3 * (pos + j)) = t3;
-      P.ocodes[pos + j] = 1;
-    }
+    pre_cut_output(P, g, NV, P.tlist[item >> 2], (int)(item & 3u), head, ends, K.tri[0], K.tri[1], K.id, K.eo,
+                   [&](int k) { return K.pos[k]; });
   }
 }
-// The cut grid triangles that were not kept (beyond the slots, or of more than
-// kPreKeep output triangles; none on ordinary meshes), by the general
-// subdivision: the crossings of their edges and their inner vertices, then
-// their triangles.
-__global__ void __launch_bounds__(256, 4) k_pre_mesh_cut_rest(OneSrc src, PreArgs P) {
+// The cut grid triangles beyond the slots, subdivided again.
+// 2000 x 2000 noise of one pixel (1.6 M cut triangles, 65536 slots), the whole call:
+// with points, pieces and faces in local arrays and the vertices looked for by walks
+// and subdivisions of their own 7.2 ms (5.6 before any was kept in full), now 2.3.
+__global__ void __launch_bounds__(256, 3) k_pre_mesh_cut_rest(OneSrc src, PreArgs P) {
+  __shared__ double2 pt[8][256];
   __shared__ int64_t dl[512];
   __shared__ int nd;
-  const int64_t slots = P.counts[4], not_kept = P.counts[5];
-  if ((slots <= P.ccap && not_kept == 0) || !pre_planned(P)) return;  // uniform
+  if (P.counts[4] <= P.ccap || !pre_planned(P)) return;  // uniform
   const Img& d = src.d;
   const Geo g = d.g;
   if (threadIdx.x == 0) nd = 0;
@@ -2686,31 +2205,14 @@ __global__ void __launch_bounds__(256, 4) k_pre_mesh_cut_rest(OneSrc src, PreArg
   const int64_t NV = *P.nused;
   pre_dense(4 * T, dl, &nd, [&](int64_t it) -> bool {
     const uint32_t rt = P.rtri[P.tlist[it >> 2]];
-    const int z = (int)(it & 3);
-    if (!((rt >> (6 * z)) & 63u) || !((rt >> (28 + z)) & 1u)) return false;
-    const int64_t slot = pre_cut_slot(P, it >> 2, z, rt);
-    return slot >= P.ccap || (P.cstore[slot].head & 255u) == kPreNotKept;
+    return ((rt >> (28 + (it & 3))) & 1u) && pre_cut_slot(P, it >> 2, (int)(it & 3), rt) >= P.ccap;
   }, [&](int64_t it) {
     int kk, ii;
     pre_tl_owner(g, P, it >> 2, kk, ii);
-    const int z = (int)(it & 3);
-    const int64_t v = (int64_t)kk * g.NI + ii;
-    const uint32_t rt = P.rtri[v], rc = P.rcount[v];
-    PreGT T;
-    if (!pre_owner_tri(P, g, kk, ii, pre_owner_slots(P, g, kk, ii), z, T)) return;
-    for (int e = 0; e < 3; ++e) {
-      const int64_t w = pre_sel3(T.eo[0], T.eo[1], T.eo[2], e);
-      const int q = pre_sel3(T.es[0], T.es[1], T.es[2], e);
-      const uint32_t rw = pre_owner_counts(P, g, (uint32_t)w);
-      const int cq = pre_rc_cross(rw, q);
-      if (cq) pre_slot_vertices(d, g, P, (int)(w / g.NI), (int)(w % g.NI), q, cq, NV + P.rbase[w] + pre_rc_before(rw, q));
-    }
-    if ((rt >> (24 + z)) & 1u)
-      pre_inner_vertex(d, g, P, kk, ii, z,
-                       NV + P.rbase[v] + pre_rc_before(rc, 8) + __builtin_popcount((rt >> 24) & ((1u << z) - 1u)));
-    int before = 0;
-    for (int z2 = 0; z2 < z; ++z2) before += (int)((rt >> (6 * z2)) & 63u);
-    pre_owner_triangle(d, g, P, kk, ii, z, rc, rt, P.rtbase[v] + before, NV);
+    PreCutWork W;
+    if (pre_cut_subdivide(d, g, P, kk, ii, (int)(it & 3), pt, W) && W.head)
+      pre_cut_output(P, g, NV, (int64_t)kk * g.NI + ii, (int)(it & 3), W.head, W.ends, W.tri[0], W.tri[1], W.id, W.eo,
+                     [&](int k) { return pt[k == 4 ? 7 : 3 + k][threadIdx.x]; });
   });
 }
 
