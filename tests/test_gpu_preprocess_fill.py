@@ -133,3 +133,38 @@ def test_fill_refuses_a_workspace_without_its_plan():
     assert refused()
     assert c.size(ws) == -7
     assert c.fill(ws) == 0 and c.filled()
+
+
+@pytest.mark.parametrize("grid_h,size,seed", [(2.5, 150, 50), (2.5, 150, 51), (1.25, 75, 52)])
+def test_a_plan_that_failed_is_not_written(grid_h, size, seed):
+    """At these edges a polyline vertex can lie within b of two sides, which the
+    oracle refuses, too.  The counts and numbers of such a plan do not fit
+    together: no pass may write by them, in the call itself or in a fill."""
+    import ctypes
+
+    import torch
+
+    import oracle
+    from paper_2602_19474_amd import _image, _lib, _stream_ptr, context
+    from paper_2602_19474_amd.preprocess import paper_thresholds
+    print(f"[gpu-pre-fill] failed plan {size} h={grid_h} seed {seed}", flush=True)
+    bm = wl.smoothed_noise(size, size, 6.0, 0.0, False, wl.rng(seed, int(grid_h * 64)))
+    with pytest.raises(oracle.OracleError):
+        oracle.mesh_preprocessed(bm, grid_h)
+    t = torch.from_numpy(bm).to("cuda")
+    L, h, img, th = _lib.lib(), context(0).handle, _image(t, grid_h, 0), paper_thresholds(grid_h)
+    b, g = ctypes.c_size_t(), ctypes.c_int64()
+    assert L.sbmt_pre_mesh_query(ctypes.byref(img), ctypes.byref(b), ctypes.byref(g)) == 0
+    ws = torch.empty(int(b.value), dtype=torch.uint8, device="cuda")
+    cap = 50000
+    counts = (ctypes.c_int64 * 8)()
+    verts = torch.full((cap, 2), -7.0, dtype=torch.float64, device="cuda")
+    tris = torch.full((cap, 3), -7, dtype=torch.int32, device="cuda")
+    codes = torch.full((cap,), 7, dtype=torch.uint8, device="cuda")
+    for byte in (0, 0xff):  # whatever the workspace held
+        ws.fill_(byte)
+        for fn, st in (("sbmt_preprocess_mesh", -6), ("sbmt_preprocess_mesh_fill", -1)):
+            assert getattr(L, fn)(h, ctypes.byref(img), *th, ws.data_ptr(), ws.numel(), verts.data_ptr(), cap,
+                                  tris.data_ptr(), codes.data_ptr(), cap, counts, _stream_ptr(None)) == st
+            assert counts[5] == st
+    assert bool((verts == -7.0).all()) and bool((tris == -7).all()) and bool((codes == 7).all())
