@@ -704,6 +704,9 @@ __global__ void __launch_bounds__(kThreads, 8) k_count(Src src, const int64_t* _
 // k_slow_tiles, for calls of few tiles.  There three launches cost more than
 // waves that are not full (one sbmt_mesh_async: 10 tiles 43 -> 35 us, 225
 // 58 -> 46, 1302 84 -> 75, 2312 118 -> 112, 5208 the same, 9248 242 -> 255).
+// The more owners are slow the fuller its waves: with cut triangles 0.05 per owner
+// 3620 tiles 123 -> 120 us, 0.23 230 -> 215, 0.33 (edge 4) 302 -> 282, and 2256 tiles
+// with 0.43 (edge 2) 417 -> 374.
 template <class Src, int RB>
 __global__ void __launch_bounds__(kThreads, 4) k_count_small(Src src, const int64_t* __restrict__ tab, Shared sh) {
   __shared__ CountLds<RB> L;

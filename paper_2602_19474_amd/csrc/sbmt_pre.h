@@ -208,7 +208,8 @@ __device__ __forceinline__ V pre_sel3(const V& x, const V& y, const V& z, int j)
 // Place of lattice vertex v = (k, i) with flags f: the grid stores everyone's
 // (kAll), the mesh only the moved ones' (1.2 GB less to write and read back on
 // 8192 x 8192).  A select and no branch, so that the loads of a triangle's corners
-// are in flight together (k_pre_count with branches 563 us, so 437).
+// are in flight together (k_pre_count, its check still on the waves as they fell,
+// with branches 563 us, so 437; with every place stored 344).
 template <bool kAll>
 __device__ __forceinline__ double2 pre_place(const PreArgs& P, const Geo& g, int64_t v, int k, int i, uint32_t f) {
   const double2* const V = reinterpret_cast<const double2*>(P.verts);
@@ -561,7 +562,8 @@ __device__ __forceinline__ bool pre_segment(const Geo& g, const Shared& sh, int6
 // per slot, two for a slot with a split side).  The owners with a moved corner or a
 // split side are gathered in LDS, their four corners' flags with them, and checked
 // on full waves: the check's FP64 work was most of the kernel, done on waves with
-// a few such owners each (8192 x 8192 416 -> 241 us, 4000 x 3000 72 -> 42 us).
+// a few such owners each (with every place stored 8192 x 8192 344 -> 229 us, 4000 x
+// 3000 72 -> 42; with computed ones 437 -> 242).
 template <bool kAll>
 __global__ void __launch_bounds__(256) k_pre_count(OneSrc src, PreArgs P, Shared sh) {
   __shared__ uint32_t lds[4][kCB];
@@ -1325,7 +1327,7 @@ __device__ __forceinline__ void pre_add_counts(const PreArgs& P, int64_t v, int 
 // are marked kPreTodo and gathered by k_pre_mesh_probe_owner, which takes their
 // four grid triangles and eight edge slots one by one, with the loads of each.
 // Taking every owner that way was bound by the latency of those loads, about
-// thirty in a row (2.26 ms on 77 M owners; now 0.75 + 0.40 ms).
+// thirty in a row (2.26 ms on 77 M owners; now 0.78 + 0.52 ms).
 constexpr uint32_t kPreTodo = 1u << 24;  // (an inner vertex without a cut triangle: no count leaves that)
 
 // Sides of a segment's ends on the line through A -> B (a segment end that is
@@ -1485,9 +1487,8 @@ __global__ void __launch_bounds__(256, 4) k_pre_mesh_probe_plain(OneSrc src, Pre
 // The owners marked kPreTodo, 64 at a time: a lane per grid triangle, then a
 // lane per edge slot in two rounds, their results added up in LDS.  A lane that
 // goes through an owner's four triangles and eight edges waits for twelve
-// chains of loads in turn: 95 us for the few owners of a 1024 x 1024 image,
-// where this takes 33 (on the 8192 x 8192 one, with waves enough to hide them,
-// 400 against 520 us).
+// chains of loads in turn: 95 us for the few owners of a 1024 x 1024 image, where
+// this takes 38 (8192 x 8192: 521).
 constexpr int kPreOwners = 64;
 __global__ void __launch_bounds__(256) k_pre_mesh_probe_owner(OneSrc src, PreArgs P, Shared sh) {
   __shared__ int32_t dl[256 + kPreOwners];
@@ -1642,7 +1643,7 @@ __global__ void __launch_bounds__(256) k_pre_cut_slots(PreArgs P, Shared sh) {
 // A cut grid triangle subdivided, on point numbers of three bits in packed words (the
 // boundary cycle, the faces) and the points' places in LDS: points, pieces and faces
 // in local arrays took 0.9 KB of scratch memory a lane and moved 3.5 GB through
-// memory for 2.3 M triangles (1.70 ms on the 8192 x 8192 image; this 0.42 ms).
+// memory for 2.3 M triangles (1.70 ms on the 8192 x 8192 image; this 0.44 ms).
 struct PreCutWork {
   uint32_t head, ends, tri[2];  // as in PreCut
   int32_t id[3], eo[3];
