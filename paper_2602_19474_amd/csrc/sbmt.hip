@@ -2859,7 +2859,6 @@ sbmt_status sbmt_pre_query(const sbmt_image* img, size_t* workspace_bytes, int64
   return SBMT_OK;
 }
 
-// Arguments of the preprocessing kernels over workspace w (layout PL).
 // What a plan leaves in its workspace (pre_planned): a word made of all that its
 // indices depend on, never 0, which is what the word is cleared to.
 constexpr int kPreStampWord = 2;  // of the call's eight counters (ctr), which k_coarsen clears; 1 is the persistent kernel's
@@ -2877,6 +2876,7 @@ static uint64_t pre_stamp(const Geo& g, double a, double b, double c) {
   }
   return s ? s : 1;
 }
+// Arguments of the preprocessing kernels over workspace w (layout PL).
 static PreArgs pre_args(const PreLayout& PL, char* w, double a, double b, double c) {
   PreArgs P;
   P.a = a;
