@@ -2859,22 +2859,18 @@ sbmt_status sbmt_pre_query(const sbmt_image* img, size_t* workspace_bytes, int64
   return SBMT_OK;
 }
 
-// What a plan leaves in its workspace (pre_planned): a word made of all that its
-// indices depend on, never 0, which is what the word is cleared to.
-constexpr int kPreStampWord = 2;  // of the call's eight counters (ctr), which k_coarsen clears; 1 is the persistent kernel's
-static uint64_t pre_stamp(const Geo& g, double a, double b, double c) {
-  uint64_t x[7] = {(uint64_t)(uint32_t)g.W | ((uint64_t)(uint32_t)g.H << 32), (uint64_t)(uint32_t)g.h | ((uint64_t)(uint32_t)g.q << 32),
-                   g.flags, 0x53424d5450524531ull, 0, 0, 0};
-  memcpy(x + 4, &a, 8);
-  memcpy(x + 5, &b, 8);
-  memcpy(x + 6, &c, 8);
-  uint64_t s = 0;
-  for (uint64_t v : x) {  // each word mixed in by two odd multiplications and shifts
-    s = (s ^ v) * 0x9e3779b97f4a7c15ull;
-    s = (s ^ (s >> 32)) * 0xd6e8feb86659fd93ull;
-    s ^= s >> 29;
-  }
-  return s ? s : 1;
+// What a plan leaves in its workspace (pre_planned): all that its indices depend on,
+// and a word that is not 0, to which k_coarsen clears every one.  They are the last
+// six of the call's eight counters (ctr), of which the persistent kernel uses the
+// second.
+static void pre_stamp(const Geo& g, double a, double b, double c, uint64_t (&s)[kPreStamp]) {
+  static_assert(kPreStamp == 6, "words 2 to 7 of ctr");
+  s[0] = 0x70726570726f6373ull;
+  s[1] = (uint64_t)(uint32_t)g.W | ((uint64_t)(uint32_t)g.H << 32);
+  s[2] = (uint64_t)(uint32_t)g.h | ((uint64_t)(uint32_t)g.q << 32) | ((uint64_t)g.flags << 48);
+  memcpy(&s[3], &a, 8);
+  memcpy(&s[4], &b, 8);
+  memcpy(&s[5], &c, 8);
 }
 // Arguments of the preprocessing kernels over workspace w (layout PL).
 static PreArgs pre_args(const PreLayout& PL, char* w, double a, double b, double c) {
@@ -2916,8 +2912,8 @@ static PreArgs pre_args(const PreLayout& PL, char* w, double a, double b, double
   P.citem = PL.off_citem ? (uint64_t*)(w + PL.off_citem) : nullptr;
   P.cstore = PL.off_cstore ? (PreCut*)(w + PL.off_cstore) : nullptr;
   P.ccap = PL.off_cstore ? PL.ccap : 0;
-  P.stamp_at = (uint64_t*)(w + PL.L.off_ctr) + kPreStampWord;
-  P.stamp = pre_stamp(PL.L.g[0], a, b, c);
+  P.stamp_at = (uint64_t*)(w + PL.L.off_ctr) + 2;
+  pre_stamp(PL.L.g[0], a, b, c, P.stamp);
   return P;
 }
 // Steps 1-3 (the grid, when `triangles` with every vertex and its triangles, else

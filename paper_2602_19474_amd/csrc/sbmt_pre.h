@@ -49,6 +49,7 @@ struct PreUsed {
   int32_t base, pad;
 };
 
+constexpr int kPreStamp = 6;  // words
 struct PreArgs {
   double a, b, c;
   double* verts;         // [NK NI + inserted][2]: lattice vertex k NI + i first (the mesh: moved and inserted ones only)
@@ -91,7 +92,7 @@ struct PreArgs {
   int64_t ccap;
   // the workspace's stamp: what a finished plan leaves there, and what this call's image and thresholds make it
   uint64_t* stamp_at;
-  uint64_t stamp;
+  uint64_t stamp[kPreStamp];
 };
 constexpr int kPreVScan = 16384;  // grid vertices per block of the compaction scan
 constexpr int kPreApplyWords = 16;  // words of 64 grid vertices per block that copies the used ones
@@ -99,11 +100,16 @@ static_assert(kPreVScan % (64 * kPreApplyWords) == 0, "in one block of the scan"
 // Whether the workspace holds the plan of this image size, edge and thresholds.
 // The passes that write the mesh follow indices and bounds from the workspace, so
 // each looks at this first: they must not run after a plan that failed, over
-// another image's, or over memory that was never planned.  The stamp is one of the
-// words that every call's k_coarsen clears, and the last pass of a plan without an
-// error sets it.  The passes take a count or a bound of 0 without it rather than
+// another image's, or over memory that was never planned.  The stamp is in words
+// that every call's k_coarsen clears, and the last pass of a plan without an error
+// sets it.  The passes take a count or a bound of 0 without it rather than
 // return, so that its load and the first ones of the pass wait together.
-__device__ __forceinline__ bool pre_planned(const PreArgs& P) { return *P.stamp_at == P.stamp; }
+__device__ __forceinline__ bool pre_planned(const PreArgs& P) {
+  uint64_t d = 0;
+#pragma unroll
+  for (int q = 0; q < kPreStamp; ++q) d |= P.stamp_at[q] ^ P.stamp[q];
+  return d == 0;
+}
 constexpr uint8_t kPreMoved = 8;
 constexpr int kPreTally = 8;
 constexpr int kPreCounts = kPreTally + 512;
@@ -2255,7 +2261,8 @@ __device__ __forceinline__ int64_t pre_mesh_status(const PreArgs& P, const Share
 }
 __global__ void __launch_bounds__(1024) k_pre_vscan_top(PreArgs P, Shared sh, int64_t nblk) {
   pre_scan_blocks(P.vbsum, nblk, P.nused);
-  if (threadIdx.x == 0 && pre_mesh_status(P, sh) == SBMT_OK) *P.stamp_at = P.stamp;
+  if (threadIdx.x == 0 && pre_mesh_status(P, sh) == SBMT_OK)
+    for (int q = 0; q < kPreStamp; ++q) P.stamp_at[q] = P.stamp[q];
 }
 __global__ void __launch_bounds__(256) k_pre_vscan_apply(OneSrc src, PreArgs P) {
   const Geo g = src.d.g;
