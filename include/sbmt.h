@@ -52,7 +52,7 @@
  *    default room for half of the owners, and for every owner up to 2^20
  *    (16 MB), so that calls of few tiles need no pass for owners without a
  *    record.  A workspace for an image is large enough for one that is no
- *    wider and no higher, too.
+ *    wider and no higher at the same grid_h, too.
  *
  * Errors
  *  - Every call returns an sbmt_status.  Arguments are validated before any
